@@ -34,7 +34,7 @@ SOURCES = [os.path.join(CSRC, n) for n in ("lbm_launch_f32.hip", "lbm_launch_f16
                                          "lbm_launch_f64.hip", "lbm_batch.hip", "lbm_api.hip",
                                          "lbm3d_launch_f64.hip", "lbm3d_launch_f32.hip", "lbm3d_launch_f16.hip",
                                          "lbm3d_launch_bf16.hip", "lbm3d_api.hip")]
-HEADERS = [os.path.join(CSRC, n) for n in ("lbm_device.hpp", "lbm_kernels.hpp", "lbm_params.hpp", "lbm_contact.hpp",
+HEADERS = [os.path.join(CSRC, n) for n in ("lbm_device.hpp", "lbm_kernels.hpp", "lbm_params.hpp", "lbm_regions.hpp", "lbm_contact.hpp",
                                             "lbm_launch.hpp", "lbm_launch_impl.hpp", "lbm3d_kernels.hpp",
                                             "lbm3d_contact.hpp", "lbm3d_launch.hpp", "lbm3d_launch_impl.hpp")] + \
     [os.path.join(ROOT, "include", "lbm.h"), os.path.join(ROOT, "include", "lbm3d.h")]

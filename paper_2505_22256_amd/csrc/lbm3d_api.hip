@@ -29,7 +29,6 @@ struct lbm3d_ctx {
     double *d_partials = nullptr;
     size_t partials_cap = 0;
     double *d_out = nullptr;  // 9 diagnostics + 7 contact-angle results
-    int *d_cc = nullptr;      // phase-region labels (2N + 2 ints)
     std::vector<uint8_t> solid;
     long long n_fluid = 0;
     double Gc = 0, Gw1 = 0, Gw2 = 0, delta = 0.8, tau = 1.0;
@@ -309,7 +308,7 @@ void lbm3d_destroy(lbm3d_ctx *c)
     if (!c) return;
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     for (void *p : {c->buf[0], c->buf[1], c->d_psi, (void *)c->d_solid, (void *)c->d_tmp, (void *)c->d_partials,
-                    (void *)c->d_out, (void *)c->d_cc})
+                    (void *)c->d_out})
         if (p) (void)hipFree(p);
     if (c->own_stream) (void)hipStreamDestroy(c->own_stream);
     delete c;
@@ -517,25 +516,18 @@ int lbm3d_contact_angle(lbm3d_ctx *c, int wall_kind, const double wall[4], doubl
         return fail(c, LBM_EINVAL, "bad wall description");
     rc = fields_reduce3(c);
     if (rc) return rc;
-    if (!c->d_cc && hipMalloc(&c->d_cc, ((size_t)c->N * 2 + 2) * sizeof(int)) != hipSuccess) {
-        c->d_cc = nullptr;
-        return fail(c, LBM_ENOMEM, "label allocation failed");
-    }
-    int *par = c->d_cc, *cnt = c->d_cc + c->N, *best = c->d_cc + 2 * c->N;
-    const double *r1 = c->d_tmp, *r2 = c->d_tmp + c->N;
-    long long bx = (c->N + 255) / 256;
-    if (bx > 4096) bx = 4096;
-    hipLaunchKernelGGL(k_cc3_init, dim3((unsigned)bx), dim3(256), 0, c->stream, c->N, c->d_solid, par, cnt);
-    hipLaunchKernelGGL(k_cc3_hook, dim3((unsigned)bx), dim3(256), 0, c->stream, c->nx, c->ny, c->nz, r1, r2, c->d_solid,
-                       par);
-    hipLaunchKernelGGL(k_cc3_count, dim3((unsigned)bx), dim3(256), 0, c->stream, c->N, c->d_solid, par, cnt);
-    hipLaunchKernelGGL(k_cc3_pick, dim3(1), dim3(256), 0, c->stream, c->N, r1, r2, c->d_solid, (const int *)par,
-                       (const int *)cnt, best);
     Wall3 wd;
     wd.kind = wall_kind;
     for (int q = 0; q < 4; ++q) wd.w[q] = wall[q];
-    hipLaunchKernelGGL(k_contact3, dim3(1), dim3(256), 0, c->stream, c->nx, c->ny, c->nz, r1, r2, c->d_solid,
-                       (const int *)par, (const int *)best, wd, c->d_out + 16);
+    const lbm::RunSet rs = {nullptr, nullptr, c->nx, c->ny, c->nz};
+    // labels and link list in the velocity part of the field staging
+    const lbm::RegionMem m = lbm::region_mem(c->d_tmp + 2 * c->N, c->N, 1, 3);
+    const double *r1 = c->d_tmp, *r2 = c->d_tmp + c->N;
+    const dim3 lg = lbm::link_grid(c->N, 1);
+    HIPCHK3(c, lbm::launch_regions(c->stream, rs, 1, c->N, r1, r2, c->d_solid, m));
+    hipLaunchKernelGGL(k_cc3_links, lg, dim3(256), 0, c->stream, rs, m, r1, r2, wd);
+    hipLaunchKernelGGL(lbm::k_cc_list<3>, lg, dim3(256), 0, c->stream, rs, m);
+    hipLaunchKernelGGL(k_contact3, dim3(1), dim3(1024), 0, c->stream, rs, m, (int)lg.x, r1, r2, wd, c->d_out + 16);
     HIPCHK3(c, hipGetLastError());
     double res[7];
     HIPCHK3(c, hipMemcpyAsync(res, c->d_out + 16, 7 * sizeof(double), hipMemcpyDeviceToHost, c->stream));

@@ -829,36 +829,21 @@ int lbm_contact_angle(lbm_ctx *c, int wall_kind, const double wall[3], double *t
         return set_err(c, LBM_EINVAL, "bad wall description");
     rc = fields_and_reduce(c);
     if (rc) return rc;
-    int dims_h[2] = {c->nx, c->ny};
-    long long off_h = 0;
-    WallDesc wd = {wall_kind, wall[0], wall[1], wall[2]};
-    // small argument block placed after the 4 field arrays would need more
-    // staging; use a dedicated tiny allocation instead
-    struct Args {
-        int dims[2];
-        long long off;
-        WallDesc wd;
-    } args_h = {{dims_h[0], dims_h[1]}, off_h, wd};
-    Args *d_args = nullptr;
-    HIPCHK(c, hipMalloc(&d_args, sizeof(Args)));
-    // region labels in the velocity half of the field staging (2N doubles
-    // hold 2N + 2 ints): parents, region sizes, the two chosen roots
-    int *par = (int *)(c->d_tmp + 2 * c->N), *cnt = par + c->N, *best = cnt + c->N;
-    hipError_t e = hipMemcpyAsync(d_args, &args_h, sizeof(Args), hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess)
-        e = launch_phase_regions(c->stream, (const int *)d_args->dims, (const long long *)&d_args->off, 1,
-                                 (long long)c->N, c->d_tmp, c->d_tmp + c->N, c->d_solid, par, cnt, best);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_contact_angle, dim3(1), dim3(256), 0, c->stream, (const int *)d_args->dims,
-                           (const long long *)&d_args->off, c->d_tmp, c->d_tmp + c->N, c->d_solid,
-                           (const int *)par, (const int *)best, (const WallDesc *)&d_args->wd, c->d_out + 8);
-        e = hipGetLastError();
-    }
+    const WallDesc wd = {wall_kind, wall[0], wall[1], wall[2]};
+    const RunSet rs = {nullptr, nullptr, c->nx, c->ny, 1};
+    // labels and link list in the velocity half of the field staging
+    const RegionMem m = region_mem(c->d_tmp + 2 * c->N, c->N, 1, 2);
+    const double *r1 = c->d_tmp, *r2 = c->d_tmp + c->N;
+    const dim3 lg = link_grid(c->N, 1);
+    HIPCHK(c, launch_regions(c->stream, rs, 1, c->N, r1, r2, c->d_solid, m));
+    hipLaunchKernelGGL(k_cc_links, lg, dim3(256), 0, c->stream, rs, m, r1, r2, (const WallDesc *)nullptr, wd);
+    hipLaunchKernelGGL(k_cc_list<2>, lg, dim3(256), 0, c->stream, rs, m);
+    hipLaunchKernelGGL(k_contact_angle, dim3(1), dim3(256), 0, c->stream, rs, m, (int)lg.x, r1, r2,
+                       (const WallDesc *)nullptr, wd, c->d_out + 8);
+    HIPCHK(c, hipGetLastError());
     double res[6] = {0, 0, 0, 0, 0, 0};
-    if (e == hipSuccess) e = hipMemcpyAsync(res, c->d_out + 8, 6 * sizeof(double), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    (void)hipFree(d_args);
-    if (e != hipSuccess) return set_err(c, LBM_EDEVICE, "contact angle failed: %s", hipGetErrorString(e));
+    HIPCHK(c, hipMemcpyAsync(res, c->d_out + 8, 6 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     if (res[5] == 1.0) return set_err(c, LBM_EUNSTABLE, "fewer than 3 interface points");
     if (res[5] != 0.0) return set_err(c, LBM_EUNSTABLE, "circle fit failed");
     *theta_deg = res[0];
