@@ -301,8 +301,10 @@ int lbm_set_stream(lbm_ctx *c, void *hip_stream);
  * seg_rows 32, LBM_SCHED_TWO_STEP | LBM_SCHED_BANDS, except that with
  * LBM_INLET or LBM_OUTFLOW BF16, and FP16 with stochastic rounding (its
  * default), take block 128, seg_rows 16, LBM_SCHED_BANDS; FP64 block 64,
- * seg_rows 48, LBM_SCHED_TWO_STEP | LBM_SCHED_BANDS.  Results do not
- * depend on the tile shape (bitwise).  sched bits: LBM_SCHED_ALIGN makes
+ * seg_rows 48, LBM_SCHED_TWO_STEP | LBM_SCHED_BANDS.  Until a tile is set
+ * or tuned, lattices too small to fill the GPU with strips (up to 851 968
+ * nodes in FP32, 1 179 648 otherwise) run in bricks of several fused steps
+ * instead.  Results do not depend on the tile shape, nor on bricks (bitwise).  sched bits: LBM_SCHED_ALIGN makes
  * strips a multiple of 128 bytes wide from x = 0, so that stores never
  * cover part of a cache line shared with another workgroup;
  * LBM_SCHED_BANDS (fixed segments only) runs units across the strips
@@ -318,7 +320,7 @@ int lbm_set_stream(lbm_ctx *c, void *hip_stream);
  * when diagnostics are due every step) runs alone.  Populations are
  * bitwise those of single steps; diagnostics agree to rounding (the sums
  * run in another order).  lbm_autotune times the
- * current tile and then every candidate for `steps` steps each on the
+ * current tile (or the bricks) and then every candidate for `steps` steps each on the
  * current state (restoring state and time afterwards); a candidate replaces
  * the best so far only when it is at least 2 % faster, so timing noise does
  * not move the choice between near-equal tiles.  LBM_SCHED_REPULL (with

@@ -30,12 +30,16 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "liblbm.so")
 BUILD_DIR = os.path.join(PKG, "_build")
 # the longest units first, so that the parallel build ends soonest
-SOURCES = [os.path.join(CSRC, n) for n in ("lbm_launch_f32.hip", "lbm_launch_f16.hip", "lbm_launch_bf16.hip",
-                                         "lbm_launch_f64.hip", "lbm_batch.hip", "lbm_api.hip",
-                                         "lbm3d_launch_f64.hip", "lbm3d_launch_f32.hip", "lbm3d_launch_f16.hip",
+SOURCES = [os.path.join(CSRC, n) for n in ("lbm_launch_f16.hip", "lbm_launch_bf16.hip", "lbm_launch_f16_bnd.hip",
+                                         "lbm_launch_bf16_bnd.hip", "lbm_batch.hip", "lbm_launch_f32.hip",
+                                         "lbm_launch_f64.hip", "lbm_launch_f32_bnd.hip", "lbm_launch_f64_bnd.hip",
+                                         "lbm_api.hip",
+                                         "lbm_brick_f16.hip", "lbm_brick_bf16.hip", "lbm_brick_f32.hip",
+                                         "lbm_brick_f64.hip", "lbm3d_launch_f64.hip", "lbm3d_launch_f32.hip", "lbm3d_launch_f16.hip",
                                          "lbm3d_launch_bf16.hip", "lbm3d_api.hip")]
 HEADERS = [os.path.join(CSRC, n) for n in ("lbm_device.hpp", "lbm_kernels.hpp", "lbm_params.hpp", "lbm_regions.hpp", "lbm_contact.hpp",
-                                            "lbm_launch.hpp", "lbm_launch_impl.hpp", "lbm3d_kernels.hpp",
+                                            "lbm_launch.hpp", "lbm_launch_impl.hpp", "lbm_brick.hpp",
+                                            "lbm_brick_impl.hpp", "lbm3d_kernels.hpp",
                                             "lbm3d_contact.hpp", "lbm3d_launch.hpp", "lbm3d_launch_impl.hpp")] + \
     [os.path.join(ROOT, "include", "lbm.h"), os.path.join(ROOT, "include", "lbm3d.h")]
 

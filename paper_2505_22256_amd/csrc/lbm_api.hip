@@ -49,6 +49,7 @@ struct lbm_ctx {
     long t = 0;
     int block = 256, seg_rows = 0;
     unsigned sched = 0;
+    bool own_tile = false;  // set by lbm_set_tile or chosen by lbm_autotune
     int diag_every = 0;
     int cus = 0;
     long diag_t = -1;
@@ -148,15 +149,65 @@ bool boundary_steps(const lbm_ctx *c)
 int grid_of(int strips, int segs) { return ((strips * segs + 7) / 8) * 8; }
 
 
-// Workgroups of the step kernel that fit on the device at once.
-template <int S>
-int resident_capacity(lbm_ctx *c, int block)
+int compute_units(lbm_ctx *c)
 {
     if (c->cus <= 0) {
         hipDeviceProp_t prop;
         c->cus = (hipGetDeviceProperties(&prop, c->device) == hipSuccess) ? prop.multiProcessorCount : 256;
     }
-    return step_occupancy<S>(block) * c->cus;
+    return c->cus;
+}
+
+// Workgroups of the step kernel that fit on the device at once.
+template <int S>
+int resident_capacity(lbm_ctx *c, int block)
+{
+    return step_occupancy<S>(block) * compute_units(c);
+}
+
+// Bricks (lbm_brick.hpp) for the steps of this lattice: the region and the
+// steps per launch, or no steps where marching strips is faster.  A tile
+// that the caller has set or tuned always marches.
+//
+// The line: a lattice stops being a latency chain when the strips fill the
+// chip.  Cylinder lattices, us per step marching / in bricks, one lattice on
+// the GPU: FP32 100 x 50 28.6 / 3.6, 400 x 400 64.8 / 7.9, 1000 x 800 71 / 22,
+// 1200 x 1000 75 / 31; three lattices stepped at the same time (per lattice):
+// 10.3 / 1.7, 23.3 / 5.6, 28.1 / 27.5, 30.7 / 41.2.  With three the chip is
+// full and the strips' smaller halo wins past 850 000 nodes in FP32; FP16
+// crosses between 1.2 M (38.8 / 27.0) and 2.1 M nodes (45.5 / 57.5), FP64
+// after 1.2 M (68.5 / 63.9, 2.1 M: 85 / 110).
+//
+// Steps per launch: while the bricks fit the chip's compute units once, a
+// deeper halo costs only idle units, so the largest region takes the most
+// steps that still fit (FP32 100 x 50: 4 steps 3.6, 2 steps 4.4, 1 step 6.7;
+// 200 x 200: 3 steps 5.3, 2 6.5, 4 7.0, where 400 bricks no longer fit).
+// Past that FP32 and the 16-bit storages take single steps in 32 x 16
+// regions, which finish 66 % of their nodes (400 x 400 FP32: 7.9 against 8.7
+// for two steps in 32 x 32; FP16 8.6 against 10.2); FP64, whose pulls are
+// twice as long, and the boundary instances take two steps in 32 x 32
+// (720 x 700 FP64 28.7 against 29.7, 26.6 against 30.2 with three lattices;
+// 700 x 300 with open edges, FP32 13.2 against 15.2).  The FP64 boundary
+// instance has no registers for 32 x 32 (204 B per lane spilled) and stays
+// in 32 x 16 (700 x 300: 22.0 against 28.3).
+struct BrickPlan {
+    int region, steps;
+};
+
+BrickPlan brick_plan(lbm_ctx *c)
+{
+    const long long most = (c->storage == LBM_F32 ? 13LL : 18LL) << 16;
+    if (c->own_tile || c->N > most) return {0, 0};
+    const int cus = compute_units(c);
+    auto fits = [&](int region, int steps) {
+        const int w = brick_core(brick_rx(region), steps), h = brick_core(brick_ry(region), steps);
+        return (long long)((c->nx + w - 1) / w) * ((c->ny + h - 1) / h) <= cus;
+    };
+    const bool bnd = boundary_steps(c);
+    if (c->storage == LBM_F64 && bnd) return {1, fits(1, 2) ? 2 : 1};
+    for (int k = 4; k > 1; --k)
+        if (fits(2, k)) return {2, k};
+    return c->storage == LBM_F64 || bnd ? BrickPlan{2, 2} : BrickPlan{1, 1};
 }
 
 // Launch one pass reading buf[cur].  P_STEP* write buf[cur^1] (the caller
@@ -266,6 +317,28 @@ int pull_window(lbm_ctx *c, int x0, int y0, int w, int h, double *out)
     case LBM_F32: return pull_window_t<ST_F32>(c, x0, y0, w, h, out);
     case LBM_F16: return pull_window_t<ST_F16>(c, x0, y0, w, h, out);
     default: return pull_window_t<ST_BF16>(c, x0, y0, w, h, out);
+    }
+}
+
+// One launch of the brick kernel: `steps` steps from buf[cur] to buf[cur ^ 1].
+template <int S>
+int run_bricks_t(lbm_ctx *c, int region, int steps)
+{
+    using C = typename Traits<S>::C;
+    const KParams<C> p = make_params<C>(c, c->buf[c->cur], c->buf[c->cur ^ 1], 256, 64);
+    const bool sr = (S == ST_F16 || S == ST_BF16) && (c->flags & LBM_ROUND_STOCHASTIC);
+    const hipError_t e = launch_brick<S>(p, region, steps, sr, boundary_steps(c), c->stream);
+    if (e != hipSuccess) return set_err(c, LBM_EDEVICE, "kernel launch failed: %s", hipGetErrorString(e));
+    return LBM_OK;
+}
+
+int run_bricks(lbm_ctx *c, int region, int steps)
+{
+    switch (c->storage) {
+    case LBM_F64: return run_bricks_t<ST_F64>(c, region, steps);
+    case LBM_F32: return run_bricks_t<ST_F32>(c, region, steps);
+    case LBM_F16: return run_bricks_t<ST_F16>(c, region, steps);
+    default: return run_bricks_t<ST_BF16>(c, region, steps);
     }
 }
 
@@ -721,11 +794,24 @@ int lbm_step(lbm_ctx *c, int n)
     int rc = ready(c);
     if (rc) return rc;
     if (n < 0) return set_err(c, LBM_EINVAL, "negative step count");
-    const bool two = (c->sched & SCHED_TWO_STEP) != 0;
+    const BrickPlan plan = brick_plan(c);
+    const bool two = (c->sched & SCHED_TWO_STEP) != 0 && !plan.steps;
     for (int s = 0; s < n; ++s) {
         const bool diag_now = c->diag_every > 0 && c->t % c->diag_every == 0;
         const bool diag_next = c->diag_every > 0 && (c->t + 1) % c->diag_every == 0;
         const bool alone = c->fresh && boundary_steps(c);
+        if (plan.steps && !diag_now) {
+            // as many steps as the plan's bricks take, up to the next record
+            long k = alone ? 1 : std::min(plan.steps, n - s);
+            if (c->diag_every > 0) k = std::min(k, c->diag_every - c->t % c->diag_every);
+            rc = run_bricks(c, plan.region, (int)k);
+            if (rc) return rc;
+            c->cur ^= 1;
+            c->t += k;
+            c->fresh = false;
+            s += (int)k - 1;
+            continue;
+        }
         if (two && !alone && !(diag_now && diag_next) && n - s >= 2) {
             // two fused steps, recording the diagnostics of whichever of
             // them is due
@@ -899,6 +985,7 @@ int lbm_set_tile(lbm_ctx *c, int block, int seg_rows, unsigned sched)
     c->block = block;
     c->seg_rows = seg_rows;
     c->sched = sched;
+    c->own_tile = true;
     return LBM_OK;
 }
 
@@ -930,6 +1017,8 @@ int lbm_autotune(lbm_ctx *c, int steps)
     const int rows[10] = {0, 8, 16, 24, 32, 48, 64, 128, 256, 512};
     const int cur_b = c->block, cur_r = c->seg_rows;
     const unsigned cur_s = c->sched;
+    const bool cur_own = c->own_tile;
+    bool best_own = cur_own;
     int best_b = cur_b, best_r = cur_r;
     unsigned best_s = cur_s;
     float best_ms = 1e30f;
@@ -954,6 +1043,7 @@ int lbm_autotune(lbm_ctx *c, int steps)
         c->block = cb;
         c->seg_rows = cr;
         c->sched = sc;
+        c->own_tile = cand >= 0 || cur_own;
         rc = lbm_step(c, 1);  // warm-up
         if (rc) break;
         e = hipEventRecord(ev0, c->stream);
@@ -969,6 +1059,7 @@ int lbm_autotune(lbm_ctx *c, int steps)
             best_b = cb;
             best_r = cr;
             best_s = sc;
+            best_own = cand >= 0 || cur_own;
         }
     }
     if (e == hipSuccess) e = hipMemcpyAsync(c->buf[cur0], backup, bytes, hipMemcpyDeviceToDevice, c->stream);
@@ -983,6 +1074,7 @@ int lbm_autotune(lbm_ctx *c, int steps)
     c->block = best_b;
     c->seg_rows = best_r;
     c->sched = best_s;
+    c->own_tile = best_own;
     if (rc) return rc;
     if (e != hipSuccess) return set_err(c, LBM_EDEVICE, "autotune failed: %s", hipGetErrorString(e));
     return LBM_OK;

@@ -1,0 +1,6 @@
+// Brick kernel instances for BF16 storage (see lbm_launch.hpp).
+#include "lbm_brick_impl.hpp"
+
+namespace lbm_host {
+template hipError_t launch_brick<lbm::ST_BF16>(lbm::KParams<float>, int, int, bool, bool, hipStream_t);
+}  // namespace lbm_host

@@ -281,11 +281,17 @@ __device__ __forceinline__ void issue_row(const KParams<typename Traits<S>::C> &
     issue_node<S>(m, p.nx, cx, ry, col_ok && ry.ok, q);
 }
 
-// Bulk cohesion sums straight from the LDS ring, pair by pair (the same
-// order and operations as cohesion_sums on a gathered stencil).
-template <class C, int BLOCK, int RS = 8>
-__device__ __forceinline__ void cohesion_sums_lds(PsiPair<C> (*ring)[BLOCK], int y, int tid, C &s1x, C &s1y, C &s2x,
-                                                  C &s2y)
+// psi around the node at (row y, lane tid) of an LDS ring of rows.
+template <class C, int BLOCK, int RS> struct RingPsi {
+    PsiPair<C> (*ring)[BLOCK];
+    int y, tid;
+    __device__ __forceinline__ PsiPair<C> at(int dx, int dy) const { return ring[ring_slot<RS>(y + dy)][tid + dx]; }
+};
+
+// Bulk cohesion sums straight from LDS, pair by pair (the same order and
+// operations as cohesion_sums on a gathered stencil).
+template <class C, class Psi>
+__device__ __forceinline__ void cohesion_sums_lds(const Psi &psi, C &s1x, C &s1y, C &s2x, C &s2y)
 {
     s1x = 0; s1y = 0; s2x = 0; s2y = 0;
 #pragma unroll
@@ -293,8 +299,8 @@ __device__ __forceinline__ void cohesion_sums_lds(PsiPair<C> (*ring)[BLOCK], int
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int n = 4 * g + h, o = n + 2;
-            const PsiPair<C> a = ring[ring_slot<RS>(y + sy(n))][tid + sx(n)];
-            const PsiPair<C> b = ring[ring_slot<RS>(y + sy(o))][tid + sx(o)];
+            const PsiPair<C> a = psi.at(sx(n), sy(n));
+            const PsiPair<C> b = psi.at(sx(o), sy(o));
             const C cx = (C)(e8wn(n) * sx(n));
             const C cy = (C)(e8wn(n) * sy(n));
             const C d1 = a.a - b.a;
@@ -305,17 +311,17 @@ __device__ __forceinline__ void cohesion_sums_lds(PsiPair<C> (*ring)[BLOCK], int
     }
 }
 
-// Lane of stencil position n, or of its ghost when the position lies
-// beyond an open x edge (left of the inlet, right of the outflow): the node
-// of the same row clamped into the domain.  `open` says which.
+// Column offset of stencil position n, or of its ghost when the position
+// lies beyond an open x edge (left of the inlet, right of the outflow): the
+// node of the same row clamped into the domain.  `open` says which.
 template <bool BND>
-__device__ __forceinline__ int stencil_lane(int n, int tid, int col, int nx, unsigned flags, bool &open)
+__device__ __forceinline__ int stencil_dx(int n, int col, int nx, unsigned flags, bool &open)
 {
     open = false;
-    if constexpr (!BND) return tid + sx(n);
+    if constexpr (!BND) return sx(n);
     const int pc = col + sx(n);
     open = ((flags & FL_INLET) && pc < 0) || ((flags & FL_OUTFLOW) && pc >= nx);
-    return tid + sx(n) + (!open ? 0 : pc < 0 ? -pc : nx - 1 - pc);
+    return sx(n) + (!open ? 0 : pc < 0 ? -pc : nx - 1 - pc);
 }
 
 // Stencil value at position n after the wall rules of Sec. 2.4 / Table 1,
@@ -326,13 +332,13 @@ __device__ __forceinline__ int stencil_lane(int n, int tid, int col, int nx, uns
 // position reads its ghost (when fluid) and a second-layer one takes the
 // Table 1 copy.  `solid` is the switch s of Eq. 9 at the position (beyond
 // an open edge: at its ghost).  Same rules as apply_wall_rules.
-template <class C, int BLOCK, int RS, bool BND>
-__device__ __forceinline__ PsiPair<C> resolve_position(PsiPair<C> (*vr)[BLOCK], int n, int y, int tid,
-                                                       int col, int nx, C r1, C r2, unsigned flags, bool &solid)
+template <class C, bool BND, class Psi>
+__device__ __forceinline__ PsiPair<C> resolve_position(const Psi &psi, int n, int col, int nx, C r1, C r2,
+                                                       unsigned flags, bool &solid)
 {
     bool open;
-    const int lane = stencil_lane<BND>(n, tid, col, nx, flags, open);
-    const PsiPair<C> v = vr[ring_slot<RS>(y + sy(n))][lane];
+    const int dx = stencil_dx<BND>(n, col, nx, flags, open);
+    const PsiPair<C> v = psi.at(dx, sy(n));
     solid = lds_sent(v.a);
     if (!solid && (!open || n < 8)) return v;
     PsiPair<C> self, zero;
@@ -345,17 +351,17 @@ __device__ __forceinline__ PsiPair<C> resolve_position(PsiPair<C> (*vr)[BLOCK], 
     if (flags & FL_COPY_OFF) return zero;
     const int m = table1(n);
     bool open_m;
-    const int lane_m = stencil_lane<BND>(m, tid, col, nx, flags, open_m);
-    const PsiPair<C> w = vr[ring_slot<RS>(y + sy(m))][lane_m];
+    const int dx_m = stencil_dx<BND>(m, col, nx, flags, open_m);
+    const PsiPair<C> w = psi.at(dx_m, sy(m));
     return lds_sent(w.a) ? first_rule : w;
 }
 
 // Cohesion and adhesion sums at a node with unavailable stencil positions:
 // the same pair order as cohesion_sums / adhesion_vector, positions
 // resolved by the wall rules, S(x) from the solid switches.
-template <class C, int BLOCK, int RS, bool BND>
-__device__ __forceinline__ void wall_sums(PsiPair<C> (*vr)[BLOCK], int y, int tid, int col, int nx, C r1, C r2,
-                                          unsigned flags, C &s1x, C &s1y, C &s2x, C &s2y, C &Sx, C &Sy)
+template <class C, bool BND, class Psi>
+__device__ __forceinline__ void wall_sums(const Psi &psi, int col, int nx, C r1, C r2, unsigned flags, C &s1x, C &s1y,
+                                          C &s2x, C &s2y, C &Sx, C &Sy)
 {
     // read the stencil afresh rather than keeping the bulk path's values
     // alive across the branch (a compiler-only memory clobber, no code)
@@ -368,8 +374,8 @@ __device__ __forceinline__ void wall_sums(PsiPair<C> (*vr)[BLOCK], int y, int ti
         for (int h = 0; h < 2; ++h) {
             const int n = 4 * g + h, o = n + 2;
             bool un, uo;
-            const PsiPair<C> a = resolve_position<C, BLOCK, RS, BND>(vr, n, y, tid, col, nx, r1, r2, flags, un);
-            const PsiPair<C> b = resolve_position<C, BLOCK, RS, BND>(vr, o, y, tid, col, nx, r1, r2, flags, uo);
+            const PsiPair<C> a = resolve_position<C, BND>(psi, n, col, nx, r1, r2, flags, un);
+            const PsiPair<C> b = resolve_position<C, BND>(psi, o, col, nx, r1, r2, flags, uo);
             const C cx = (C)(e8wn(n) * sx(n));
             const C cy = (C)(e8wn(n) * sy(n));
             const C d1 = a.a - b.a;
@@ -381,34 +387,63 @@ __device__ __forceinline__ void wall_sums(PsiPair<C> (*vr)[BLOCK], int y, int ti
     }
 }
 
-// Finish node (x, y) of an interior column: stencil, forces, velocity,
-// collision and the selected outputs.
-template <int S, int BLOCK, int MODE, int RS = 8, class St>
-__device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C> &p, const PopMem<S> &mw,
-                                            const Axis &cx, int y, int yw, const St &st,
-                                            PsiPair<typename Traits<S>::C> (*ring)[BLOCK], RedAcc &acc,
-                                            FRingMem<S, BLOCK> *fring = nullptr, unsigned dtick = 0,
-                                            FPending<S> *pend = nullptr, bool count = true)
+// Where finish_node's results go: HBM, or the LDS ring of the first of two
+// fused steps (the values held until the second step has read the row
+// before stay in `pend`).
+template <int S> struct GlobalOut {
+    const PopMem<S> &mw;
+    uint32_t voff;  // byte offset of the node
+    __device__ __forceinline__ void solid() const {}
+    __device__ __forceinline__ void put(const typename Traits<S>::raw_t (&out)[2][9]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            pop_store<S>(mw, 0, i, voff, out[0][i]);
+            pop_store<S>(mw, 1, i, voff, out[1][i]);
+        }
+    }
+};
+template <int S, int BLOCK> struct RingOut {
+    FRingMem<S, BLOCK> *fring;
+    FPending<S> *pend;
+    int y, tid;
+    __device__ __forceinline__ void set(int k, int i, typename Traits<S>::raw_t v) const
+    {
+        if (qy(i) < 0) fr_at<S, BLOCK>(fring, k, i, y, tid) = v;
+        else if (qy(i) == 0) pend->h[k][fr_gidx(i)] = v;
+        else pend->u[k][fr_gidx(i)] = v;
+    }
+    __device__ __forceinline__ void solid() const
+    {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int i = 0; i < 9; ++i) set(k, i, Traits<S>::sentinel());
+    }
+    __device__ __forceinline__ void put(const typename Traits<S>::raw_t (&out)[2][9]) const
+    {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int i = 0; i < 9; ++i) set(k, i, out[k][i]);
+    }
+};
+
+// Finish the node in column cx: stencil, forces, velocity, collision and the
+// selected outputs.  y is its row as the stencil counts (it may lie outside
+// the lattice in a halo of fused steps), yw the lattice row after wrapping.
+template <int S, int MODE, class St, class Psi, class Out>
+__device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C> &p, const Axis &cx, int y, int yw,
+                                            const St &st, const Psi &psi, const Out &sink, RedAcc &acc,
+                                            unsigned dtick = 0, bool count = true)
 {
     using T = Traits<S>;
     using C = typename T::C;
     using R = typename T::raw_t;
-    // y numbers the LDS ring rows (it may lie outside the lattice in a halo
-    // of the fused two-step kernel); yw is the lattice row after wrapping
     const int node = yw * p.nx + cx.c;
-    const int tid = threadIdx.x;
 
     if (st.info & 256) {  // solid node (or outside the domain)
-        if constexpr (MODE & M_LDS) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-#pragma unroll
-                for (int i = 0; i < 9; ++i) {
-                    if (qy(i) < 0) fr_at<S, BLOCK>(fring, k, i, y, tid) = T::sentinel();
-                    else if (qy(i) == 0) pend->h[k][fr_gidx(i)] = T::sentinel();
-                    else pend->u[k][fr_gidx(i)] = T::sentinel();
-                }
-        }
+        if (MODE & M_STORE) sink.solid();
         if (MODE & M_FIELDS) {
             p.out_rho1[node] = 0.0;
             p.out_rho2[node] = 0.0;
@@ -422,7 +457,7 @@ __device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C>
         return;
     }
 
-    const PsiPair<C> ctr = ring[ring_slot<RS>(y)][tid];
+    const PsiPair<C> ctr = psi.at(0, 0);
     const C r1 = ctr.a, r2 = ctr.b;
 
     // first moments j_k = sum_i f_i e_i (Eq. 4), definition order; the
@@ -449,18 +484,17 @@ __device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C>
     // E8 cohesion sums (Eq. 8); a sentinel (unavailable position) turns
     // them into NaN and selects the wall path
     C s1x, s1y, s2x, s2y;
-    cohesion_sums_lds<C, BLOCK, RS>(ring, y, tid, s1x, s1y, s2x, s2y);
+    cohesion_sums_lds<C>(psi, s1x, s1y, s2x, s2y);
     C Sx = 0, Sy = 0;
     const bool near = __builtin_isnan(s1x + s1y + s2x + s2y);
     if (near) {
-        wall_sums<C, BLOCK, RS, (MODE & M_BND) != 0>(ring, y, tid, cx.c, p.nx, r1, r2, p.flags, s1x, s1y, s2x, s2y,
-                                                    Sx, Sy);
+        wall_sums<C, (MODE & M_BND) != 0>(psi, cx.c, p.nx, r1, r2, p.flags, s1x, s1y, s2x, s2y, Sx, Sy);
     }
 
     if (MODE & M_TABLES) {
         uint32_t unav = 0;
 #pragma unroll
-        for (int n = 0; n < 24; ++n) unav |= (uint32_t)lds_sent(ring[ring_slot<RS>(y + sy(n))][tid + sx(n)].a) << n;
+        for (int n = 0; n < 24; ++n) unav |= (uint32_t)lds_sent(psi.at(sx(n), sy(n)).a) << n;
         p.tab_link[node] = (uint8_t)(st.info & 255);
         p.tab_nw[node] = unav ? 1 : 0;
         if (unav) {
@@ -472,8 +506,8 @@ __device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C>
                 const Axis ay = make_axis(y + sy(n), p.ny, p.flags & FL_PERIODIC_Y);
                 idx[n] = (ax.ok && ay.ok) ? ay.c * p.nx + ax.c : -1;
                 bool open;
-                const int gl = stencil_lane<(MODE & M_BND) != 0>(n, tid, cx.c, p.nx, p.flags, open);
-                if (open && n < 8 && ay.ok && !lds_sent(ring[ring_slot<RS>(y + sy(n))][gl].a)) {
+                const int gdx = stencil_dx<(MODE & M_BND) != 0>(n, cx.c, p.nx, p.flags, open);
+                if (open && n < 8 && ay.ok && !lds_sent(psi.at(gdx, sy(n)).a)) {
                     // first layer beyond an open edge: the fluid ghost
                     idx[n] = ay.c * p.nx + (cx.c + sx(n) < 0 ? 0 : p.nx - 1);
                     rule &= ~(1u << n);
@@ -564,7 +598,6 @@ __device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C>
         }
         constexpr bool sr = (S == ST_F16 || S == ST_BF16) && (MODE & M_SR);
         uint32_t rs = sr ? sr_seed(node, p.tick + dtick) : 1u;
-        const uint32_t voff = (uint32_t)node * (uint32_t)sizeof(R);
         C gs[2][9];
 #pragma unroll
         for (int k = 0; k < 2; ++k) gs[k][0] = p.omw * st.get(k, 0) + (C)qw(0) * c0[k];
@@ -604,22 +637,7 @@ __device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C>
                 out[1][i] = T::enc(gs[1][i]);
             }
         }
-        if constexpr (MODE & M_LDS) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-#pragma unroll
-                for (int i = 0; i < 9; ++i) {
-                    if (qy(i) < 0) fr_at<S, BLOCK>(fring, k, i, y, tid) = out[k][i];
-                    else if (qy(i) == 0) pend->h[k][fr_gidx(i)] = out[k][i];
-                    else pend->u[k][fr_gidx(i)] = out[k][i];
-                }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                pop_store<S>(mw, 0, i, voff, out[0][i]);
-                pop_store<S>(mw, 1, i, voff, out[1][i]);
-            }
-        }
+        sink.put(out);
     }
 }
 
@@ -712,6 +730,11 @@ __device__ __forceinline__ void process_segment(const KParams<typename Traits<S>
     const bool col_ok = active && cx.ok;
     const int last = y1 + 1;  // last row whose psi is needed
 
+    auto finish = [&](int y, const StateOf<S, BND> &st) {
+        const GlobalOut<S> sink{mw, (uint32_t)(y * p.nx + cx.c) * (uint32_t)sizeof(typename Traits<S>::raw_t)};
+        finish_node<S, MODE>(p, cx, y, y, st, RingPsi<C, BLOCK, 8>{ring, y, tid}, sink, acc);
+    };
+
     StateOf<S, BND> ra, rb, rc;
     RawRow<S> q;
     issue_row<S>(p, mr, cx, col_ok, y0 - 2, q);
@@ -729,19 +752,19 @@ __device__ __forceinline__ void process_segment(const KParams<typename Traits<S>
         process_row<S, BLOCK, 8, BND>(p, mr, cx, col_ok, y + 2, q, ring, rc);
         if (y + 3 <= last) issue_row<S>(p, mr, cx, col_ok, y + 3, q);
         __syncthreads();
-        if (interior) finish_node<S, BLOCK, MODE>(p, mw, cx, y, y, ra, ring, acc);
+        if (interior) finish(y, ra);
         ++y;
         if (y >= y1) break;
         process_row<S, BLOCK, 8, BND>(p, mr, cx, col_ok, y + 2, q, ring, ra);
         if (y + 3 <= last) issue_row<S>(p, mr, cx, col_ok, y + 3, q);
         __syncthreads();
-        if (interior) finish_node<S, BLOCK, MODE>(p, mw, cx, y, y, rb, ring, acc);
+        if (interior) finish(y, rb);
         ++y;
         if (y >= y1) break;
         process_row<S, BLOCK, 8, BND>(p, mr, cx, col_ok, y + 2, q, ring, rb);
         if (y + 3 <= last) issue_row<S>(p, mr, cx, col_ok, y + 3, q);
         __syncthreads();
-        if (interior) finish_node<S, BLOCK, MODE>(p, mw, cx, y, y, rc, ring, acc);
+        if (interior) finish(y, rc);
         ++y;
     }
 }
@@ -752,38 +775,37 @@ __device__ __forceinline__ void process_segment(const KParams<typename Traits<S>
 // band_order the units of a fixed-segment tiling are taken across the
 // strips first, so that workgroups running at the same time cover whole
 // rows of the lattice.
+// One call of `seg` in the code (inlined, it is most of a kernel; with a call
+// per schedule the two-step kernels were three times as long, up to 370 KB,
+// and the long branches and spilled scalars of the FP64 boundary instances
+// went with wrong results): every schedule gives a first strip and row and
+// a number of strip-major rows.
 template <class Seg>
 __device__ __forceinline__ void for_unit_segments(int n_strips, int n_segs, int ny, int xcd_slabs, int band_order,
                                                   int u, int n_units, Seg &&seg)
 {
-    if (xcd_slabs) {
-        // workgroup b runs on XCD b % 8: slab b % 8 of the rows, strip b / 8
-        const int strip = u >> 3, slab = u & 7;
-        const int y0 = (int)(((long long)slab * ny) >> 3);
-        const int y1 = (int)(((long long)(slab + 1) * ny) >> 3);
-        if (strip < n_strips && y1 > y0) seg(strip, y0, y1);
-        return;
+    int strip, y0;
+    long long left;
+    if (xcd_slabs || (band_order && n_units == n_strips * n_segs)) {
+        // slabs: workgroup b runs on XCD b % 8: slab b % 8 of the rows, strip b / 8
+        strip = xcd_slabs ? u >> 3 : u % n_strips;
+        const int sg = xcd_slabs ? u & 7 : u / n_strips, n = xcd_slabs ? 8 : n_segs;
+        y0 = (int)(((long long)sg * ny) / n);
+        left = strip < n_strips ? (int)(((long long)(sg + 1) * ny) / n) - y0 : 0;
+    } else {
+        const long long R = (long long)n_strips * ny;
+        const long long q0 = (long long)u * R / n_units;
+        left = (long long)(u + 1) * R / n_units - q0;
+        strip = (int)(q0 / ny);
+        y0 = (int)(q0 - (long long)strip * ny);
     }
-    if (band_order && n_units == n_strips * n_segs) {
-        const int strip = u % n_strips, sg = u / n_strips;
-        const int y0 = (int)(((long long)sg * ny) / n_segs);
-        const int y1 = (int)(((long long)(sg + 1) * ny) / n_segs);
-        seg(strip, y0, y1);
-        return;
-    }
-    const long long R = (long long)n_strips * ny;
-    long long q0 = (long long)u * R / n_units;
-    const long long q1 = (long long)(u + 1) * R / n_units;
-    bool first = true;
-    while (q0 < q1) {
-        const int strip = (int)(q0 / ny);
-        const int y0 = (int)(q0 - (long long)strip * ny);
-        const long long end = (long long)(strip + 1) * ny < q1 ? (long long)(strip + 1) * ny : q1;
-        const int y1 = (int)(end - (long long)strip * ny);
+    for (bool first = true; left > 0; first = false) {
+        const int y1 = y0 + left < ny ? (int)(y0 + left) : ny;
         if (!first) __syncthreads();  // the LDS rings are reused
         seg(strip, y0, y1);
-        first = false;
-        q0 = end;
+        left -= y1 - y0;
+        ++strip;
+        y0 = 0;
     }
 }
 
@@ -886,7 +908,7 @@ __device__ __forceinline__ void process_segment2(const KParams<typename Traits<S
     // halo is computed twice), those of step t+1 from the second
     constexpr bool red1 = (MODE & M_REDUCE) && (MODE & M_DIAG_FIRST);
     constexpr bool red2 = (MODE & M_REDUCE) && !(MODE & M_DIAG_FIRST);
-    constexpr int M1 = (MODE & (M_SR | M_BND)) | M_STORE | M_LDS | (red1 ? M_REDUCE : 0);
+    constexpr int M1 = (MODE & (M_SR | M_BND)) | M_STORE | (red1 ? M_REDUCE : 0);
     constexpr int M2 = (MODE & (M_SR | M_BND)) | M_STORE | (red2 ? M_REDUCE : 0);
     // with M_REPULL the first step keeps no pulled rows in registers: it
     // pulls the row it finishes again (the second read of addresses read
@@ -941,17 +963,23 @@ __device__ __forceinline__ void process_segment2(const KParams<typename Traits<S
         // s2 holds row p - 6 (written three iterations ago) until the pull
         // of row p - 3 below replaces it
         if (in2 && pp - 6 >= y0 && pp - 6 < y1)
-            finish_node<S, BLOCK, M2, TWO_PR>(p, mw, cx, pp - 6, pp - 6, s2, ring2, acc, nullptr, 1u);
+        {
+            const int yy = pp - 6;
+            const GlobalOut<S> sink{mw, (uint32_t)(yy * p.nx + cx.c) * (uint32_t)sizeof(typename Traits<S>::raw_t)};
+            finish_node<S, M2>(p, cx, yy, yy, s2, RingPsi<C, BLOCK, TWO_PR>{ring2, yy, tid}, sink, acc, 1u);
+        }
         if (fin1) {
             const Axis ry = make_axis_near(pp - 2, p.ny, wrap_y);
             const bool core = core_col && pp - 2 >= y0 && pp - 2 < y1;
+            const RingPsi<C, BLOCK, TWO_PR> psi{ring1, pp - 2, tid};
+            const RingOut<S, BLOCK> sink{fring, &pend, pp - 2, tid};
             if constexpr (REPULL) {
                 St st;
                 C r1 = 0, r2 = 0;
                 process_node<S, BND>(p, mr, cx, ry, act1 && ry.ok, qf, st, r1, r2);
-                finish_node<S, BLOCK, M1, TWO_PR>(p, mw, cx, pp - 2, ry.c, st, ring1, acc, fring, 0u, &pend, core);
+                finish_node<S, M1>(p, cx, pp - 2, ry.c, st, psi, sink, acc, 0u, core);
             } else {
-                finish_node<S, BLOCK, M1, TWO_PR>(p, mw, cx, pp - 2, ry.c, s1f, ring1, acc, fring, 0u, &pend, core);
+                finish_node<S, M1>(p, cx, pp - 2, ry.c, s1f, psi, sink, acc, 0u, core);
             }
         }
         __syncthreads();

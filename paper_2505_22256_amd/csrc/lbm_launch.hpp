@@ -23,6 +23,23 @@ template <int S>
 hipError_t launch_pass(const lbm::KParams<typename lbm::Traits<S>::C> &p, Pass pass, int block, bool sr, bool bnd,
                        hipStream_t st, bool repull = false);
 
+// Regions of the brick kernel (lbm_brick.hpp): nodes along x and y, one
+// thread each, and what is left of a side after the halo of `steps` steps.
+constexpr int BRICK_REGIONS = 3;
+constexpr int brick_rx(int region) { return region == 0 ? 16 : 32; }
+constexpr int brick_ry(int region) { return region == 2 ? 32 : 16; }
+constexpr int brick_core(int side, int steps) { return side - 2 * (3 * steps - 1); }
+
+// Advance `steps` steps in one launch of the brick kernel.
+template <int S>
+hipError_t launch_brick(lbm::KParams<typename lbm::Traits<S>::C> p, int region, int steps, bool sr, bool bnd,
+                        hipStream_t st);
+
+extern template hipError_t launch_brick<lbm::ST_F64>(lbm::KParams<double>, int, int, bool, bool, hipStream_t);
+extern template hipError_t launch_brick<lbm::ST_F32>(lbm::KParams<float>, int, int, bool, bool, hipStream_t);
+extern template hipError_t launch_brick<lbm::ST_F16>(lbm::KParams<float>, int, int, bool, bool, hipStream_t);
+extern template hipError_t launch_brick<lbm::ST_BF16>(lbm::KParams<float>, int, int, bool, bool, hipStream_t);
+
 // Resident workgroups per CU of the one-step kernel at this block size.
 template <int S>
 int step_occupancy(int block);

@@ -99,6 +99,13 @@ hipError_t launch_pass_b(const KParams<typename Traits<S>::C> &p, Pass pass, int
     return hipErrorInvalidValue;
 }
 
+// (the instances with boundary code are compiled in a unit of their own,
+// lbm_launch_<storage>_bnd.hip)
+extern template hipError_t launch_pass_b<ST_F64, M_BND>(const KParams<double> &, Pass, int, bool, hipStream_t, bool);
+extern template hipError_t launch_pass_b<ST_F32, M_BND>(const KParams<float> &, Pass, int, bool, hipStream_t, bool);
+extern template hipError_t launch_pass_b<ST_F16, M_BND>(const KParams<float> &, Pass, int, bool, hipStream_t, bool);
+extern template hipError_t launch_pass_b<ST_BF16, M_BND>(const KParams<float> &, Pass, int, bool, hipStream_t, bool);
+
 // Stepping passes take the instance without boundary code unless open or
 // moving boundaries are on; the (rare) field and table passes always have it.
 template <int S>
