@@ -30,13 +30,11 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "liblbm.so")
 BUILD_DIR = os.path.join(PKG, "_build")
 # the longest units first, so that the parallel build ends soonest
-SOURCES = [os.path.join(CSRC, n) for n in ("lbm_launch_f16.hip", "lbm_launch_bf16.hip", "lbm_launch_f16_bnd.hip",
-                                         "lbm_launch_bf16_bnd.hip", "lbm_batch.hip", "lbm_launch_f32.hip",
-                                         "lbm_launch_f64.hip", "lbm_launch_f32_bnd.hip", "lbm_launch_f64_bnd.hip",
-                                         "lbm_api.hip",
-                                         "lbm_brick_f16.hip", "lbm_brick_bf16.hip", "lbm_brick_f32.hip",
-                                         "lbm_brick_f64.hip", "lbm3d_launch_f64.hip", "lbm3d_launch_f32.hip", "lbm3d_launch_f16.hip",
-                                         "lbm3d_launch_bf16.hip", "lbm3d_api.hip")]
+SOURCES = [os.path.join(CSRC, n + ".hip") for n in
+           ["lbm_launch_" + n for n in ("bf16", "f16", "bf16_bnd", "f16_bnd", "bf16_tau1", "f16_tau1")] + ["lbm_batch"] +
+           ["lbm_launch_" + n for n in ("f32", "f32_bnd", "f64_bnd", "f64", "f32_tau1", "f64_tau1")] +
+           [u + n for u in ("lbm3d_launch_", "lbm_brick_") for n in ("bf16", "f16", "f64", "f32")] +
+           ["lbm3d_api", "lbm_api"]]
 HEADERS = [os.path.join(CSRC, n) for n in ("lbm_device.hpp", "lbm_kernels.hpp", "lbm_params.hpp", "lbm_regions.hpp", "lbm_contact.hpp",
                                             "lbm_launch.hpp", "lbm_launch_impl.hpp", "lbm_brick.hpp",
                                             "lbm_brick_impl.hpp", "lbm3d_kernels.hpp",

@@ -111,8 +111,43 @@ bool moving_walls(const lbm_ctx *c)
     return c->uw[0][0] != 0.0 || c->uw[0][1] != 0.0 || c->uw[1][0] != 0.0 || c->uw[1][1] != 0.0;
 }
 
+// Open or moving boundaries are on.  Right after the populations were set
+// the first step must pull them as given while the second applies the
+// boundary conditions, so that step runs alone.
+bool boundary_steps(const lbm_ctx *c)
+{
+    return (c->flags & (LBM_INLET | LBM_OUTFLOW)) || moving_walls(c);
+}
+
+struct Tile {
+    int block, seg_rows;
+    unsigned sched;
+};
+
+// The tile of the marching kernels: the caller's, or the default, which at
+// relaxation time 1 gives way to the one its kernels run best with.  They
+// keep 4 values per row and component pair instead of 18 (FP32 123 registers
+// against 210, FP64 218 against 256 and 126 accumulation registers), so more
+// wavefronts share a SIMD and wider strips pay.  16384 x 2048 channel, us per
+// step, general kernels in the default tile / relaxation time 1 in that tile
+// / in this one: FP32 737 / 702 / 653, FP16 604 / 520 / 509, BF16 613 / 520 /
+// 505, FP64 (8192 x 2048) 820 / 774 / 702; with open edges (8192 x 1024) FP32
+// - / 248 / 233, FP64 - / 467 / 419; 16-bit storage stays at one step per
+// launch (232 either way).
+Tile march_tile(const lbm_ctx *c)
+{
+    const Tile t = {c->block, c->seg_rows, c->sched};
+    if (c->own_tile || c->tau != 1.0 || !(t.sched & SCHED_TWO_STEP)) return t;
+    const bool bnd = boundary_steps(c);
+    switch (c->storage) {
+    case LBM_F64: return {128, bnd ? 32 : 24, t.sched};
+    case LBM_F32: return {bnd ? 128 : 256, 24, t.sched};
+    default: return bnd ? t : Tile{128, 32, t.sched};
+    }
+}
+
 template <class C>
-KParams<C> make_params(const lbm_ctx *c, const void *A, void *B, int block, int seg_rows, int halo = 2)
+KParams<C> make_params(const lbm_ctx *c, const void *A, void *B, const Tile &t, int halo = 2)
 {
     KParams<C> p;
     std::memset(&p, 0, sizeof p);
@@ -121,9 +156,9 @@ KParams<C> make_params(const lbm_ctx *c, const void *A, void *B, int block, int 
     p.nx = c->nx;
     p.ny = c->ny;
     p.flags = c->flags;
-    tile_counts(block, seg_rows, c->nx, c->ny, &p.n_strips, &p.n_segs, c->sched,
+    tile_counts(t.block, t.seg_rows, c->nx, c->ny, &p.n_strips, &p.n_segs, t.sched,
                 (int)(128 / elem_size(c->storage)), &p.strip_w, halo);
-    p.band_order = (c->sched & SCHED_BANDS) ? 1 : 0;
+    p.band_order = (t.sched & SCHED_BANDS) ? 1 : 0;
     p.xcd_slabs = 0;
     p.n_units = p.n_strips * p.n_segs;
     p.item0 = 0;
@@ -136,14 +171,6 @@ KParams<C> make_params(const lbm_ctx *c, const void *A, void *B, int block, int 
     p.plain = c->fresh ? 1 : 0;
     p.inlet = c->d_inlet;
     return p;
-}
-
-// Open or moving boundaries are on.  Right after the populations were set
-// the first step must pull them as given while the second applies the
-// boundary conditions, so that step runs alone.
-bool boundary_steps(const lbm_ctx *c)
-{
-    return (c->flags & (LBM_INLET | LBM_OUTFLOW)) || moving_walls(c);
 }
 
 int grid_of(int strips, int segs) { return ((strips * segs + 7) / 8) * 8; }
@@ -219,19 +246,21 @@ int run_pass_t(lbm_ctx *c, Pass pass, double *fields, uint8_t *link, uint8_t *nw
     using C = typename Traits<S>::C;
     const bool two = pass == P_STEP2 || pass == P_STEP2_RED1 || pass == P_STEP2_RED2;
     const bool stepping = pass == P_STEP || pass == P_STEP_REDUCE || two;
-    const int block = stepping ? c->block : 256;
-    const int seg = c->seg_rows > 0 ? c->seg_rows : 64;
-    KParams<C> p = make_params<C>(c, c->buf[c->cur], c->buf[c->cur ^ 1], block, seg, two ? 5 : 2);
-    if ((c->sched & SCHED_XCD_SLABS) && stepping) {
+    Tile t = march_tile(c);
+    const bool persistent = t.seg_rows == 0;
+    if (persistent) t.seg_rows = 64;
+    if (!stepping) t = {256, c->seg_rows > 0 ? c->seg_rows : 64, c->sched};
+    KParams<C> p = make_params<C>(c, c->buf[c->cur], c->buf[c->cur ^ 1], t, two ? 5 : 2);
+    if ((t.sched & SCHED_XCD_SLABS) && stepping) {
         // one unit per (strip, row slab); the grid is 8 * strips so that
         // workgroup b lands on XCD b % 8 = its slab
         p.xcd_slabs = 1;
         p.band_order = 0;
         p.n_segs = 8;
         p.n_units = 8 * p.n_strips;
-    } else if (c->seg_rows == 0 && stepping) {
+    } else if (persistent && stepping) {
         // persistent: one unit per resident workgroup, balanced rows per unit
-        const int cap = resident_capacity<S>(c, block);
+        const int cap = resident_capacity<S>(c, t.block);
         const long long rows = (long long)p.n_strips * c->ny;
         p.n_units = (int)std::max(1LL, std::min((long long)cap, rows));
     }
@@ -260,7 +289,7 @@ int run_pass_t(lbm_ctx *c, Pass pass, double *fields, uint8_t *link, uint8_t *nw
     p.tab_src = src;
     if (pass == P_TABLES) p.plain = 1;  // link bits: plain unavailability of each source
     const bool sr = (S == ST_F16 || S == ST_BF16) && (c->flags & LBM_ROUND_STOCHASTIC);
-    const hipError_t e = launch_pass<S>(p, pass, block, sr, boundary_steps(c), c->stream, (c->sched & SCHED_REPULL) != 0);
+    const hipError_t e = launch_pass<S>(p, pass, t.block, sr, boundary_steps(c), c->stream, (t.sched & SCHED_REPULL) != 0);
     if (e != hipSuccess) return set_err(c, LBM_EDEVICE, "kernel launch failed: %s", hipGetErrorString(e));
     return LBM_OK;
 }
@@ -282,7 +311,7 @@ template <int S>
 int inverse_stream_t(lbm_ctx *c, const double *fsrc, const double *rho)
 {
     using C = typename Traits<S>::C;
-    KParams<C> p = make_params<C>(c, nullptr, c->buf[c->cur], 256, 64);
+    KParams<C> p = make_params<C>(c, nullptr, c->buf[c->cur], {256, 64, 0});
     const long long blocks = (c->N + 255) / 256;
     hipLaunchKernelGGL((k_inverse_stream<S>), dim3((unsigned)blocks), dim3(256), 0, c->stream, p, c->d_solid, fsrc, rho);
     HIPCHK(c, hipGetLastError());
@@ -303,7 +332,7 @@ template <int S>
 int pull_window_t(lbm_ctx *c, int x0, int y0, int w, int h, double *out)
 {
     using C = typename Traits<S>::C;
-    KParams<C> p = make_params<C>(c, c->buf[c->cur], nullptr, 256, 64);
+    KParams<C> p = make_params<C>(c, c->buf[c->cur], nullptr, {256, 64, 0});
     const long long blocks = ((long long)w * h + 255) / 256;
     hipLaunchKernelGGL((k_pull_window<S>), dim3((unsigned)blocks), dim3(256), 0, c->stream, p, x0, y0, w, h, out);
     HIPCHK(c, hipGetLastError());
@@ -325,7 +354,7 @@ template <int S>
 int run_bricks_t(lbm_ctx *c, int region, int steps)
 {
     using C = typename Traits<S>::C;
-    const KParams<C> p = make_params<C>(c, c->buf[c->cur], c->buf[c->cur ^ 1], 256, 64);
+    const KParams<C> p = make_params<C>(c, c->buf[c->cur], c->buf[c->cur ^ 1], {256, 64, 0});
     const bool sr = (S == ST_F16 || S == ST_BF16) && (c->flags & LBM_ROUND_STOCHASTIC);
     const hipError_t e = launch_brick<S>(p, region, steps, sr, boundary_steps(c), c->stream);
     if (e != hipSuccess) return set_err(c, LBM_EDEVICE, "kernel launch failed: %s", hipGetErrorString(e));
@@ -795,7 +824,7 @@ int lbm_step(lbm_ctx *c, int n)
     if (rc) return rc;
     if (n < 0) return set_err(c, LBM_EINVAL, "negative step count");
     const BrickPlan plan = brick_plan(c);
-    const bool two = (c->sched & SCHED_TWO_STEP) != 0 && !plan.steps;
+    const bool two = (march_tile(c).sched & SCHED_TWO_STEP) != 0 && !plan.steps;
     for (int s = 0; s < n; ++s) {
         const bool diag_now = c->diag_every > 0 && c->t % c->diag_every == 0;
         const bool diag_next = c->diag_every > 0 && (c->t + 1) % c->diag_every == 0;

@@ -106,7 +106,7 @@ __device__ __forceinline__ void process_brick(const KParams<typename Traits<S>::
     // nodes between this one and the edge of the region
     const int edge = min(min(lx, RX - 1 - lx), min(ly, RY - 1 - ly));
     RedAcc none;
-    StateOf<S, BND> st;
+    StateOf<S, MODE> st;
     for (int s = 0; s < steps; ++s) {
         if (edge >= 3 * s) {
             RawRow<S> q;
@@ -124,7 +124,7 @@ __device__ __forceinline__ void process_brick(const KParams<typename Traits<S>::
             }
             const BrickReload<S, RX, RY> reload{mr, off, post, c, s == 0};
             C r1 = 0, r2 = 0;
-            process_node_src<S, BND>(p, reload, cx, ry, inside, q, st, r1, r2);
+            process_node_src<S, MODE>(p, reload, cx, ry, inside, q, st, r1, r2);
             PsiPair<C> ps;
             ps.a = (st.info & 256) ? lds_sentinel<C>() : r1;
             ps.b = (st.info & 256) ? lds_sentinel<C>() : r2;
@@ -135,7 +135,7 @@ __device__ __forceinline__ void process_brick(const KParams<typename Traits<S>::
         // (after the last step only the brick's own nodes inside the lattice)
         if (edge >= 3 * s + 2 && (!last || (gx < p.nx && gy < p.ny))) {
             const BrickOut<S, RX, RY> sink{mw, off, post, c, last};
-            finish_node<S, M_STORE | (MODE & (M_SR | M_BND))>(p, cx, ry.c, ry.c, st, BrickPsi<C, RX>{psi, tid}, sink, none,
+            finish_node<S, M_STORE | (MODE & (M_SR | M_BND | M_TAU1))>(p, cx, ry.c, ry.c, st, BrickPsi<C, RX>{psi, tid}, sink, none,
                                                               (unsigned)s);
         }
         if (!last) __syncthreads();

@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace lbm {
 
 enum Storage : int { ST_F64 = 0, ST_F32 = 1, ST_F16 = 2, ST_BF16 = 3 };
@@ -39,6 +41,7 @@ enum : int {
     M_FIELDS = 4,  // write rho_1, rho_2, u (FP64)
     M_TABLES = 8,  // write link bits and resolved stencil sources
     M_SR = 16,     // stochastic rounding of FP16 / BF16 stores (compile-time)
+    M_TAU1 = 32,   // relaxation time 1: nodes keep their momenta instead of their populations
     M_TWO = 64,    // kernel advances two steps per launch
     M_DIAG_FIRST = 128,  // two steps: M_REDUCE records the first step (else the second)
     M_BND = 256,         // open and moving boundaries compiled in (else plain walls only)
@@ -417,9 +420,44 @@ template <int S> struct RowState<S, true> {
     __device__ __forceinline__ void put_raw(int i, R a, R b) { h[i] = (uint32_t)a | (uint32_t)b << 16; }
 };
 
-// The state type of a kernel: packed for 16-bit storage without boundary code.
-template <int S, bool BND>
-using StateOf = RowState<S, (S == ST_F16 || S == ST_BF16) && !BND>;
+// Momenta j_k = sum_i f_i e_i (Eq. 4) of a state, definition order; the
+// deviation base w_i rho0 has zero first moment.
+template <class St, class C> __device__ __forceinline__ void momenta(const St &st, C (&jx)[2], C (&jy)[2])
+{
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        C ax = st.get(k, 1);
+        ax -= st.get(k, 3);
+        ax += st.get(k, 5);
+        ax -= st.get(k, 6);
+        ax -= st.get(k, 7);
+        ax += st.get(k, 8);
+        C ay = st.get(k, 2);
+        ay -= st.get(k, 4);
+        ay += st.get(k, 5);
+        ay += st.get(k, 6);
+        ay -= st.get(k, 7);
+        ay -= st.get(k, 8);
+        jx[k] = ax;
+        jy[k] = ay;
+    }
+}
+
+// Relaxation time 1: f* = f - (f - f^eq)/tau + (1 - 1/2tau) F_i no longer
+// holds the populations pulled (their factor 1 - omega is exactly zero), so
+// all a node needs until its collision are its densities, which lie in the
+// psi ring, and its momenta: 4 values instead of 18.
+template <int S> struct RowMomenta {
+    using C = typename Traits<S>::C;
+    C jx[2], jy[2];
+    int info;
+};
+
+// The state type of a kernel: the momenta at relaxation time 1, else the
+// populations, packed for 16-bit storage without boundary code.
+template <int S, bool BND> using FullState = RowState<S, (S == ST_F16 || S == ST_BF16) && !BND>;
+template <int S, int MODE>
+using StateOf = std::conditional_t<(MODE & M_TAU1) != 0, RowMomenta<S>, FullState<S, (MODE & M_BND) != 0>>;
 
 // Cohesion sums sum_n W_n e_n Psi_n over the 24 positions, by opposite
 // pairs (n, n+2) in each group of four (Eq. 8 on the E8 stencil).

@@ -119,11 +119,10 @@ template <int S> struct GlobalReload {
 // f_i(x, t), with halfway bounce-back f_i(x, t) = f*_opp(i)(x, t-1) where
 // the source is unavailable (a sentinel or outside the domain), and the
 // densities rho_k = sum_i f_i (Eq. 3) in the definition's summation order.
-template <int S, bool BND, class Reload>
-__device__ __forceinline__ void process_node_src(const KParams<typename Traits<S>::C> &p, const Reload &reload,
-                                                 const Axis &cx, const Axis &ry, bool valid, const RawRow<S> &q,
-                                                 StateOf<S, BND> &st, typename Traits<S>::C &r1,
-                                                 typename Traits<S>::C &r2)
+template <int S, bool BND, class St, class Reload>
+__device__ __forceinline__ void process_full(const KParams<typename Traits<S>::C> &p, const Reload &reload,
+                                             const Axis &cx, const Axis &ry, bool valid, const RawRow<S> &q, St &st,
+                                             typename Traits<S>::C &r1, typename Traits<S>::C &r2)
 {
     using T = Traits<S>;
     using C = typename T::C;
@@ -246,27 +245,46 @@ __device__ __forceinline__ void process_node_src(const KParams<typename Traits<S
     r2 = s2;
 }
 
-template <int S, bool BND>
+// The same into the state the kernel keeps: the populations, or their
+// momenta (relaxation time 1).
+template <int S, int MODE, class Reload>
+__device__ __forceinline__ void process_node_src(const KParams<typename Traits<S>::C> &p, const Reload &reload,
+                                                 const Axis &cx, const Axis &ry, bool valid, const RawRow<S> &q,
+                                                 StateOf<S, MODE> &st, typename Traits<S>::C &r1,
+                                                 typename Traits<S>::C &r2)
+{
+    constexpr bool BND = (MODE & M_BND) != 0;
+    if constexpr (MODE & M_TAU1) {
+        RowState<S> f;
+        process_full<S, BND>(p, reload, cx, ry, valid, q, f, r1, r2);
+        st.info = f.info;
+        if (!(f.info & 256)) momenta(f, st.jx, st.jy);
+    } else {
+        process_full<S, BND>(p, reload, cx, ry, valid, q, st, r1, r2);
+    }
+}
+
+template <int S, int MODE>
 __device__ __forceinline__ void process_node(const KParams<typename Traits<S>::C> &p, const PopMem<S> &m,
                                              const Axis &cx, const Axis &ry, bool valid, const RawRow<S> &q,
-                                             StateOf<S, BND> &st, typename Traits<S>::C &r1,
+                                             StateOf<S, MODE> &st, typename Traits<S>::C &r1,
                                              typename Traits<S>::C &r2)
 {
     const GlobalReload<S> reload{m, (uint32_t)(ry.c * p.nx + cx.c) * (uint32_t)sizeof(typename Traits<S>::raw_t)};
-    process_node_src<S, BND>(p, reload, cx, ry, valid, q, st, r1, r2);
+    process_node_src<S, MODE>(p, reload, cx, ry, valid, q, st, r1, r2);
 }
 
 // Process a prefetched row: node state into `st`, psi into the LDS ring.
-template <int S, int BLOCK, int RS, bool BND>
+template <int S, int BLOCK, int RS, int MODE>
 __device__ __forceinline__ void process_row(const KParams<typename Traits<S>::C> &p, const PopMem<S> &m,
                                             const Axis &cx, bool col_ok, int r, const RawRow<S> &q,
                                             PsiPair<typename Traits<S>::C> (*ring)[BLOCK],
-                                            StateOf<S, BND> &st)
+                                            StateOf<S, MODE> &st)
 {
     using C = typename Traits<S>::C;
     const Axis ry = make_axis_near(r, p.ny, p.flags & FL_PERIODIC_Y);
     C r1 = 0, r2 = 0;
-    process_node<S, BND>(p, m, cx, ry, col_ok && ry.ok, q, st, r1, r2);
+    process_node<S, MODE>(p, m, cx, ry, col_ok && ry.ok, q, st, r1, r2);
     PsiPair<C> ps;
     ps.a = (st.info & 256) ? lds_sentinel<C>() : r1;
     ps.b = (st.info & 256) ? lds_sentinel<C>() : r2;
@@ -460,25 +478,14 @@ __device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C>
     const PsiPair<C> ctr = psi.at(0, 0);
     const C r1 = ctr.a, r2 = ctr.b;
 
-    // first moments j_k = sum_i f_i e_i (Eq. 4), definition order; the
-    // deviation base w_i rho0 has zero first moment
     C jx[2], jy[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        C ax = st.get(k, 1);
-        ax -= st.get(k, 3);
-        ax += st.get(k, 5);
-        ax -= st.get(k, 6);
-        ax -= st.get(k, 7);
-        ax += st.get(k, 8);
-        C ay = st.get(k, 2);
-        ay -= st.get(k, 4);
-        ay += st.get(k, 5);
-        ay += st.get(k, 6);
-        ay -= st.get(k, 7);
-        ay -= st.get(k, 8);
-        jx[k] = ax;
-        jy[k] = ay;
+    if constexpr (MODE & M_TAU1) {
+        jx[0] = st.jx[0];
+        jx[1] = st.jx[1];
+        jy[0] = st.jy[0];
+        jy[1] = st.jy[1];
+    } else {
+        momenta(st, jx, jy);
     }
 
     // E8 cohesion sums (Eq. 8); a sentinel (unavailable position) turns
@@ -600,7 +607,10 @@ __device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C>
         uint32_t rs = sr ? sr_seed(node, p.tick + dtick) : 1u;
         C gs[2][9];
 #pragma unroll
-        for (int k = 0; k < 2; ++k) gs[k][0] = p.omw * st.get(k, 0) + (C)qw(0) * c0[k];
+        for (int k = 0; k < 2; ++k) {
+            if constexpr (MODE & M_TAU1) gs[k][0] = (C)qw(0) * c0[k];
+            else gs[k][0] = p.omw * st.get(k, 0) + (C)qw(0) * c0[k];
+        }
 #pragma unroll
         for (int pair = 0; pair < 4; ++pair) {
             const int i = pair < 2 ? pair + 1 : pair + 3;  // 1, 2, 5, 6; partners 3, 4, 7, 8
@@ -615,8 +625,13 @@ __device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C>
                 const C eF = ex == 0 ? (C)ey * Fy[k] : (ey == 0 ? (C)ex * Fx[k] : (C)ex * Fx[k] + (C)ey * Fy[k]);
                 const C E = (c0[k] + c2[k] * eu2) + h9 * eF;
                 const C O = c1[k] * eu + p.cf3 * eF;
-                gs[k][i] = p.omw * st.get(k, i) + w * (E + O);
-                gs[k][o] = p.omw * st.get(k, o) + w * (E - O);
+                if constexpr (MODE & M_TAU1) {
+                    gs[k][i] = w * (E + O);
+                    gs[k][o] = w * (E - O);
+                } else {
+                    gs[k][i] = p.omw * st.get(k, i) + w * (E + O);
+                    gs[k][o] = p.omw * st.get(k, o) + w * (E - O);
+                }
             }
         }
         // encode (with stochastic rounding: one random word per direction,
@@ -730,38 +745,38 @@ __device__ __forceinline__ void process_segment(const KParams<typename Traits<S>
     const bool col_ok = active && cx.ok;
     const int last = y1 + 1;  // last row whose psi is needed
 
-    auto finish = [&](int y, const StateOf<S, BND> &st) {
+    auto finish = [&](int y, const StateOf<S, MODE> &st) {
         const GlobalOut<S> sink{mw, (uint32_t)(y * p.nx + cx.c) * (uint32_t)sizeof(typename Traits<S>::raw_t)};
         finish_node<S, MODE>(p, cx, y, y, st, RingPsi<C, BLOCK, 8>{ring, y, tid}, sink, acc);
     };
 
-    StateOf<S, BND> ra, rb, rc;
+    StateOf<S, MODE> ra, rb, rc;
     RawRow<S> q;
     issue_row<S>(p, mr, cx, col_ok, y0 - 2, q);
-    process_row<S, BLOCK, 8, BND>(p, mr, cx, col_ok, y0 - 2, q, ring, ra);
+    process_row<S, BLOCK, 8, MODE>(p, mr, cx, col_ok, y0 - 2, q, ring, ra);
     issue_row<S>(p, mr, cx, col_ok, y0 - 1, q);
-    process_row<S, BLOCK, 8, BND>(p, mr, cx, col_ok, y0 - 1, q, ring, ra);
+    process_row<S, BLOCK, 8, MODE>(p, mr, cx, col_ok, y0 - 1, q, ring, ra);
     issue_row<S>(p, mr, cx, col_ok, y0, q);
-    process_row<S, BLOCK, 8, BND>(p, mr, cx, col_ok, y0, q, ring, ra);
+    process_row<S, BLOCK, 8, MODE>(p, mr, cx, col_ok, y0, q, ring, ra);
     issue_row<S>(p, mr, cx, col_ok, y0 + 1, q);
-    process_row<S, BLOCK, 8, BND>(p, mr, cx, col_ok, y0 + 1, q, ring, rb);
+    process_row<S, BLOCK, 8, MODE>(p, mr, cx, col_ok, y0 + 1, q, ring, rb);
     issue_row<S>(p, mr, cx, col_ok, y0 + 2, q);
     int y = y0;
     for (;;) {
         if (y >= y1) break;
-        process_row<S, BLOCK, 8, BND>(p, mr, cx, col_ok, y + 2, q, ring, rc);
+        process_row<S, BLOCK, 8, MODE>(p, mr, cx, col_ok, y + 2, q, ring, rc);
         if (y + 3 <= last) issue_row<S>(p, mr, cx, col_ok, y + 3, q);
         __syncthreads();
         if (interior) finish(y, ra);
         ++y;
         if (y >= y1) break;
-        process_row<S, BLOCK, 8, BND>(p, mr, cx, col_ok, y + 2, q, ring, ra);
+        process_row<S, BLOCK, 8, MODE>(p, mr, cx, col_ok, y + 2, q, ring, ra);
         if (y + 3 <= last) issue_row<S>(p, mr, cx, col_ok, y + 3, q);
         __syncthreads();
         if (interior) finish(y, rb);
         ++y;
         if (y >= y1) break;
-        process_row<S, BLOCK, 8, BND>(p, mr, cx, col_ok, y + 2, q, ring, rb);
+        process_row<S, BLOCK, 8, MODE>(p, mr, cx, col_ok, y + 2, q, ring, rb);
         if (y + 3 <= last) issue_row<S>(p, mr, cx, col_ok, y + 3, q);
         __syncthreads();
         if (interior) finish(y, rc);
@@ -860,19 +875,19 @@ template <int S, int BLOCK> struct LdsReload {
     }
 };
 
-template <int S, int BLOCK, bool BND>
+template <int S, int BLOCK, int MODE>
 __device__ __forceinline__ void process_row_lds(const KParams<typename Traits<S>::C> &p, FRingMem<S, BLOCK> *fring,
                                                 const Axis &cx, bool col_ok, int r,
                                                 PsiPair<typename Traits<S>::C> (*ring)[BLOCK],
-                                                StateOf<S, BND> &st)
+                                                StateOf<S, MODE> &st)
 {
     using C = typename Traits<S>::C;
     const Axis ry = make_axis_near(r, p.ny, p.flags & FL_PERIODIC_Y);
     RawRow<S> q;
-    issue_row_lds<S, BLOCK>(fring, r, q, BND && cx.okp && cx.p == cx.c);
+    issue_row_lds<S, BLOCK>(fring, r, q, (MODE & M_BND) != 0 && cx.okp && cx.p == cx.c);
     const LdsReload<S, BLOCK> reload{fring, r, (int)threadIdx.x};
     C r1 = 0, r2 = 0;
-    process_node_src<S, BND>(p, reload, cx, ry, col_ok && ry.ok, q, st, r1, r2);
+    process_node_src<S, MODE>(p, reload, cx, ry, col_ok && ry.ok, q, st, r1, r2);
     PsiPair<C> ps;
     ps.a = (st.info & 256) ? lds_sentinel<C>() : r1;
     ps.b = (st.info & 256) ? lds_sentinel<C>() : r2;
@@ -908,8 +923,8 @@ __device__ __forceinline__ void process_segment2(const KParams<typename Traits<S
     // halo is computed twice), those of step t+1 from the second
     constexpr bool red1 = (MODE & M_REDUCE) && (MODE & M_DIAG_FIRST);
     constexpr bool red2 = (MODE & M_REDUCE) && !(MODE & M_DIAG_FIRST);
-    constexpr int M1 = (MODE & (M_SR | M_BND)) | M_STORE | (red1 ? M_REDUCE : 0);
-    constexpr int M2 = (MODE & (M_SR | M_BND)) | M_STORE | (red2 ? M_REDUCE : 0);
+    constexpr int M1 = (MODE & (M_SR | M_BND | M_TAU1)) | M_STORE | (red1 ? M_REDUCE : 0);
+    constexpr int M2 = (MODE & (M_SR | M_BND | M_TAU1)) | M_STORE | (red2 ? M_REDUCE : 0);
     // with M_REPULL the first step keeps no pulled rows in registers: it
     // pulls the row it finishes again (the second read of addresses read
     // two iterations earlier, served by the caches), which frees the
@@ -936,7 +951,7 @@ __device__ __forceinline__ void process_segment2(const KParams<typename Traits<S
     const bool wrap_y = p.flags & FL_PERIODIC_Y;
     const bool core_col = tid >= 5 && tid < w + 5;
 
-    using St = StateOf<S, BND>;
+    using St = StateOf<S, MODE>;
     St a1, b1, c1, a2, b2, c2;
     RawRow<S> q;
     FPending<S> pend;  // held group of the row step 1 finished last
@@ -948,7 +963,7 @@ __device__ __forceinline__ void process_segment2(const KParams<typename Traits<S
         if constexpr (REPULL) {
             if (fin1) issue_row<S>(p, mr, cx, act1, pp - 2, qf);
         }
-        if (pp <= p_pull_last) process_row<S, BLOCK, TWO_PR, BND>(p, mr, cx, act1, pp, q, ring1, s1w);
+        if (pp <= p_pull_last) process_row<S, BLOCK, TWO_PR, MODE>(p, mr, cx, act1, pp, q, ring1, s1w);
         if (pp + 1 <= p_pull_last) issue_row<S>(p, mr, cx, act1, pp + 1, q);
         __syncthreads();
         if (held) {
@@ -976,14 +991,14 @@ __device__ __forceinline__ void process_segment2(const KParams<typename Traits<S
             if constexpr (REPULL) {
                 St st;
                 C r1 = 0, r2 = 0;
-                process_node<S, BND>(p, mr, cx, ry, act1 && ry.ok, qf, st, r1, r2);
+                process_node<S, MODE>(p, mr, cx, ry, act1 && ry.ok, qf, st, r1, r2);
                 finish_node<S, M1>(p, cx, pp - 2, ry.c, st, psi, sink, acc, 0u, core);
             } else {
                 finish_node<S, M1>(p, cx, pp - 2, ry.c, s1f, psi, sink, acc, 0u, core);
             }
         }
         __syncthreads();
-        if (pp - 3 >= y0 - 2 && pp - 3 <= y1 + 1) process_row_lds<S, BLOCK, BND>(p, fring, cx, act2, pp - 3, ring2, s2);
+        if (pp - 3 >= y0 - 2 && pp - 3 <= y1 + 1) process_row_lds<S, BLOCK, MODE>(p, fring, cx, act2, pp - 3, ring2, s2);
     };
     // state of row r: step 1 in {a1, b1, c1}, step 2 in {a2, b2, c2}, both by
     // (r - p_first) mod 3; iteration p writes rows p (step 1) and p - 3
@@ -1215,9 +1230,9 @@ k_pull_window(const KParams<typename Traits<S>::C> p, int x0, int y0, int w, int
     const PopMem<S> m = make_mem<S>(p.A, p.N);
     RawRow<S> raw;
     issue_node<S>(m, p.nx, cx, ry, true, raw);
-    StateOf<S, true> st;
+    StateOf<S, M_BND> st;
     C r1, r2;
-    process_node<S, true>(p, m, cx, ry, true, raw, st, r1, r2);
+    process_node<S, M_BND>(p, m, cx, ry, true, raw, st, r1, r2);
     const bool solid = st.info & 256;
 #pragma unroll
     for (int k = 0; k < 2; ++k)

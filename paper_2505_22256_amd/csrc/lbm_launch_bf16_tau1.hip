@@ -1,0 +1,6 @@
+// Step-kernel instances of relaxation time 1 for BF16 storage (see lbm_launch.hpp).
+#include "lbm_launch_impl.hpp"
+
+namespace lbm_host {
+template hipError_t launch_tau1<lbm::ST_BF16>(const lbm::KParams<float> &, Pass, int, bool, bool, hipStream_t);
+}  // namespace lbm_host

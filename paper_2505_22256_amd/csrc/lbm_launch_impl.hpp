@@ -99,12 +99,38 @@ hipError_t launch_pass_b(const KParams<typename Traits<S>::C> &p, Pass pass, int
     return hipErrorInvalidValue;
 }
 
-// (the instances with boundary code are compiled in a unit of their own,
-// lbm_launch_<storage>_bnd.hip)
-extern template hipError_t launch_pass_b<ST_F64, M_BND>(const KParams<double> &, Pass, int, bool, hipStream_t, bool);
-extern template hipError_t launch_pass_b<ST_F32, M_BND>(const KParams<float> &, Pass, int, bool, hipStream_t, bool);
-extern template hipError_t launch_pass_b<ST_F16, M_BND>(const KParams<float> &, Pass, int, bool, hipStream_t, bool);
-extern template hipError_t launch_pass_b<ST_BF16, M_BND>(const KParams<float> &, Pass, int, bool, hipStream_t, bool);
+// Steps at relaxation time 1 (M_TAU1): the plain one- and two-step passes.
+template <int S, int MODE>
+hipError_t launch_tau1_m(const KParams<typename Traits<S>::C> &p, Pass pass, int block, hipStream_t st)
+{
+    if (pass == P_STEP) return launch_step_b<S, MODE>(p, block, st);
+    if constexpr (S == ST_F64)
+        return block == 128 ? launch_step2_t<S, 128, MODE>(p, st) : launch_step2_t<S, 64, MODE>(p, st);
+    else
+        return launch_step2_b<S, MODE>(p, block, st);
+}
+
+template <int S>
+hipError_t launch_tau1(const KParams<typename Traits<S>::C> &p, Pass pass, int block, bool sr, bool bnd, hipStream_t st)
+{
+    constexpr int M = M_STORE | M_TAU1;
+    if constexpr (S == ST_F16 || S == ST_BF16) {
+        if (sr)
+            return bnd ? launch_tau1_m<S, M | M_SR | M_BND>(p, pass, block, st) : launch_tau1_m<S, M | M_SR>(p, pass, block, st);
+    }
+    return bnd ? launch_tau1_m<S, M | M_BND>(p, pass, block, st) : launch_tau1_m<S, M>(p, pass, block, st);
+}
+
+// (the instances with boundary code and those of relaxation time 1 are
+// compiled in units of their own, lbm_launch_<storage>_bnd.hip and _tau1.hip)
+#define LBM_EXTERN_LAUNCH(S, C)                                                                                       \
+    extern template hipError_t launch_pass_b<S, M_BND>(const KParams<C> &, Pass, int, bool, hipStream_t, bool);        \
+    extern template hipError_t launch_tau1<S>(const KParams<C> &, Pass, int, bool, bool, hipStream_t);
+LBM_EXTERN_LAUNCH(ST_F64, double)
+LBM_EXTERN_LAUNCH(ST_F32, float)
+LBM_EXTERN_LAUNCH(ST_F16, float)
+LBM_EXTERN_LAUNCH(ST_BF16, float)
+#undef LBM_EXTERN_LAUNCH
 
 // Stepping passes take the instance without boundary code unless open or
 // moving boundaries are on; the (rare) field and table passes always have it.
@@ -115,6 +141,10 @@ hipError_t launch_pass(const KParams<typename Traits<S>::C> &p, Pass pass, int b
     if (pass == P_FIELDS_REDUCE) return launch_step_t<S, 256, M_BND | M_FIELDS | M_REDUCE>(p, st);
     if (pass == P_REDUCE) return launch_step_t<S, 256, M_BND | M_REDUCE>(p, st);
     if (pass == P_TABLES) return launch_step_t<S, 256, M_BND | M_TABLES>(p, st);
+    // (1 - omega is exactly 0; the diagnostic passes and the re-pull variant
+    // are not compiled for it and give the same results)
+    if (p.omw == 0 && (pass == P_STEP || pass == P_STEP2) && !(repull && !bnd))
+        return launch_tau1<S>(p, pass, block, sr, bnd, st);
     return bnd ? launch_pass_b<S, M_BND>(p, pass, block, sr, st, false)
                : launch_pass_b<S, 0>(p, pass, block, sr, st, repull);
 }
