@@ -100,7 +100,6 @@ KParams3<C> make_params3(const lbm3d_ctx *c, const void *A, void *B, int bx, int
     p.bricks_x = (c->nx + bx - 1) / bx;
     p.bricks_y = (c->ny + by - 1) / by;
     p.bricks_z = (c->nz + bz - 1) / bz;
-    p.n_units = p.bricks_x * p.bricks_y * p.bricks_z;
     p.psi = (PsiPair<C> *)c->d_psi;
     p.tick = (unsigned)c->t;
     p.N = c->N;
@@ -141,7 +140,7 @@ int run_pass3_t(lbm3d_ctx *c, Pass3 pass, double *fields, int *nparts)
     const bool fp = pass == P3_FIELDS_REDUCE;
     KParams3<C> p = make_params3<C>(c, c->buf[c->cur], c->buf[c->cur ^ 1], fp ? 32 : c->bx, fp ? 8 : c->by,
                                     fp ? 4 : c->bz);
-    const int grid = ((p.n_units + 7) / 8) * 8;
+    const int grid = collide3_grid(p);
     if (nparts) *nparts = grid;
     if (pass != P3_STEP) {
         int rc = ensure_partials(c, (size_t)grid);

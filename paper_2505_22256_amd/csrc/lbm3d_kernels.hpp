@@ -126,7 +126,7 @@ template <class C> struct KParams3 {
     void *B;        // post-collision set at t   (written)
     int nx, ny, nz;
     unsigned flags;
-    int bricks_x, bricks_y, bricks_z, n_units;
+    int bricks_x, bricks_y, bricks_z;
     PsiPair<C> *psi;  // psi = rho of both components per node (density pass output)
     unsigned tick;
     long long N;
@@ -644,18 +644,26 @@ __global__ void __launch_bounds__(256) k_density3(const KParams3<typename Traits
     p.psi[id] = ps;
 }
 
+template <class C> inline int collide3_grid(const KParams3<C> &p)
+{
+    return (p.bricks_y * p.bricks_z + 7) / 8 * 8 * p.bricks_x;
+}
+
 // Collide pass over bricks of BXB x BYB x BZB nodes.  The workgroup has
 // BXB x BYB x TZ threads: thread (x, y, t) finishes planes t, t + TZ, ...
 // of its column (TZ = BZB: one node per thread; TZ < BZB: a short march,
 // the next node's loads issued before the current one is finished).  The
 // FP32 stepping instances are held to 128 registers (four waves per SIMD,
 // a few values spilled), which lets two 512-thread workgroups share a CU.
-// Grid: 8 * per_xcd workgroups; workgroup b takes brick (b % 8) * per_xcd
-// + b / 8, so each XCD works on a contiguous run of bricks (numbered x
-// fastest, then y, then z), whose psi halos meet in that XCD's L2.
+// Grid: collide3_grid workgroups.  Rows of bricks along x go to the 8 XCDs in
+// turn (workgroup b runs on XCD b % 8): bricks of a row share cache lines at
+// their ends and stay in one L2, while the bricks near walls, which take
+// several times as long, spread over all XCDs.  Against one contiguous run
+// of bricks per XCD (200 x 200 x 280 with the sphere in three of them): FP32
+// 1400 -> 1294 us per step, FP16 1006 -> 858, FP64 2485 -> 2328.
 template <int S, int BXB, int BYB, int BZB, int TZ, int MODE>
 __global__ void __launch_bounds__(BXB * BYB * TZ)
-__attribute__((amdgpu_waves_per_eu((S == lbm::ST_F32 && !(MODE & K3_REDUCE)) ? 4 : 1))) k_collide3(const KParams3<typename Traits<S>::C> p, int per_xcd)
+__attribute__((amdgpu_waves_per_eu((S == lbm::ST_F32 && !(MODE & K3_REDUCE)) ? 4 : 1))) k_collide3(const KParams3<typename Traits<S>::C> p)
 {
     using C = typename Traits<S>::C;
     using BR = Brick<BXB, BYB, BZB>;
@@ -663,12 +671,11 @@ __attribute__((amdgpu_waves_per_eu((S == lbm::ST_F32 && !(MODE & K3_REDUCE)) ? 4
     static_assert(BZB % TZ == 0, "the brick depth must be a multiple of the threads in z");
     __shared__ PsiPair<C> tile[BR::TX * BR::TY * BR::TZ];
     const int b = blockIdx.x;
-    const int unit = (b & 7) * per_xcd + (b >> 3);
     const int tid = threadIdx.x;
     RedAcc3 acc;
-    if (unit < p.n_units) {
-        const int bxi = unit % p.bricks_x, rest = unit / p.bricks_x;
-        const int byi = rest % p.bricks_y, bzi = rest / p.bricks_y;
+    const int bxi = (b >> 3) % p.bricks_x, row = (b >> 3) / p.bricks_x * 8 + (b & 7);
+    if (row < p.bricks_y * p.bricks_z) {
+        const int byi = row % p.bricks_y, bzi = row / p.bricks_y;
         const int x0 = bxi * BXB, y0 = byi * BYB, z0 = bzi * BZB;
         const bool wx = p.flags & F3_PERIODIC_X, wy = p.flags & F3_PERIODIC_Y, wz = p.flags & F3_PERIODIC_Z;
         // psi of the brick and its halo (outside a closed face: the sentinel)

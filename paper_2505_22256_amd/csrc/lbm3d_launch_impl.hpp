@@ -13,9 +13,7 @@ hipError_t launch3_t(const KParams3<typename lbm::Traits<S>::C> &p, hipStream_t 
 {
     const long long blocks = (p.N + 255) / 256;
     hipLaunchKernelGGL((k_density3<S>), dim3((unsigned)blocks), dim3(256), 0, st, p);
-    const int per_xcd = (p.n_units + 7) / 8;
-    hipLaunchKernelGGL((k_collide3<S, BX, BY, BZ, TZ, MODE>), dim3(per_xcd * 8), dim3(BX * BY * TZ), 0, st, p,
-                       per_xcd);
+    hipLaunchKernelGGL((k_collide3<S, BX, BY, BZ, TZ, MODE>), dim3((unsigned)collide3_grid(p)), dim3(BX * BY * TZ), 0, st, p);
     return hipGetLastError();
 }
 
