@@ -126,11 +126,16 @@ int lbm3d_contact_angle(lbm3d_ctx *c, int wall_kind, const double wall[4], doubl
  * bx * by * tz threads (tz threads per column, each finishing every tz-th
  * plane of it), one of 32 x 8 x 4 with tz 1, 2 or 4, 32 x 8 x 8 with tz 1
  * or 2, and 64 x 4 x 4 with tz 2; EINVAL otherwise.  The default is
- * 32 x 8 x 4 with tz 2 for FP32 and with tz 1 for the other storages.  Each
- * step runs a density pass (psi = rho of every node from the pulled
- * populations, 2 values per node) and then the collide pass, which stages
- * psi of its brick and a 2-node halo in LDS and pulls the populations of
- * its own nodes.  Results do not depend on the brick (bitwise). */
+ * 32 x 8 x 4 with tz 2 for FP32 and with tz 1 for the other storages; until a
+ * brick is set, the library takes more threads per column on small lattices
+ * and at tau = 1 (lbm3d_get_tile keeps giving the default).  Each step runs
+ * a density pass (psi = rho of every node from the pulled populations, 2
+ * values per node) and then the collide pass, which stages psi of its brick
+ * and a 2-node halo in LDS and pulls the populations of its own nodes; at
+ * tau = 1 the density pass also leaves the nodes' momenta (6 values per node
+ * of device memory, allocated by lbm3d_set_params when there is room) and
+ * the collide pass pulls nothing.  Results do not depend on the brick
+ * (bitwise). */
 int lbm3d_set_tile(lbm3d_ctx *c, int bx, int by, int bz, int tz);
 int lbm3d_get_tile(const lbm3d_ctx *c, int *bx, int *by, int *bz, int *tz);
 

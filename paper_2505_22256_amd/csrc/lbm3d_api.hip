@@ -37,7 +37,10 @@ struct lbm3d_ctx {
     bool have_geom = false, have_params = false, have_fields = false;
     long t = 0;
     int bx = 32, by = 8, bz = 4, tz = 1;  // collide-pass brick and threads in z
+    bool own_tile = false;                // set by lbm3d_set_tile
+    int cus = 256;
     void *d_psi = nullptr;        // density-pass output: psi of both components per node
+    void *d_mom = nullptr;        // and their momenta, once the relaxation time is set to 1
     std::string err;
 };
 
@@ -101,6 +104,7 @@ KParams3<C> make_params3(const lbm3d_ctx *c, const void *A, void *B, int bx, int
     p.bricks_y = (c->ny + by - 1) / by;
     p.bricks_z = (c->nz + bz - 1) / bz;
     p.psi = (PsiPair<C> *)c->d_psi;
+    p.mom = (PsiPair<C> *)c->d_mom;
     p.tick = (unsigned)c->t;
     p.N = c->N;
     const double tau = c->tau;
@@ -133,6 +137,27 @@ KParams3<C> make_params3(const lbm3d_ctx *c, const void *A, void *B, int bx, int
     return p;
 }
 
+// Threads in z of the collide pass: the caller's, or for the default brick
+// the number that this lattice runs best with (us per step with 1 / 2 / 4).
+// A lattice of fewer bricks than two per compute unit is bound by the march of
+// one thread and gets one node per thread (72 x 65 x 40: FP32 100 / 65 / 45,
+// FP16 103 / 65 / 48), except the FP64 kernel with populations, whose 1024
+// threads have no registers for it (115 / 80 / 92).  At relaxation time 1 the
+// collide kernels are light and want more wavefronts (200 x 200 x 280: FP32
+// 1090 / 1040 / 980, FP16 680 / 650 / 750, FP64 1930 / 1780 / 1730); else the
+// defaults stand (FP32 1360 / 1294 / 1345, FP16 858 / 1033 / 1122, FP64 2328 /
+// 2379 / 4104).
+int collide_tz(const lbm3d_ctx *c, int cus)
+{
+    if (c->own_tile) return c->tz;
+    const bool tau1 = c->tau == 1.0 && c->d_mom;
+    const long long bricks = (long long)((c->nx + c->bx - 1) / c->bx) * ((c->ny + c->by - 1) / c->by) *
+                             ((c->nz + c->bz - 1) / c->bz);
+    if (bricks < 2LL * cus) return c->storage == LBM_F64 && !tau1 ? 2 : 4;
+    if (tau1) return c->storage == LBM_F16 || c->storage == LBM_BF16 ? 2 : 4;
+    return c->tz;
+}
+
 template <int S>
 int run_pass3_t(lbm3d_ctx *c, Pass3 pass, double *fields, int *nparts)
 {
@@ -155,7 +180,7 @@ int run_pass3_t(lbm3d_ctx *c, Pass3 pass, double *fields, int *nparts)
         p.out_uz = fields + 4 * c->N;
     }
     const bool sr = (S == lbm::ST_F16 || S == lbm::ST_BF16) && (c->flags & LBM_ROUND_STOCHASTIC);
-    const hipError_t e = launch3<S>(p, pass, c->bx, c->by, c->bz, c->tz, sr, c->stream);
+    const hipError_t e = launch3<S>(p, pass, c->bx, c->by, c->bz, collide_tz(c, c->cus), sr, c->stream);
     if (e != hipSuccess) return fail(c, LBM_EDEVICE, "kernel launch failed: %s", hipGetErrorString(e));
     return LBM_OK;
 }
@@ -281,6 +306,7 @@ int lbm3d_create(lbm3d_ctx **out, int nx, int ny, int nz, int storage, unsigned 
         delete c;
         return LBM_EDEVICE;
     }
+    c->cus = prop.multiProcessorCount;
     if (hipStreamCreateWithFlags(&c->own_stream, hipStreamNonBlocking) != hipSuccess) {
         delete c;
         return LBM_EDEVICE;
@@ -306,7 +332,7 @@ void lbm3d_destroy(lbm3d_ctx *c)
 {
     if (!c) return;
     if (c->stream) (void)hipStreamSynchronize(c->stream);
-    for (void *p : {c->buf[0], c->buf[1], c->d_psi, (void *)c->d_solid, (void *)c->d_tmp, (void *)c->d_partials,
+    for (void *p : {c->buf[0], c->buf[1], c->d_psi, c->d_mom, (void *)c->d_solid, (void *)c->d_tmp, (void *)c->d_partials,
                     (void *)c->d_out})
         if (p) (void)hipFree(p);
     if (c->own_stream) (void)hipStreamDestroy(c->own_stream);
@@ -355,6 +381,15 @@ int lbm3d_set_params(lbm3d_ctx *c, double G_c, double G_ads, double tau)
     c->delta = 0.8;
     c->tau = tau;
     c->have_params = true;
+    if (tau == 1.0 && !c->d_mom) {
+        // (here and not in a step, which a caller may capture; without room
+        // the steps pull twice, as at any other relaxation time)
+        const size_t bytes = (size_t)c->N * 6 * (c->storage == LBM_F64 ? sizeof(double) : sizeof(float));
+        if (hipMalloc(&c->d_mom, bytes) != hipSuccess) {
+            c->d_mom = nullptr;
+            (void)hipGetLastError();
+        }
+    }
     return LBM_OK;
 }
 
@@ -547,6 +582,7 @@ int lbm3d_set_tile(lbm3d_ctx *c, int bx, int by, int bz, int tz)
     c->by = by;
     c->bz = bz;
     c->tz = tz;
+    c->own_tile = true;
     return LBM_OK;
 }
 

@@ -27,6 +27,8 @@
 
 #include "lbm_device.hpp"
 
+#include <type_traits>
+
 namespace lbm3 {
 
 using lbm::Axis;
@@ -41,7 +43,9 @@ enum : unsigned { F3_PERIODIC_X = 1u, F3_PERIODIC_Y = 2u, F3_ORIGINAL = 4u, F3_C
                   F3_WALLPSI_SELF = 16u, F3_VEL_LITERAL = 32u, F3_FORCE_DENSITY = 64u,
                   F3_ROUND_STOCHASTIC = 128u, F3_ROUND_NEAREST = 1024u, F3_PERIODIC_Z = 2048u };
 
-enum : int { K3_STORE = 1, K3_REDUCE = 2, K3_FIELDS = 4, K3_SR = 16 };
+// K3_TAU1: relaxation time 1, where the collision holds nothing of the
+// populations pulled (their factor 1 - omega is exactly zero).
+enum : int { K3_STORE = 1, K3_REDUCE = 2, K3_FIELDS = 4, K3_SR = 16, K3_TAU1 = 32 };
 
 // ---------------------------------------------------------------------------
 // D3Q19
@@ -128,6 +132,7 @@ template <class C> struct KParams3 {
     unsigned flags;
     int bricks_x, bricks_y, bricks_z;
     PsiPair<C> *psi;  // psi = rho of both components per node (density pass output)
+    PsiPair<C> *mom;  // momenta of both components, [3][node] (K3_TAU1: density pass output)
     unsigned tick;
     long long N;
     C omega, half, negGc, Gw1, Gw2, s1, s2, s3, t2, t3, delta;
@@ -190,6 +195,13 @@ template <int S> struct Raw3 {
     typename Traits<S>::raw_t v[2][19];
 };
 
+// What the collide pass loads for one node: its pulled populations, or at
+// relaxation time 1 the momenta that the density pass left.
+template <int S> struct Mom3 {
+    PsiPair<typename Traits<S>::C> j[3];
+};
+template <int S, int MODE> using Pulled3 = std::conditional_t<(MODE & K3_TAU1) != 0, Mom3<S>, Raw3<S>>;
+
 // Source x - e_i of direction i for a node with axes (ax, ay, az), and
 // whether it lies inside the domain.
 __device__ __forceinline__ uint32_t src_node3(int i, const Axis &ax, const Axis &ay, const Axis &az, int nx, int ny,
@@ -219,6 +231,19 @@ __device__ __forceinline__ void issue3(const PopMem3<S> &m, int nx, int ny, cons
         const uint32_t voff = (valid && ok) ? src * (uint32_t)sizeof(R) : lbm::OOB;
 #pragma unroll
         for (int k = 0; k < 2; ++k) q.v[k][i] = load3<S>(m, k, i, voff);
+    }
+}
+
+template <int S, int MODE>
+__device__ __forceinline__ void issue_node3(const KParams3<typename Traits<S>::C> &p, const PopMem3<S> &m, const Axis &ax,
+                                            const Axis &ay, const Axis &az, bool valid, uint32_t node, Pulled3<S, MODE> &q)
+{
+    if constexpr (MODE & K3_TAU1) {
+        if (valid)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) q.j[d] = p.mom[(long long)d * p.N + node];
+    } else {
+        issue3<S>(m, p.nx, p.ny, ax, ay, az, valid, q);
     }
 }
 
@@ -273,6 +298,27 @@ __device__ __forceinline__ bool pull3(const KParams3<typename Traits<S>::C> &p, 
 struct RedAcc3 {
     double m1 = 0, m2 = 0, px = 0, py = 0, pz = 0, umax = 0, rmin = __builtin_inf(), rmax = -__builtin_inf(), bad = 0;
 };
+
+// Momenta j_k = sum_i f_i e_i (Eq. 4).
+template <class C> __device__ __forceinline__ void momenta3(const C (&f)[2][19], C (&j)[2][3])
+{
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        C a = 0, b = 0, cc = 0;
+#pragma unroll
+        for (int i = 1; i < 19; ++i) {
+            if (dx3(i) == 1) a += f[k][i];
+            if (dx3(i) == -1) a -= f[k][i];
+            if (dy3(i) == 1) b += f[k][i];
+            if (dy3(i) == -1) b -= f[k][i];
+            if (dz3(i) == 1) cc += f[k][i];
+            if (dz3(i) == -1) cc -= f[k][i];
+        }
+        j[k][0] = a;
+        j[k][1] = b;
+        j[k][2] = cc;
+    }
+}
 
 // Eq. 11 (local adhesion parameter of component 1).
 template <class C>
@@ -391,7 +437,7 @@ constexpr int PAIRS_PER_FENCE = LBM3_PAIRS_PER_FENCE;
 template <int S, class BR, int MODE>
 __device__ __forceinline__ void finish3(const KParams3<typename Traits<S>::C> &p, const PopMem3<S> &mr,
                                        const PopMem3<S> &mw, const Axis &ax, const Axis &ay, const Axis &az,
-                                       const Raw3<S> &q, const PsiPair<typename Traits<S>::C> *tile, int c,
+                                       const Pulled3<S, MODE> &q, const PsiPair<typename Traits<S>::C> *tile, int c,
                                        uint32_t node, RedAcc3 &acc)
 {
     using T = Traits<S>;
@@ -408,28 +454,18 @@ __device__ __forceinline__ void finish3(const KParams3<typename Traits<S>::C> &p
         }
         return;
     }
-    C f[2][19];
-    C pr1, pr2;
-    (void)pull3<S>(p, mr, ax, ay, az, true, q, f, pr1, pr2);
-    const C r1 = ctr.a, r2 = ctr.b;  // bitwise pr1, pr2: the density pass pulled the same values
-
-    // momenta j_k = sum_i f_i e_i (Eq. 4)
-    C j[2][3];
+    const C r1 = ctr.a, r2 = ctr.b;  // those of the pull below, bitwise: the density pass pulled the same values
+    C f[2][19], j[2][3];
+    if constexpr (MODE & K3_TAU1) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        C a = 0, b = 0, cc = 0;
-#pragma unroll
-        for (int i = 1; i < 19; ++i) {
-            if (dx3(i) == 1) a += f[k][i];
-            if (dx3(i) == -1) a -= f[k][i];
-            if (dy3(i) == 1) b += f[k][i];
-            if (dy3(i) == -1) b -= f[k][i];
-            if (dz3(i) == 1) cc += f[k][i];
-            if (dz3(i) == -1) cc -= f[k][i];
+        for (int d = 0; d < 3; ++d) {
+            j[0][d] = q.j[d].a;
+            j[1][d] = q.j[d].b;
         }
-        j[k][0] = a;
-        j[k][1] = b;
-        j[k][2] = cc;
+    } else {
+        C pr1, pr2;
+        (void)pull3<S>(p, mr, ax, ay, az, true, q, f, pr1, pr2);
+        momenta3(f, j);
     }
 
     // cohesion sums over the 46 opposite pairs; a sentinel turns them into
@@ -529,7 +565,10 @@ __device__ __forceinline__ void finish3(const KParams3<typename Traits<S>::C> &p
         uint32_t rs = sr ? lbm::sr_seed((int)node, p.tick) : 1u;
         C gs[2][19];
 #pragma unroll
-        for (int k = 0; k < 2; ++k) gs[k][0] = p.omw * f[k][0] + (C)w3(0) * c0[k];
+        for (int k = 0; k < 2; ++k) {
+            if constexpr (MODE & K3_TAU1) gs[k][0] = (C)w3(0) * c0[k];
+            else gs[k][0] = p.omw * f[k][0] + (C)w3(0) * c0[k];
+        }
 #pragma unroll
         for (int i = 1; i < 19; i += 2) {
             const int o = i + 1;
@@ -549,8 +588,13 @@ __device__ __forceinline__ void finish3(const KParams3<typename Traits<S>::C> &p
                 if (ez != 0) eF += (C)ez * F[k][2];
                 const C E = (c0[k] + c2[k] * eu2) + h9 * eF;
                 const C O = c1[k] * eu + p.cf3 * eF;
-                gs[k][i] = p.omw * f[k][i] + w * (E + O);
-                gs[k][o] = p.omw * f[k][o] + w * (E - O);
+                if constexpr (MODE & K3_TAU1) {
+                    gs[k][i] = w * (E + O);
+                    gs[k][o] = w * (E - O);
+                } else {
+                    gs[k][i] = p.omw * f[k][i] + w * (E + O);
+                    gs[k][o] = p.omw * f[k][o] + w * (E - O);
+                }
             }
         }
         const uint32_t voff = node * (uint32_t)sizeof(R);
@@ -618,8 +662,10 @@ __device__ void block_reduce3(const RedAcc3 &acc, double *out)
 
 // Density pass: psi = rho of both components at every node (Eq. 3 on the
 // pulled populations, Eq. 1 streaming with halfway bounce-back), the
-// all-ones sentinel at solid nodes.  One thread per node.
-template <int S>
+// all-ones sentinel at solid nodes; with TAU1 the fluid nodes' momenta too,
+// so that the collide pass need not pull the populations again.  One thread
+// per node.
+template <int S, bool TAU1>
 __global__ void __launch_bounds__(256) k_density3(const KParams3<typename Traits<S>::C> p)
 {
     using C = typename Traits<S>::C;
@@ -642,6 +688,14 @@ __global__ void __launch_bounds__(256) k_density3(const KParams3<typename Traits
     ps.a = fluid ? r1 : lds_sentinel<C>();
     ps.b = fluid ? r2 : lds_sentinel<C>();
     p.psi[id] = ps;
+    if constexpr (TAU1) {
+        if (fluid) {
+            C j[2][3];
+            momenta3(f, j);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) p.mom[(long long)d * p.N + id] = PsiPair<C>{j[0][d], j[1][d]};
+        }
+    }
 }
 
 template <class C> inline int collide3_grid(const KParams3<C> &p)
@@ -706,23 +760,24 @@ __attribute__((amdgpu_waves_per_eu((S == lbm::ST_F32 && !(MODE & K3_REDUCE)) ? 4
             const Axis ay = make_axis_near(y, p.ny, wy);
             const int zend = z0 + BZB < p.nz ? z0 + BZB : p.nz;
             const int zs = z0 + lt;
-            Raw3<S> q;
+            const uint32_t plane = (uint32_t)p.nx * (uint32_t)p.ny;
+            Pulled3<S, MODE> q;
             if (zs < zend) {
                 const Axis az = make_axis_near(zs, p.nz, wz);
                 const bool solid = lds_sent(tile[BR::at(lx + 2, ly + 2, lt + 2)].a);
-                issue3<S>(mr, p.nx, p.ny, ax, ay, az, !solid, q);
+                issue_node3<S, MODE>(p, mr, ax, ay, az, !solid, (uint32_t)zs * plane + (uint32_t)y * (uint32_t)p.nx + (uint32_t)x, q);
             }
             for (int z = zs; z < zend; z += TZ) {
                 const Axis az = make_axis_near(z, p.nz, wz);
                 const int c = BR::at(lx + 2, ly + 2, z - z0 + 2);
                 const uint32_t node = ((uint32_t)z * (uint32_t)p.ny + (uint32_t)y) * (uint32_t)p.nx + (uint32_t)x;
-                Raw3<S> cur = q;
+                const Pulled3<S, MODE> cur = q;
                 // the next node's loads go out before this one is finished
                 if constexpr (TZ < BZB) {
                     if (z + TZ < zend) {
                         const Axis azn = make_axis_near(z + TZ, p.nz, wz);
                         const bool solid = lds_sent(tile[c + BR::at(0, 0, TZ)].a);
-                        issue3<S>(mr, p.nx, p.ny, ax, ay, azn, !solid, q);
+                        issue_node3<S, MODE>(p, mr, ax, ay, azn, !solid, node + (uint32_t)TZ * plane, q);
                     }
                 }
                 finish3<S, BR, MODE>(p, mr, mw, ax, ay, az, cur, tile, c, node, acc);

@@ -12,7 +12,7 @@ template <int S, int BX, int BY, int BZ, int TZ, int MODE>
 hipError_t launch3_t(const KParams3<typename lbm::Traits<S>::C> &p, hipStream_t st)
 {
     const long long blocks = (p.N + 255) / 256;
-    hipLaunchKernelGGL((k_density3<S>), dim3((unsigned)blocks), dim3(256), 0, st, p);
+    hipLaunchKernelGGL((k_density3<S, (MODE & K3_TAU1) != 0>), dim3((unsigned)blocks), dim3(256), 0, st, p);
     hipLaunchKernelGGL((k_collide3<S, BX, BY, BZ, TZ, MODE>), dim3((unsigned)collide3_grid(p)), dim3(BX * BY * TZ), 0, st, p);
     return hipGetLastError();
 }
@@ -36,11 +36,15 @@ hipError_t launch3(const KParams3<typename lbm::Traits<S>::C> &p, Pass3 pass, in
                    hipStream_t st)
 {
     if (pass == P3_FIELDS_REDUCE) return launch3_t<S, 32, 8, 4, 1, K3_FIELDS | K3_REDUCE>(p, st);
+    // relaxation time 1 (1 - omega is exactly 0) with room for the momenta
+    const bool tau1 = pass == P3_STEP && p.omw == 0 && p.mom;
     if constexpr (S == lbm::ST_F16 || S == lbm::ST_BF16) {
+        if (sr && tau1) return launch3_tile<S, K3_STORE | K3_SR | K3_TAU1>(p, bx, by, bz, tz, st);
         if (sr)
             return pass == P3_STEP ? launch3_tile<S, K3_STORE | K3_SR>(p, bx, by, bz, tz, st)
                                    : launch3_tile<S, K3_STORE | K3_REDUCE | K3_SR>(p, bx, by, bz, tz, st);
     }
+    if (tau1) return launch3_tile<S, K3_STORE | K3_TAU1>(p, bx, by, bz, tz, st);
     return pass == P3_STEP ? launch3_tile<S, K3_STORE>(p, bx, by, bz, tz, st)
                            : launch3_tile<S, K3_STORE | K3_REDUCE>(p, bx, by, bz, tz, st);
 }
