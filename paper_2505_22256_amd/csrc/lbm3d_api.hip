@@ -3,6 +3,7 @@
 #include "lbm3d.h"
 #include "lbm3d_contact.hpp"
 #include "lbm3d_launch.hpp"
+#include "lbm_hostcopy.hpp"
 #include "lbm_params.hpp"
 
 #include <cmath>
@@ -41,6 +42,7 @@ struct lbm3d_ctx {
     int cus = 256;
     void *d_psi = nullptr;        // density-pass output: psi of both components per node
     void *d_mom = nullptr;        // and their momenta, once the relaxation time is set to 1
+    lbm_host::HostCopier copier;  // large arrays to host memory
     std::string err;
 };
 
@@ -483,8 +485,9 @@ int lbm3d_get_populations(lbm3d_ctx *c, double *f)
     if (rc) return rc;
     rc = pull_all(c, c->d_tmp);
     if (rc) return rc;
-    HIPCHK3(c, hipMemcpyAsync(f, c->d_tmp, (size_t)c->N * 38 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK3(c, hipStreamSynchronize(c->stream));
+    void *const dst = f;
+    const void *const src = c->d_tmp;
+    HIPCHK3(c, c->copier.copy(c->device, c->stream, &dst, &src, (size_t)c->N * 38 * sizeof(double), 1));
     return LBM_OK;
 }
 
@@ -517,12 +520,10 @@ int lbm3d_get_fields(lbm3d_ctx *c, double *rho1, double *rho2, double *ux, doubl
     if (rc) return rc;
     rc = fields_reduce3(c);
     if (rc) return rc;
-    double *outs[5] = {rho1, rho2, ux, uy, uz};
-    for (int q = 0; q < 5; ++q)
-        if (outs[q])
-            HIPCHK3(c, hipMemcpyAsync(outs[q], c->d_tmp + (size_t)q * c->N, (size_t)c->N * sizeof(double),
-                                      hipMemcpyDeviceToHost, c->stream));
-    HIPCHK3(c, hipStreamSynchronize(c->stream));
+    void *const outs[5] = {rho1, rho2, ux, uy, uz};
+    const void *src[5];
+    for (int q = 0; q < 5; ++q) src[q] = c->d_tmp + (size_t)q * c->N;
+    HIPCHK3(c, c->copier.copy(c->device, c->stream, outs, src, (size_t)c->N * sizeof(double), 5));
     return LBM_OK;
 }
 

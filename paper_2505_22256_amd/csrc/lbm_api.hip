@@ -2,6 +2,7 @@
 // mapping, launches, diagnostics, tables, checkpoints and the tile tuner.
 #include "lbm.h"
 #include "lbm_contact.hpp"
+#include "lbm_hostcopy.hpp"
 #include "lbm_kernels.hpp"
 #include "lbm_launch.hpp"
 #include "lbm_params.hpp"
@@ -53,6 +54,7 @@ struct lbm_ctx {
     int diag_every = 0;
     int cus = 0;
     long diag_t = -1;
+    lbm_host::HostCopier copier;  // large arrays to host memory
     std::string err;
 };
 
@@ -370,6 +372,14 @@ int run_bricks(lbm_ctx *c, int region, int steps)
     default: return run_bricks_t<ST_BF16>(c, region, steps);
     }
 }
+
+// n device arrays of `bytes` each to the caller's memory (null: skipped).
+int copy_out(lbm_ctx *c, void *const *dst, const void *const *src, size_t bytes, int n)
+{
+    HIPCHK(c, c->copier.copy(c->device, c->stream, dst, src, bytes, n));
+    return LBM_OK;
+}
+int copy_out(lbm_ctx *c, void *dst, const void *src, size_t bytes) { return copy_out(c, &dst, &src, bytes, 1); }
 
 int ready(lbm_ctx *c)
 {
@@ -794,9 +804,7 @@ int lbm_get_populations(lbm_ctx *c, double *f)
     if (rc) return rc;
     rc = pull_window(c, 0, 0, c->nx, c->ny, c->d_tmp);
     if (rc) return rc;
-    HIPCHK(c, hipMemcpyAsync(f, c->d_tmp, (size_t)c->N * 18 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    return LBM_OK;
+    return copy_out(c, f, c->d_tmp, (size_t)c->N * 18 * sizeof(double));
 }
 
 int lbm_get_populations_window(lbm_ctx *c, int x0, int y0, int w, int h, double *f)
@@ -813,9 +821,7 @@ int lbm_get_populations_window(lbm_ctx *c, int x0, int y0, int w, int h, double 
     if (rc) return rc;
     rc = pull_window(c, x0, y0, w, h, c->d_tmp);
     if (rc) return rc;
-    HIPCHK(c, hipMemcpyAsync(f, c->d_tmp, bytes, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    return LBM_OK;
+    return copy_out(c, f, c->d_tmp, bytes);
 }
 
 int lbm_step(lbm_ctx *c, int n)
@@ -911,13 +917,10 @@ int lbm_get_fields(lbm_ctx *c, double *rho1, double *rho2, double *ux, double *u
     if (rc) return rc;
     rc = fields_and_reduce(c);
     if (rc) return rc;
-    double *outs[4] = {rho1, rho2, ux, uy};
-    for (int q = 0; q < 4; ++q)
-        if (outs[q])
-            HIPCHK(c, hipMemcpyAsync(outs[q], c->d_tmp + (size_t)q * c->N, (size_t)c->N * sizeof(double),
-                                     hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    return LBM_OK;
+    void *const outs[4] = {rho1, rho2, ux, uy};
+    const void *src[4];
+    for (int q = 0; q < 4; ++q) src[q] = c->d_tmp + (size_t)q * c->N;
+    return copy_out(c, outs, src, (size_t)c->N * sizeof(double), 4);
 }
 
 int lbm_reduce(lbm_ctx *c, double out[8])
@@ -1131,8 +1134,8 @@ int lbm_save(lbm_ctx *c, const char *path)
     if (!path) return set_err(c, LBM_EINVAL, "null path");
     const size_t bytes = (size_t)c->N * 18 * elem_size(c->storage);
     std::vector<char> host(bytes);
-    HIPCHK(c, hipMemcpyAsync(host.data(), c->buf[c->cur], bytes, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+    rc = copy_out(c, host.data(), c->buf[c->cur], bytes);
+    if (rc) return rc;
     CkptHeader h;
     std::memset(&h, 0, sizeof h);
     std::memcpy(h.magic, "LBM2CPK", 8);
