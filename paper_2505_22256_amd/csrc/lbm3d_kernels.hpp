@@ -330,99 +330,91 @@ __device__ __forceinline__ C local_G3(const KParams3<C> &p, C re)
     return p.Gw2;
 }
 
-// The stencil again as a table in constant memory, for the near-wall path,
-// which walks it in a loop that is not unrolled (it runs only where a wall
-// is within two nodes, and unrolled it would take twice the registers of
-// everything else).  One 32-bit word per opposite pair (n, n + 1), so that
-// the uniform loop index turns each entry into one scalar load (bytes
-// would take vector loads, and every such wait would also drain the
-// population loads in flight): bits 0-8 the offset e_n (x, y, z, each + 2
-// in 3 bits), bit 9 set for a second-layer position, bits 10-18 its
-// first-layer partner (same coding).  Position n + 1 and its partner are
-// the negations.  The weight W(|e_n|^2) goes beside it.
-struct NearTable3 {
-    uint32_t code[NS3 / 2];
-    double w[NS3 / 2];
-};
-
-constexpr NearTable3 make_near3()
-{
-    NearTable3 t{};
-    for (int q = 0; q < NS3 / 2; ++q) {
-        const int n = 2 * q, x = kS3.x[n], y = kS3.y[n], z = kS3.z[n], m = kS3.partner[n];
-        uint32_t c = (uint32_t)(x + 2) | (uint32_t)(y + 2) << 3 | (uint32_t)(z + 2) << 6;
-        if (m >= 0)
-            c |= 1u << 9 | (uint32_t)(kS3.x[m] + 2) << 10 | (uint32_t)(kS3.y[m] + 2) << 13 |
-                 (uint32_t)(kS3.z[m] + 2) << 16;
-        t.code[q] = c;
-        t.w[q] = e8w3(x * x + y * y + z * z);
-    }
-    return t;
-}
-
-__constant__ NearTable3 c_near3 = make_near3();
-
 // A brick of BXB x BYB x BZB nodes and its psi tile (2-node halo).
 template <int BXB, int BYB, int BZB> struct Brick {
     static constexpr int TX = BXB + 4, TY = BYB + 4, TZ = BZB + 4, NT = BXB * BYB;
     static constexpr int at(int x, int y, int z) { return (z * TY + y) * TX + x; }  // tile coordinates
 };
 
-// Stencil value at offset (dx, dy, dz) from tile index c after the wall
-// rules (Sec. 2.4): an unavailable first-layer position reads zero (psi(x)
-// under WALLPSI_SELF), an unavailable second-layer one what its partner m
-// resolves to (zero under E8_COPY_OFF).  `solid` returns the switch s of
-// Eq. 9 there.
-template <class C>
-__device__ __forceinline__ PsiPair<C> resolve3(const PsiPair<C> *tile, int c, int off, bool second, int poff,
-                                               PsiPair<C> first, unsigned flags, bool &solid)
+// The stencil again as a table in constant memory, for the near-wall path,
+// which walks it in a loop (it runs only where a wall is within two nodes,
+// and unrolled it would take twice the registers of everything else).  One
+// entry per opposite pair (n, n + 1), in the brick's tile offsets, so that
+// the uniform loop index makes an entry a scalar load: the offset of position
+// n, that of its first-layer partner, which components of e_n are nonzero
+// (bits 0-2) and whether the position lies in the second layer (bit 3), and
+// the products W(|e_n|^2) e_n.  Tile offsets are linear: position n + 1 and
+// its partner are the negations.
+template <class C> struct NearEntry3 {
+    int off, poff, bits, pad;
+    C we[4];
+};
+template <class BR, class C> struct NearTable3 {
+    NearEntry3<C> e[NS3 / 2];
+};
+
+template <class BR, class C> constexpr NearTable3<BR, C> make_near3()
 {
-    const PsiPair<C> v = tile[c + off];
-    solid = lds_sent(v.a);
-    if (!solid) return v;
-    if (!second) return first;
-    if (flags & F3_COPY_OFF) {
-        PsiPair<C> zero;
-        zero.a = 0;
-        zero.b = 0;
-        return zero;
+    NearTable3<BR, C> t{};
+    for (int q = 0; q < NS3 / 2; ++q) {
+        const int n = 2 * q, x = kS3.x[n], y = kS3.y[n], z = kS3.z[n], m = kS3.partner[n];
+        const double w = e8w3(x * x + y * y + z * z);
+        t.e[q].off = BR::at(x, y, z);
+        t.e[q].poff = m >= 0 ? BR::at(kS3.x[m], kS3.y[m], kS3.z[m]) : 0;
+        t.e[q].bits = (x != 0) | (y != 0) << 1 | (z != 0) << 2 | (m >= 0) << 3;
+        t.e[q].we[0] = (C)(w * x);
+        t.e[q].we[1] = (C)(w * y);
+        t.e[q].we[2] = (C)(w * z);
     }
-    const PsiPair<C> w = tile[c + poff];
-    return lds_sent(w.a) ? first : w;
+    return t;
 }
 
+template <class BR, class C> __constant__ NearTable3<BR, C> c_near3 = make_near3<BR, C>();
+
 // Cohesion and adhesion sums at a node with unavailable stencil positions,
-// by opposite pairs in the order of the bulk path.
+// by opposite pairs in the order and with the products of the bulk path.  The
+// wall rules (Sec. 2.4): an unavailable first-layer position reads zero
+// (psi(x) under WALLPSI_SELF), an unavailable second-layer one what its
+// partner resolves to (zero under E8_COPY_OFF).  A position and its partner
+// are read together and chosen between afterwards: a branch per lane, with
+// the partner's read behind it, makes each pair two LDS round trips.  72 x
+// 65 x 40 nodes, us per step, with the staging below: FP32 at tau = 1 44.4 ->
+// 40.8, FP16 52.6 -> 47.3, FP64 87.7 -> 80.9; 200 x 200 x 280 the same as
+// before (there the other wavefronts hide it).
 template <class BR, class C>
 __device__ __forceinline__ void near_sums3(const PsiPair<C> *tile, int c, C r1, C r2, unsigned flags, C (&s1)[3],
                                            C (&s2)[3], C (&Sv)[3])
 {
-    PsiPair<C> first;
-    first.a = (flags & F3_WALLPSI_SELF) ? r1 : (C)0;
-    first.b = (flags & F3_WALLPSI_SELF) ? r2 : (C)0;
+    // (values, not pairs: a choice between structs would go through memory)
+    const C f1 = (flags & F3_WALLPSI_SELF) ? r1 : (C)0, f2 = (flags & F3_WALLPSI_SELF) ? r2 : (C)0;
+    const bool copy_off = flags & F3_COPY_OFF;
+    const C g1 = copy_off ? (C)0 : f1, g2 = copy_off ? (C)0 : f2;
     for (int d = 0; d < 3; ++d) {
         s1[d] = 0;
         s2[d] = 0;
         Sv[d] = 0;
     }
-#pragma unroll 1
+#pragma unroll 2
     for (int q = 0; q < NS3 / 2; ++q) {
-        const uint32_t code = c_near3.code[q];
-        const int ex = (int)(code & 7u) - 2, ey = (int)(code >> 3 & 7u) - 2, ez = (int)(code >> 6 & 7u) - 2;
-        const bool second = (code >> 9) & 1u;
-        // tile offsets are linear in (x, y, z): the opposite's is the negation
-        const int off = BR::at(ex, ey, ez);
-        const int poff = BR::at((int)(code >> 10 & 7u) - 2, (int)(code >> 13 & 7u) - 2, (int)(code >> 16 & 7u) - 2);
-        bool ua, ub;
-        const PsiPair<C> a = resolve3<C>(tile, c, off, second, poff, first, flags, ua);
-        const PsiPair<C> b = resolve3<C>(tile, c, -off, second, -poff, first, flags, ub);
-        const C w = (C)c_near3.w[q];
-        const C d1 = a.a - b.a, d2 = a.b - b.b, ds = (C)(int)ua - (C)(int)ub;
-        // the same products and order as the unrolled bulk path (w times
-        // +-1 or +-2 is exact, so w e is the bulk path's constant)
-        if (ex != 0) { const C wx = w * (C)ex; s1[0] += wx * d1; s2[0] += wx * d2; Sv[0] += wx * ds; }
-        if (ey != 0) { const C wy = w * (C)ey; s1[1] += wy * d1; s2[1] += wy * d2; Sv[1] += wy * ds; }
-        if (ez != 0) { const C wz = w * (C)ez; s1[2] += wz * d1; s2[2] += wz * d2; Sv[2] += wz * ds; }
+        const NearEntry3<C> &t = c_near3<BR, C>.e[q];
+        const bool second = t.bits & 8;
+        const PsiPair<C> a = tile[c + t.off], b = tile[c - t.off];
+        const bool ua = lds_sent(a.a), ub = lds_sent(b.a);
+        // what an unavailable position reads
+        C fa1 = f1, fa2 = f2, fb1 = f1, fb2 = f2;
+        if (second) {
+            const PsiPair<C> pa = tile[c + t.poff], pb = tile[c - t.poff];
+            const bool na = copy_off || lds_sent(pa.a), nb = copy_off || lds_sent(pb.a);
+            fa1 = na ? g1 : pa.a;
+            fa2 = na ? g2 : pa.b;
+            fb1 = nb ? g1 : pb.a;
+            fb2 = nb ? g2 : pb.b;
+        }
+        const C d1 = (ua ? fa1 : a.a) - (ub ? fb1 : b.a), d2 = (ua ? fa2 : a.b) - (ub ? fb2 : b.b);
+        const C ds = (C)(int)ua - (C)(int)ub;
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+            if (t.bits >> d & 1) { s1[d] += t.we[d] * d1; s2[d] += t.we[d] * d2; Sv[d] += t.we[d] * ds; }
     }
 }
 
@@ -732,23 +724,29 @@ __attribute__((amdgpu_waves_per_eu((S == lbm::ST_F32 && !(MODE & K3_REDUCE)) ? 4
         const int byi = row % p.bricks_y, bzi = row / p.bricks_y;
         const int x0 = bxi * BXB, y0 = byi * BYB, z0 = bzi * BZB;
         const bool wx = p.flags & F3_PERIODIC_X, wy = p.flags & F3_PERIODIC_Y, wz = p.flags & F3_PERIODIC_Z;
-        // psi of the brick and its halo (outside a closed face: the sentinel)
-        for (int t = tid; t < BR::TX * BR::TY * BR::TZ; t += NTH) {
-            const int lx = t % BR::TX, r = t / BR::TX;
-            const int ly = r % BR::TY, lz = r / BR::TY;
-            // (a brick may be wider than a small periodic lattice: full wrap)
-            const Axis gx = make_axis(x0 - 2 + lx, p.nx, wx);
-            const Axis gy = make_axis(y0 - 2 + ly, p.ny, wy);
-            const Axis gz = make_axis(z0 - 2 + lz, p.nz, wz);
-            PsiPair<C> v;
-            if (gx.ok && gy.ok && gz.ok) {
-                v = p.psi[((long long)gz.c * p.ny + gy.c) * p.nx + gx.c];
-            } else {
-                v.a = lds_sentinel<C>();
-                v.b = lds_sentinel<C>();
+        // psi of the brick and its halo (outside a closed face: the sentinel).  A
+        // brick of a lattice at least as wide reaches one period out at most
+        // and wraps without a division.
+        const bool roomy = p.nx >= BXB + 2 && p.ny >= BYB + 2 && p.nz >= BZB + 2;
+        auto stage = [&](auto &&axis) {
+            for (int t = tid; t < BR::TX * BR::TY * BR::TZ; t += NTH) {
+                const int lx = t % BR::TX, r = t / BR::TX;
+                const int ly = r % BR::TY, lz = r / BR::TY;
+                const Axis gx = axis(x0 - 2 + lx, p.nx, wx);
+                const Axis gy = axis(y0 - 2 + ly, p.ny, wy);
+                const Axis gz = axis(z0 - 2 + lz, p.nz, wz);
+                PsiPair<C> v;
+                if (gx.ok && gy.ok && gz.ok) {
+                    v = p.psi[((uint32_t)gz.c * (uint32_t)p.ny + (uint32_t)gy.c) * (uint32_t)p.nx + (uint32_t)gx.c];
+                } else {
+                    v.a = lds_sentinel<C>();
+                    v.b = lds_sentinel<C>();
+                }
+                tile[t] = v;
             }
-            tile[t] = v;
-        }
+        };
+        if (roomy) stage([](int v, int n, bool per) { return make_axis_near(v, n, per); });
+        else stage([](int v, int n, bool per) { return make_axis(v, n, per); });
         __syncthreads();
         const int lx = tid % BXB, ly = (tid / BXB) % BYB, lt = tid / (BXB * BYB);
         const int x = x0 + lx, y = y0 + ly;
