@@ -336,18 +336,15 @@ template <int BXB, int BYB, int BZB> struct Brick {
     static constexpr int at(int x, int y, int z) { return (z * TY + y) * TX + x; }  // tile coordinates
 };
 
-// The stencil again as a table in constant memory, for the near-wall path,
-// which walks it in a loop (it runs only where a wall is within two nodes,
-// and unrolled it would take twice the registers of everything else).  One
-// entry per opposite pair (n, n + 1), in the brick's tile offsets, so that
-// the uniform loop index makes an entry a scalar load: the offset of position
-// n, that of its first-layer partner, which components of e_n are nonzero
-// (bits 0-2) and whether the position lies in the second layer (bit 3), and
-// the products W(|e_n|^2) e_n.  Tile offsets are linear: position n + 1 and
-// its partner are the negations.
+// The stencil for the near-wall path.  One entry per opposite pair (n, n + 1),
+// in the brick's tile offsets: the offset of position n, that of its
+// first-layer partner, which components of e_n are nonzero (bits 0-2) and
+// whether the position lies in the second layer (bit 3), and the products
+// W(|e_n|^2) e_n.  Tile offsets are linear: position n + 1 and its partner are
+// the negations.
 template <class C> struct NearEntry3 {
-    int off, poff, bits, pad;
-    C we[4];
+    int off, poff, bits;
+    C we[3];
 };
 template <class BR, class C> struct NearTable3 {
     NearEntry3<C> e[NS3 / 2];
@@ -369,18 +366,21 @@ template <class BR, class C> constexpr NearTable3<BR, C> make_near3()
     return t;
 }
 
-template <class BR, class C> __constant__ NearTable3<BR, C> c_near3 = make_near3<BR, C>();
-
 // Cohesion and adhesion sums at a node with unavailable stencil positions,
 // by opposite pairs in the order and with the products of the bulk path.  The
 // wall rules (Sec. 2.4): an unavailable first-layer position reads zero
 // (psi(x) under WALLPSI_SELF), an unavailable second-layer one what its
 // partner resolves to (zero under E8_COPY_OFF).  A position and its partner
 // are read together and chosen between afterwards: a branch per lane, with
-// the partner's read behind it, makes each pair two LDS round trips.  72 x
-// 65 x 40 nodes, us per step, with the staging below: FP32 at tau = 1 44.4 ->
-// 40.8, FP16 52.6 -> 47.3, FP64 87.7 -> 80.9; 200 x 200 x 280 the same as
-// before (there the other wavefronts hide it).
+// the partner's read behind it, makes each pair two LDS round trips.
+// Unrolled, with a compiler fence at each pair: the reads of the next pair are
+// issued over the arithmetic of this one, and no more of them are held.  (As a
+// loop over the table in constant memory a wavefront waited for the entry of
+// each pair, then for its reads; without the fences FP32 spills.)  72 x 65 x
+// 40 nodes in 32 x 8 x 4 bricks, us per step, loop / unrolled: at tau = 1 FP32
+// 40.5 / 27.3, FP16 42.4 / 31.5, FP64 53.9 / 40.5, at tau = 1.1 with two
+// threads per column 63.8 / 38.5, 64.9 / 39.9, 80.4 / 58.0; 200 x 200 x 280 at
+// tau = 1: 980 / 953, 646 / 640, 1721 / 1702 (other wavefronts hide most).
 template <class BR, class C>
 __device__ __forceinline__ void near_sums3(const PsiPair<C> *tile, int c, C r1, C r2, unsigned flags, C (&s1)[3],
                                            C (&s2)[3], C (&Sv)[3])
@@ -394,9 +394,11 @@ __device__ __forceinline__ void near_sums3(const PsiPair<C> *tile, int c, C r1, 
         s2[d] = 0;
         Sv[d] = 0;
     }
-#pragma unroll 2
+    constexpr NearTable3<BR, C> T = make_near3<BR, C>();
+#pragma unroll
     for (int q = 0; q < NS3 / 2; ++q) {
-        const NearEntry3<C> &t = c_near3<BR, C>.e[q];
+        asm volatile("" ::: "memory");
+        const NearEntry3<C> t = T.e[q];
         const bool second = t.bits & 8;
         const PsiPair<C> a = tile[c + t.off], b = tile[c - t.off];
         const bool ua = lds_sent(a.a), ub = lds_sent(b.a);
