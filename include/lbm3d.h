@@ -127,8 +127,8 @@ int lbm3d_contact_angle(lbm3d_ctx *c, int wall_kind, const double wall[4], doubl
  * plane of it), one of 32 x 8 x 4 with tz 1, 2 or 4, 32 x 8 x 8 with tz 1
  * or 2, and 64 x 4 x 4 with tz 2; EINVAL otherwise.  The default is
  * 32 x 8 x 4 with tz 2 for FP32 and with tz 1 for the other storages; until a
- * brick is set, the library takes more threads per column on small lattices
- * and at tau = 1 (lbm3d_get_tile keeps giving the default).  Each step runs
+ * brick is set, the library takes smaller bricks on small lattices and more
+ * threads per column at tau = 1 (lbm3d_get_tile keeps giving the default).  Each step runs
  * a density pass (psi = rho of every node from the pulled populations, 2
  * values per node) and then the collide pass, which stages psi of its brick
  * and a 2-node halo in LDS and pulls the populations of its own nodes; at

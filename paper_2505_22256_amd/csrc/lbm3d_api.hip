@@ -139,34 +139,50 @@ KParams3<C> make_params3(const lbm3d_ctx *c, const void *A, void *B, int bx, int
     return p;
 }
 
-// Threads in z of the collide pass: the caller's, or for the default brick
-// the number that this lattice runs best with (us per step with 1 / 2 / 4).
-// A lattice of fewer bricks than two per compute unit is bound by the march of
-// one thread and gets one node per thread (72 x 65 x 40: FP32 100 / 65 / 45,
-// FP16 103 / 65 / 48), except the FP64 kernel with populations, whose 1024
-// threads have no registers for it (115 / 80 / 92).  At relaxation time 1 the
-// collide kernels are light and want more wavefronts (200 x 200 x 280: FP32
-// 1090 / 1040 / 980, FP16 680 / 650 / 750, FP64 1930 / 1780 / 1730); else the
-// defaults stand (FP32 1360 / 1294 / 1345, FP16 858 / 1033 / 1122, FP64 2328 /
-// 2379 / 4104).
-int collide_tz(const lbm3d_ctx *c, int cus)
+struct Brick3 {
+    int bx, by, bz, tz;
+};
+
+// Whether a lattice is of fewer than `per_cu` bricks of 16 x 4 x 4 per compute
+// unit and runs in them, one node per thread: 256 threads start and end apart
+// from each other, where workgroups of 1024 (the general kernels have registers
+// for one on a compute unit) leave a last round nearly empty.  us per step,
+// 32 x 8 x 4 bricks with the best threads in z / these, at relaxation time 1
+// and 1.1: 72 x 65 x 40 nodes FP32 27.3 / 26.4 and 38.0 / 31.1, FP16 31.5 /
+// 28.6 and 39.9 / 35.3, FP64 40.5 / 38.1 and 58.0 / 47.6; 96^3 (13.5 bricks)
+// FP32 68.1 / 65.8 and 81.5 / 79.4, FP16 56.8 / 52.7 and 77.8 / 73.4, FP64
+// 144.7 / 147.0 and 187.0 / 183.0; 128^3 (32 bricks) FP32 204 / 213 and 237 /
+// 247, FP16 123 / 124 and 175 / 165, FP64 330 / 333 and 424 / 444: 16.
+// The field and diagnostic passes, which store no population: 72 x 65 x 40
+// FP32 46 / 26 us, 96^3 54 / 59: 8.
+bool small_lattice(const lbm3d_ctx *c, int per_cu)
 {
-    if (c->own_tile) return c->tz;
-    const bool tau1 = c->tau == 1.0 && c->d_mom;
-    const long long bricks = (long long)((c->nx + c->bx - 1) / c->bx) * ((c->ny + c->by - 1) / c->by) *
-                             ((c->nz + c->bz - 1) / c->bz);
-    if (bricks < 2LL * cus) return c->storage == LBM_F64 && !tau1 ? 2 : 4;
-    if (tau1) return c->storage == LBM_F16 || c->storage == LBM_BF16 ? 2 : 4;
-    return c->tz;
+    const long long bricks = (long long)((c->nx + 15) / 16) * ((c->ny + 3) / 4) * ((c->nz + 3) / 4);
+    return bricks < (long long)per_cu * c->cus;
+}
+
+// Brick and threads in z of the stepping pass: the caller's, or those that
+// this lattice runs best with.  Large lattices take the default brick (us per
+// step with 1 / 2 / 4 threads in z): at relaxation time 1 the collide kernels
+// are light and want more wavefronts (200 x 200 x 280: FP32 1090 / 1040 / 953,
+// FP16 671 / 640 / 723, FP64 1870 / 1765 / 1702); else the defaults stand (FP32
+// 1349 / 1284 / 1334, FP16 837 / 996 / 1074, FP64 2298 / 2303 / 4200).
+Brick3 step_brick(const lbm3d_ctx *c)
+{
+    if (c->own_tile) return {c->bx, c->by, c->bz, c->tz};
+    if (small_lattice(c, 16)) return {16, 4, 4, 4};
+    const bool half = c->storage == LBM_F16 || c->storage == LBM_BF16;
+    return {32, 8, 4, c->tau == 1.0 && c->d_mom ? (half ? 2 : 4) : c->tz};
 }
 
 template <int S>
 int run_pass3_t(lbm3d_ctx *c, Pass3 pass, double *fields, int *nparts)
 {
     using C = typename lbm::Traits<S>::C;
-    const bool fp = pass == P3_FIELDS_REDUCE;
-    KParams3<C> p = make_params3<C>(c, c->buf[c->cur], c->buf[c->cur ^ 1], fp ? 32 : c->bx, fp ? 8 : c->by,
-                                    fp ? 4 : c->bz);
+    const Brick3 b = pass == P3_STEP        ? step_brick(c)
+                     : small_lattice(c, 8) ? Brick3{16, 4, 4, 4}
+                                           : Brick3{32, 8, 4, 1};
+    KParams3<C> p = make_params3<C>(c, c->buf[c->cur], c->buf[c->cur ^ 1], b.bx, b.by, b.bz);
     const int grid = collide3_grid(p);
     if (nparts) *nparts = grid;
     if (pass != P3_STEP) {
@@ -182,7 +198,7 @@ int run_pass3_t(lbm3d_ctx *c, Pass3 pass, double *fields, int *nparts)
         p.out_uz = fields + 4 * c->N;
     }
     const bool sr = (S == lbm::ST_F16 || S == lbm::ST_BF16) && (c->flags & LBM_ROUND_STOCHASTIC);
-    const hipError_t e = launch3<S>(p, pass, c->bx, c->by, c->bz, collide_tz(c, c->cus), sr, c->stream);
+    const hipError_t e = launch3<S>(p, pass, b.bx, b.by, b.bz, b.tz, sr, c->stream);
     if (e != hipSuccess) return fail(c, LBM_EDEVICE, "kernel launch failed: %s", hipGetErrorString(e));
     return LBM_OK;
 }
@@ -257,17 +273,23 @@ int check_adh3(lbm3d_ctx *c, double Gw1, double Gw2, double delta)
     return LBM_OK;
 }
 
-// Fields + diagnostics pass into d_tmp (5N doubles) and d_out[0..8].
-int fields_reduce3(lbm3d_ctx *c)
+// The diagnostics into d_out[0..8], with the fields (5N doubles) or without
+// (P3_REDUCE: 40 B per node not written; 200^3 FP32 418 -> 371 us).
+int reduce3(lbm3d_ctx *c, Pass3 pass, double *fields)
 {
-    int rc = ensure_tmp(c, (size_t)c->N * 5 * sizeof(double));
-    if (rc) return rc;
     int nparts = 0;
-    rc = run_pass3(c, P3_FIELDS_REDUCE, c->d_tmp, &nparts);
+    const int rc = run_pass3(c, pass, fields, &nparts);
     if (rc) return rc;
     hipLaunchKernelGGL(k_reduce3_final, dim3(1), dim3(256), 0, c->stream, c->d_partials, nparts, c->d_out);
     HIPCHK3(c, hipGetLastError());
     return LBM_OK;
+}
+
+// Fields + diagnostics pass into d_tmp and d_out.
+int fields_reduce3(lbm3d_ctx *c)
+{
+    const int rc = ensure_tmp(c, (size_t)c->N * 5 * sizeof(double));
+    return rc ? rc : reduce3(c, P3_FIELDS_REDUCE, c->d_tmp);
 }
 
 }  // namespace
@@ -532,7 +554,7 @@ int lbm3d_reduce(lbm3d_ctx *c, double out[9])
     int rc = ready3(c);
     if (rc) return rc;
     if (!out) return fail(c, LBM_EINVAL, "null output");
-    rc = fields_reduce3(c);
+    rc = reduce3(c, P3_REDUCE, nullptr);
     if (rc) return rc;
     HIPCHK3(c, hipMemcpyAsync(out, c->d_out, 9 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK3(c, hipStreamSynchronize(c->stream));

@@ -7,9 +7,9 @@
 
 namespace lbm3_host {
 
-// Kinds of pass: one step (optionally with the diagnostics), or the
-// fields + diagnostics pass.
-enum Pass3 { P3_STEP, P3_STEP_REDUCE, P3_FIELDS_REDUCE };
+// Kinds of pass: one step, the fields + diagnostics pass, or the diagnostics
+// alone.
+enum Pass3 { P3_STEP, P3_FIELDS_REDUCE, P3_REDUCE };
 
 // Launch one pass (the density pass, then the collide pass with the
 // instance selected by the brick bx x by x bz with tz threads in z, the
