@@ -106,7 +106,7 @@ __device__ __forceinline__ void process_brick(const KParams<typename Traits<S>::
     // nodes between this one and the edge of the region
     const int edge = min(min(lx, RX - 1 - lx), min(ly, RY - 1 - ly));
     RedAcc none;
-    StateOf<S, MODE> st;
+    StateOf<S, M_STORE | MODE> st;
     for (int s = 0; s < steps; ++s) {
         if (edge >= 3 * s) {
             RawRow<S> q;
@@ -124,7 +124,7 @@ __device__ __forceinline__ void process_brick(const KParams<typename Traits<S>::
             }
             const BrickReload<S, RX, RY> reload{mr, off, post, c, s == 0};
             C r1 = 0, r2 = 0;
-            process_node_src<S, MODE>(p, reload, cx, ry, inside, q, st, r1, r2);
+            process_node_src<S, M_STORE | MODE>(p, reload, cx, ry, inside, q, st, r1, r2);
             PsiPair<C> ps;
             ps.a = (st.info & 256) ? lds_sentinel<C>() : r1;
             ps.b = (st.info & 256) ? lds_sentinel<C>() : r2;

@@ -446,7 +446,8 @@ template <class St, class C> __device__ __forceinline__ void momenta(const St &s
 // Relaxation time 1: f* = f - (f - f^eq)/tau + (1 - 1/2tau) F_i no longer
 // holds the populations pulled (their factor 1 - omega is exactly zero), so
 // all a node needs until its collision are its densities, which lie in the
-// psi ring, and its momenta: 4 values instead of 18.
+// psi ring, and its momenta: 4 values instead of 18.  The same holds for the
+// passes that store no populations, at any relaxation time.
 template <int S> struct RowMomenta {
     using C = typename Traits<S>::C;
     C jx[2], jy[2];
@@ -456,8 +457,9 @@ template <int S> struct RowMomenta {
 // The state type of a kernel: the momenta at relaxation time 1, else the
 // populations, packed for 16-bit storage without boundary code.
 template <int S, bool BND> using FullState = RowState<S, (S == ST_F16 || S == ST_BF16) && !BND>;
+constexpr bool keeps_momenta(int mode) { return (mode & M_TAU1) || !(mode & M_STORE); }
 template <int S, int MODE>
-using StateOf = std::conditional_t<(MODE & M_TAU1) != 0, RowMomenta<S>, FullState<S, (MODE & M_BND) != 0>>;
+using StateOf = std::conditional_t<keeps_momenta(MODE), RowMomenta<S>, FullState<S, (MODE & M_BND) != 0>>;
 
 // Cohesion sums sum_n W_n e_n Psi_n over the 24 positions, by opposite
 // pairs (n, n+2) in each group of four (Eq. 8 on the E8 stencil).

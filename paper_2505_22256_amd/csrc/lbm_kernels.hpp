@@ -246,7 +246,7 @@ __device__ __forceinline__ void process_full(const KParams<typename Traits<S>::C
 }
 
 // The same into the state the kernel keeps: the populations, or their
-// momenta (relaxation time 1).
+// momenta (relaxation time 1, and the passes that store none).
 template <int S, int MODE, class Reload>
 __device__ __forceinline__ void process_node_src(const KParams<typename Traits<S>::C> &p, const Reload &reload,
                                                  const Axis &cx, const Axis &ry, bool valid, const RawRow<S> &q,
@@ -254,7 +254,7 @@ __device__ __forceinline__ void process_node_src(const KParams<typename Traits<S
                                                  typename Traits<S>::C &r2)
 {
     constexpr bool BND = (MODE & M_BND) != 0;
-    if constexpr (MODE & M_TAU1) {
+    if constexpr (keeps_momenta(MODE)) {
         RowState<S> f;
         process_full<S, BND>(p, reload, cx, ry, valid, q, f, r1, r2);
         st.info = f.info;
@@ -479,7 +479,7 @@ __device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C>
     const C r1 = ctr.a, r2 = ctr.b;
 
     C jx[2], jy[2];
-    if constexpr (MODE & M_TAU1) {
+    if constexpr (keeps_momenta(MODE)) {
         jx[0] = st.jx[0];
         jx[1] = st.jx[1];
         jy[0] = st.jy[0];
@@ -608,7 +608,7 @@ __device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C>
         C gs[2][9];
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            if constexpr (MODE & M_TAU1) gs[k][0] = (C)qw(0) * c0[k];
+            if constexpr (keeps_momenta(MODE)) gs[k][0] = (C)qw(0) * c0[k];
             else gs[k][0] = p.omw * st.get(k, 0) + (C)qw(0) * c0[k];
         }
 #pragma unroll
@@ -625,7 +625,7 @@ __device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C>
                 const C eF = ex == 0 ? (C)ey * Fy[k] : (ey == 0 ? (C)ex * Fx[k] : (C)ex * Fx[k] + (C)ey * Fy[k]);
                 const C E = (c0[k] + c2[k] * eu2) + h9 * eF;
                 const C O = c1[k] * eu + p.cf3 * eF;
-                if constexpr (MODE & M_TAU1) {
+                if constexpr (keeps_momenta(MODE)) {
                     gs[k][i] = w * (E + O);
                     gs[k][o] = w * (E - O);
                 } else {
@@ -1230,9 +1230,9 @@ k_pull_window(const KParams<typename Traits<S>::C> p, int x0, int y0, int w, int
     const PopMem<S> m = make_mem<S>(p.A, p.N);
     RawRow<S> raw;
     issue_node<S>(m, p.nx, cx, ry, true, raw);
-    StateOf<S, M_BND> st;
+    StateOf<S, M_STORE | M_BND> st;
     C r1, r2;
-    process_node<S, M_BND>(p, m, cx, ry, true, raw, st, r1, r2);
+    process_node<S, M_STORE | M_BND>(p, m, cx, ry, true, raw, st, r1, r2);
     const bool solid = st.info & 256;
 #pragma unroll
     for (int k = 0; k < 2; ++k)
