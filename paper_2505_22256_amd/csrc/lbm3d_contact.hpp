@@ -55,41 +55,10 @@ k_cc3_links(lbm::RunSet rs, lbm::RegionMem m, const double *__restrict__ r1, con
     lbm::links_of_run<3>(rs, m, pt);
 }
 
-static __device__ bool solve4(double A[4][4], double b[4], double x[4])
-{
-    double M[4][5];
-    for (int r = 0; r < 4; ++r) {
-        for (int q = 0; q < 4; ++q) M[r][q] = A[r][q];
-        M[r][4] = b[r];
-    }
-    for (int col = 0; col < 4; ++col) {
-        int piv = col;
-        for (int r = col + 1; r < 4; ++r)
-            if (__builtin_fabs(M[r][col]) > __builtin_fabs(M[piv][col])) piv = r;
-        if (M[piv][col] == 0.0) return false;
-        if (piv != col)
-            for (int q = 0; q < 5; ++q) {
-                const double tmp = M[col][q];
-                M[col][q] = M[piv][q];
-                M[piv][q] = tmp;
-            }
-        for (int r = col + 1; r < 4; ++r) {
-            const double fct = M[r][col] / M[col][col];
-            for (int q = col; q < 5; ++q) M[r][q] -= fct * M[col][q];
-        }
-    }
-    for (int r = 3; r >= 0; --r) {
-        double s = M[r][4];
-        for (int q = r + 1; q < 4; ++q) s -= M[r][q] * x[q];
-        x[r] = s / M[r][r];
-    }
-    return true;
-}
-
 // One workgroup of 1024 threads over the list of interface links: out = theta
 // (deg), centre (3), radius, number of points, status (0 ok, 1 too few
-// points, 2 fit failed).  Every pass recomputes the points in a fixed order
-// per thread and sums with a fixed tree, so the result is deterministic.
+// points, 2 fit failed).  Every pass sums the points in a fixed order, so the
+// result is deterministic.
 static __global__ void __launch_bounds__(1024)
 k_contact3(lbm::RunSet rs, lbm::RegionMem mem, int nblocks, const double *__restrict__ r1,
            const double *__restrict__ r2, Wall3 wd, double *out)
@@ -107,12 +76,11 @@ k_contact3(lbm::RunSet rs, lbm::RegionMem mem, int nblocks, const double *__rest
         double dist;
         link_point3(q.nx, q.ny, r1, r2, wd, (int)(l / 3u), (int)(l % 3u), pt, dist);
     };
+    const lbm::FitPoints<3, NT, 4, decltype(point)> points(M, point);
     double m[3] = {0, 0, 0};
-    for (int i = t; i < M; i += NT) {
-        double p[3];
-        point(i, p);
+    points.each([&](const double (&p)[3]) {
         for (int d = 0; d < 3; ++d) m[d] += p[d];
-    }
+    });
     lbm::block_sum<3, NT>(m, sh);
     if (M < 4) {
         if (t == 0) {
@@ -125,22 +93,20 @@ k_contact3(lbm::RunSet rs, lbm::RegionMem mem, int nblocks, const double *__rest
     const double mx = m[0] / M, my = m[1] / M, mz = m[2] / M;
     // algebraic fit x^2 + y^2 + z^2 + D x + E y + F z + G = 0 on centred points
     double k14[14] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    for (int i = t; i < M; i += NT) {
-        double p[3];
-        point(i, p);
+    points.each([&](const double (&p)[3]) {
         const double u = p[0] - mx, v = p[1] - my, w = p[2] - mz, s = u * u + v * v + w * w;
         k14[0] += u * u; k14[1] += u * v; k14[2] += u * w; k14[3] += u;
         k14[4] += v * v; k14[5] += v * w; k14[6] += v;
         k14[7] += w * w; k14[8] += w;
         k14[9] += 1.0;
         k14[10] -= u * s; k14[11] -= v * s; k14[12] -= w * s; k14[13] -= s;
-    }
+    });
     lbm::block_sum<14, NT>(k14, sh);
     if (t == 0) {
-        double A[4][4] = {{k14[0], k14[1], k14[2], k14[3]}, {k14[1], k14[4], k14[5], k14[6]},
-                          {k14[2], k14[5], k14[7], k14[8]}, {k14[3], k14[6], k14[8], k14[9]}};
-        double bb[4] = {k14[10], k14[11], k14[12], k14[13]}, D[4] = {0, 0, 0, 0};
-        flag = solve4(A, bb, D) ? 0 : 2;
+        double A[4][5] = {{k14[0], k14[1], k14[2], k14[3], k14[10]}, {k14[1], k14[4], k14[5], k14[6], k14[11]},
+                          {k14[2], k14[5], k14[7], k14[8], k14[12]}, {k14[3], k14[6], k14[8], k14[9], k14[13]}};
+        double D[4] = {0, 0, 0, 0};
+        flag = lbm::solve_linear<4>(A, D) ? 0 : 2;
         const double r2v = (D[0] * D[0] + D[1] * D[1] + D[2] * D[2]) / 4.0 - D[3];
         if (!(r2v > 0.0)) flag = 2;
         prm[0] = mx - D[0] / 2.0;
@@ -161,12 +127,10 @@ k_contact3(lbm::RunSet rs, lbm::RegionMem mem, int nblocks, const double *__rest
     for (int it = 0; it < 100; ++it) {
         const double cx = prm[0], cy = prm[1], cz = prm[2], rr = prm[3];
         double g14[14] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-        for (int i = t; i < M; i += NT) {
-            double p[3];
-            point(i, p);
+        points.each([&](const double (&p)[3]) {
             const double dx = p[0] - cx, dy = p[1] - cy, dz = p[2] - cz;
             const double d = __builtin_sqrt(dx * dx + dy * dy + dz * dz);
-            if (d == 0.0) continue;
+            if (d == 0.0) return;
             const double J[4] = {-dx / d, -dy / d, -dz / d, -1.0};
             const double res = d - rr;
             g14[0] += J[0] * J[0]; g14[1] += J[0] * J[1]; g14[2] += J[0] * J[2]; g14[3] += J[0] * J[3];
@@ -174,14 +138,14 @@ k_contact3(lbm::RunSet rs, lbm::RegionMem mem, int nblocks, const double *__rest
             g14[7] += J[2] * J[2]; g14[8] += J[2] * J[3];
             g14[9] += J[3] * J[3];
             g14[10] -= J[0] * res; g14[11] -= J[1] * res; g14[12] -= J[2] * res; g14[13] -= J[3] * res;
-        }
+        });
         lbm::block_sum<14, NT>(g14, sh);
         if (t == 0) {
-            double A[4][4] = {{g14[0], g14[1], g14[2], g14[3]}, {g14[1], g14[4], g14[5], g14[6]},
-                              {g14[2], g14[5], g14[7], g14[8]}, {g14[3], g14[6], g14[8], g14[9]}};
-            double bb[4] = {g14[10], g14[11], g14[12], g14[13]}, dl[4];
+            double A[4][5] = {{g14[0], g14[1], g14[2], g14[3], g14[10]}, {g14[1], g14[4], g14[5], g14[6], g14[11]},
+                              {g14[2], g14[5], g14[7], g14[8], g14[12]}, {g14[3], g14[6], g14[8], g14[9], g14[13]}};
+            double dl[4];
             flag = 1;
-            if (solve4(A, bb, dl)) {
+            if (lbm::solve_linear<4>(A, dl)) {
                 for (int k = 0; k < 4; ++k) prm[k] += dl[k];
                 const double step = __builtin_fabs(dl[0]) + __builtin_fabs(dl[1]) + __builtin_fabs(dl[2]) +
                                     __builtin_fabs(dl[3]);

@@ -304,9 +304,11 @@ int fields_run(lbm_batch *b, int r)
 
 // Fields of every run (at the batch's current time) into d_fields, one launch.
 // A run alone is latency-bound (a few workgroups, each a serial march of its
-// rows), so the runs go together and in short segments: 48 runs of 128 to
-// 512 nodes a side took 5.8 ms one after the other and 0.21 ms together.
-constexpr int FIELD_BLOCK = 256, FIELD_ROWS = 32;
+// rows), so the runs go together and in short segments: 48 runs of 128 to 512
+// nodes a side took 5.8 ms one after the other and take 0.15 ms together in
+// FP32 (strips of 252 columns in segments of 32 rows 0.17 ms, of 60 in 16 rows
+// 0.16).
+constexpr int FIELD_BLOCK = 128, FIELD_ROWS = 16;
 
 template <int S>
 int fields_all_t(lbm_batch *b)

@@ -59,42 +59,10 @@ k_cc_links(RunSet rs, RegionMem m, const double *__restrict__ rho1, const double
     links_of_run<2>(rs, m, pt);
 }
 
-static __device__ bool solve3(double A[3][3], double b[3], double x[3])
-{
-    double M[3][4];
-    for (int r = 0; r < 3; ++r) {
-        for (int q = 0; q < 3; ++q) M[r][q] = A[r][q];
-        M[r][3] = b[r];
-    }
-    for (int col = 0; col < 3; ++col) {
-        int piv = col;
-        for (int r = col + 1; r < 3; ++r)
-            if (__builtin_fabs(M[r][col]) > __builtin_fabs(M[piv][col])) piv = r;
-        if (M[piv][col] == 0.0) return false;
-        if (piv != col)
-            for (int q = 0; q < 4; ++q) {
-                const double tmp = M[col][q];
-                M[col][q] = M[piv][q];
-                M[piv][q] = tmp;
-            }
-        for (int r = col + 1; r < 3; ++r) {
-            const double fct = M[r][col] / M[col][col];
-            for (int q = col; q < 4; ++q) M[r][q] -= fct * M[col][q];
-        }
-    }
-    for (int r = 2; r >= 0; --r) {
-        double s = M[r][3];
-        for (int q = r + 1; q < 3; ++q) s -= M[r][q] * x[q];
-        x[r] = s / M[r][r];
-    }
-    return true;
-}
-
 // One workgroup per run, over the run's list of interface links.  out[run*6]:
 // theta (deg), centre x, centre y, radius, number of points, status (0 ok, 1
-// too few points, 2 fit failed).  Every pass recomputes the points from the
-// fields (a few hundred, from cache) and sums them in a fixed order, so the
-// result is deterministic and the same alone and in a batch.
+// too few points, 2 fit failed).  Every pass sums the points in a fixed order,
+// so the result is deterministic and the same alone and in a batch.
 static __global__ void __launch_bounds__(256)
 k_contact_angle(RunSet rs, RegionMem mem, int nblocks, const double *__restrict__ rho1, const double *__restrict__ rho2,
                 const WallDesc *__restrict__ walls, WallDesc one, double *out)
@@ -109,20 +77,19 @@ k_contact_angle(RunSet rs, RegionMem mem, int nblocks, const double *__restrict_
     const WallDesc wd = walls ? walls[run] : one;
     const unsigned *list = mem.list + 2 * q.off;
     const int M = (int)link_total<NT>(q, mem, nblocks);
-    auto point = [&](int i, double &px, double &py) {
+    auto point = [&](int i, double (&pt)[2]) {
         const unsigned l = list[i];
         double dist;
-        link_point(q.nx, r1, r2, wd, (int)(l >> 1), (int)(l & 1), px, py, dist);
+        link_point(q.nx, r1, r2, wd, (int)(l >> 1), (int)(l & 1), pt[0], pt[1], dist);
     };
+    const FitPoints<2, NT, 4, decltype(point)> points(M, point);
 
     // pass 1: mean
     double mn[2] = {0, 0};
-    for (int i = t; i < M; i += NT) {
-        double px, py;
-        point(i, px, py);
-        mn[0] += px;
-        mn[1] += py;
-    }
+    points.each([&](const double (&pt)[2]) {
+        mn[0] += pt[0];
+        mn[1] += pt[1];
+    });
     block_sum<2, NT>(mn, sh);
     double *o = out + (long long)run * 6;
     if (M < 3) {
@@ -134,21 +101,19 @@ k_contact_angle(RunSet rs, RegionMem mem, int nblocks, const double *__restrict_
     const double mx = mn[0] / M, my = mn[1] / M;
     // pass 2: algebraic fit on centred points
     double k9[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    for (int i = t; i < M; i += NT) {
-        double px, py;
-        point(i, px, py);
-        const double u = px - mx, v = py - my, z = u * u + v * v;
+    points.each([&](const double (&pt)[2]) {
+        const double u = pt[0] - mx, v = pt[1] - my, z = u * u + v * v;
         k9[0] += u * u; k9[1] += u * v; k9[2] += u;
         k9[3] += v * v; k9[4] += v;
         k9[5] += 1.0;
         k9[6] -= u * z; k9[7] -= v * z; k9[8] -= z;
-    }
+    });
     block_sum<9, NT>(k9, sh);
     if (t == 0) {
-        double A[3][3] = {{k9[0], k9[1], k9[2]}, {k9[1], k9[3], k9[4]}, {k9[2], k9[4], k9[5]}};
-        double bb[3] = {k9[6], k9[7], k9[8]}, DEF[3];
+        double A[3][4] = {{k9[0], k9[1], k9[2], k9[6]}, {k9[1], k9[3], k9[4], k9[7]}, {k9[2], k9[4], k9[5], k9[8]}};
+        double DEF[3] = {0, 0, 0};
         flag = 0;
-        if (!solve3(A, bb, DEF)) flag = 2;
+        if (!solve_linear<3>(A, DEF)) flag = 2;
         const double r2v = DEF[0] * DEF[0] / 4.0 + DEF[1] * DEF[1] / 4.0 - DEF[2];
         if (!(r2v > 0.0)) flag = 2;
         params[0] = mx - DEF[0] / 2.0;
@@ -166,23 +131,21 @@ k_contact_angle(RunSet rs, RegionMem mem, int nblocks, const double *__restrict_
     for (int it = 0; it < 100; ++it) {
         const double a0 = params[0], b0 = params[1], rr = params[2];
         double g9[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        for (int i = t; i < M; i += NT) {
-            double px, py;
-            point(i, px, py);
-            const double dx = px - a0, dy = py - b0;
+        points.each([&](const double (&pt)[2]) {
+            const double dx = pt[0] - a0, dy = pt[1] - b0;
             const double d = __builtin_sqrt(dx * dx + dy * dy);
-            if (d == 0.0) continue;
+            if (d == 0.0) return;
             const double J0 = -dx / d, J1 = -dy / d, J2 = -1.0, res = d - rr;
             g9[0] += J0 * J0; g9[1] += J0 * J1; g9[2] += J0 * J2;
             g9[3] += J1 * J1; g9[4] += J1 * J2; g9[5] += J2 * J2;
             g9[6] -= J0 * res; g9[7] -= J1 * res; g9[8] -= J2 * res;
-        }
+        });
         block_sum<9, NT>(g9, sh);
         if (t == 0) {
-            double A[3][3] = {{g9[0], g9[1], g9[2]}, {g9[1], g9[3], g9[4]}, {g9[2], g9[4], g9[5]}};
-            double bb[3] = {g9[6], g9[7], g9[8]}, dl[3];
+            double A[3][4] = {{g9[0], g9[1], g9[2], g9[6]}, {g9[1], g9[3], g9[4], g9[7]}, {g9[2], g9[4], g9[5], g9[8]}};
+            double dl[3];
             flag = 1;  // stop
-            if (solve3(A, bb, dl)) {
+            if (solve_linear<3>(A, dl)) {
                 params[0] += dl[0];
                 params[1] += dl[1];
                 params[2] += dl[2];

@@ -14,15 +14,13 @@
 // wavefront lane per bit), and every later test of a node and its neighbours
 // is a shift and a few logic operations on those words.  Labels start at the
 // first node of each run inside a word, so that union-find only joins runs,
-// one link per pair of runs that touch.  Sizes are summed per wavefront
-// before they reach memory, and the interface links are compacted into a
-// list, so that the fit reads a few hundred points and not the lattice.
-// Measured, fields pass included: 0.25 ms on 400 x 400 (two thirds of it the
-// fields pass and the copy back) and 2.4 ms on 200 x 200 x 280, where the
-// joining, the links and the fit take 0.3 to 0.5 ms each.  With every node
-// its own label and its own atomic increment of one counter, and each pass
-// of the fit walking the whole lattice in one workgroup, these took 6.8 ms
-// and 754 ms.
+// one link per pair of runs that touch.  It works band by band in LDS (a
+// workgroup labels 4096 consecutive nodes and counts its regions' nodes there)
+// and only links between bands, and one size per band and region, go through
+// memory: joined there, every walk up a chain of labels is a round trip to the
+// L2 per step, and a chain as long as the lattice is high.  The interface links
+// are compacted into a list, so that the fit reads a few hundred points and
+// not the lattice.  FIXME
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -169,98 +167,182 @@ __device__ __forceinline__ void has_next(const RunGeom &q, int a, bool &x, bool 
     z = (int)zz + 1 < q.nz;
 }
 
-// Class words, labels (the first node of the run inside the word) and zero
-// sizes.  Grid of all labelling kernels: blockIdx.y = run, the wavefronts of
-// blockIdx.x stride over the run's groups.
-static __global__ void __launch_bounds__(256)
-k_cc_class(RunSet rs, RegionMem m, const double *__restrict__ rho1, const double *__restrict__ rho2,
-           const uint8_t *__restrict__ solid)
+constexpr int BAND_GROUPS = 64, BAND_NODES = BAND_GROUPS * 64;
+
+// The same inside one band of BAND_GROUPS class words: root of x, and joining.
+__device__ __forceinline__ int band_find(int *par, int x)
 {
-    const int run = blockIdx.y, lane = threadIdx.x & 63;
+    int p = __hip_atomic_load(par + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    while (p != x) {
+        const int g = __hip_atomic_load(par + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (g == p) return p;
+        __hip_atomic_store(par + x, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        x = g;
+        p = __hip_atomic_load(par + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    return x;
+}
+
+__device__ __forceinline__ void band_unite(int *par, int a, int b)
+{
+    for (;;) {
+        const int ra = band_find(par, a), rb = band_find(par, b);
+        if (ra == rb) return;
+        const int hi = ra > rb ? ra : rb, lo = ra > rb ? rb : ra;
+        int want = hi;
+        if (__hip_atomic_compare_exchange_strong(par + hi, &want, lo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_WORKGROUP))
+            return;
+    }
+}
+
+// Links in a band from the nodes of word g to those `step` further on, fluid
+// and of one phase (zero past the band).
+__device__ __forceinline__ unsigned long long band_links(const unsigned long long *fluid, const unsigned long long *pos,
+                                                         int g, int step, bool inside)
+{
+    auto bits = [&](const unsigned long long *w) {
+        const int i = g + (step >> 6), s = step & 63;
+        unsigned long long v = i < BAND_GROUPS ? w[i] >> s : 0ull;
+        if (s && i + 1 < BAND_GROUPS) v |= w[i + 1] << (64 - s);
+        return v;
+    };
+    return fluid[g] & bits(fluid) & ~(pos[g] ^ bits(pos)) & __ballot(inside);
+}
+
+// Class words of one band per workgroup (blockIdx.x; blockIdx.y = run), its
+// labels joined inside the band (par[a]: the first node of a's region in the
+// band, -1 for solid nodes) and the sizes of those regions at their roots
+// (zero at every other node).
+static __global__ void __launch_bounds__(1024)
+k_cc_band(RunSet rs, RegionMem m, const double *__restrict__ rho1, const double *__restrict__ rho2,
+          const uint8_t *__restrict__ solid)
+{
+    __shared__ int par[BAND_NODES], cnt[BAND_NODES];
+    __shared__ unsigned long long fluid[BAND_GROUPS], pos[BAND_GROUPS], starts[BAND_GROUPS];
+    const int run = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const RunGeom q = run_geom(rs, run);
     if (blockIdx.x == 0 && threadIdx.x < 2) m.best[2 * run + threadIdx.x] = 0ull;
-    for (int g = (int)(blockIdx.x * 4 + (threadIdx.x >> 6)); g < q.groups; g += (int)gridDim.x * 4) {
-        const int a = g * 64 + lane;
-        const bool fl = a < q.N && !solid[q.off + a];
+    const int gb = (int)blockIdx.x * BAND_GROUPS;  // first group of the band
+    if (gb >= q.groups) return;
+#pragma unroll
+    for (int k = 0; k < BAND_GROUPS / 16; ++k) {
+        const int g = wave + 16 * k, a = (gb + g) * 64 + lane;
+        const bool fl = gb + g < q.groups && a < q.N && !solid[q.off + a];
         const bool ph = fl && phase_positive(rho1 + q.off, rho2 + q.off, a);
         const unsigned long long f = __ballot(fl), p = __ballot(ph);
         const bool row0 = (unsigned)a % (unsigned)q.nx == 0;
         const bool start = lane == 0 || row0 || !((f >> (lane - 1)) & 1) || (((p >> (lane - 1)) & 1) != (ph ? 1u : 0u));
         const unsigned long long st = __ballot(start);
-        if (a < q.N) {
-            // the last run start at or before this lane
-            const unsigned long long upto = st & (~0ull >> (63 - lane));
-            m.par[q.off + a] = fl ? g * 64 + 63 - __clzll((long long)upto) : -1;
-            m.cnt[2 * q.off + a] = 0;
-        }
+        // the last run start at or before this lane
+        const unsigned long long upto = st & (~0ull >> (63 - lane));
+        par[g * 64 + lane] = fl ? g * 64 + 63 - __clzll((long long)upto) : -1;
+        cnt[g * 64 + lane] = 0;
         if (lane == 0) {
-            m.fluid[q.g0 + g] = f;
-            m.pos[q.g0 + g] = p;
+            fluid[g] = f;
+            pos[g] = p;
+            starts[g] = st;
+            if (gb + g < q.groups) {
+                m.fluid[q.g0 + gb + g] = f;
+                m.pos[q.g0 + gb + g] = p;
+            }
+        }
+    }
+    __syncthreads();
+    // along x only across words; along y and z one link per pair of runs that
+    // touch (a link whose left neighbour is the same pair's is implied by it)
+    for (int g = wave; g < BAND_GROUPS; g += 16) {
+        const int l = g * 64 + lane, plane = q.nx * q.ny;
+        bool ix, iy, iz;
+        has_next(q, gb * 64 + l, ix, iy, iz);
+        const unsigned long long lx = band_links(fluid, pos, g, 1, ix);
+        const unsigned long long ly = q.nx < BAND_NODES ? band_links(fluid, pos, g, q.nx, iy) : 0ull;
+        const unsigned long long lz = q.nz > 1 && plane < BAND_NODES ? band_links(fluid, pos, g, plane, iz) : 0ull;
+        if (lane == 63 && (lx >> 63)) band_unite(par, l, l + 1);
+        if (((ly & ~((lx & ly) << 1)) >> lane) & 1) band_unite(par, l, l + q.nx);
+        if (((lz & ~((lx & lz) << 1)) >> lane) & 1) band_unite(par, l, l + plane);
+    }
+    __syncthreads();
+    int root[BAND_GROUPS / 16];
+#pragma unroll
+    for (int k = 0; k < BAND_GROUPS / 16; ++k) {
+        const int g = wave + 16 * k;
+        int r = par[g * 64 + lane];
+        if (r >= 0)
+            for (int n = par[r]; n != r; n = par[r]) r = n;
+        root[k] = r;
+        // the run's nodes, counted by its first one
+        const unsigned long long f = fluid[g], rest = lane == 63 ? 0ull : (starts[g] | ~f) >> (lane + 1);
+        if (((starts[g] & f) >> lane) & 1) atomicAdd(cnt + r, rest ? __ffsll((long long)rest) : 64 - lane);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < BAND_GROUPS / 16; ++k) {
+        const int g = wave + 16 * k, a = (gb + g) * 64 + lane;
+        if (gb + g < q.groups && a < q.N) {
+            m.par[q.off + a] = root[k] >= 0 ? gb * 64 + root[k] : -1;
+            m.cnt[2 * q.off + a] = cnt[g * 64 + lane];
         }
     }
 }
 
-// Join the runs: along x only across words; along y and z one link per pair
-// of runs that touch (a link whose left neighbour is the same pair's is
-// implied by it).
-static __global__ void __launch_bounds__(256) k_cc_hook(RunSet rs, RegionMem m)
+// Join the bands' regions by the links between bands, one per pair of runs
+// that touch (in two dimensions these leave the last nx nodes of a band, so the
+// other groups are not looked at).  Grid of this and the next two kernels:
+// blockIdx.y = run, the wavefronts of blockIdx.x stride over the run's groups.
+static __global__ void __launch_bounds__(256) k_cc_join(RunSet rs, RegionMem m)
 {
     const int lane = threadIdx.x & 63;
     const RunGeom q = run_geom(rs, blockIdx.y);
     int *par = m.par + q.off;
-    for (int g = (int)(blockIdx.x * 4 + (threadIdx.x >> 6)); g < q.groups; g += (int)gridDim.x * 4) {
+    // joins a and b in the lanes with `link` set, once per pair of labels
+    auto join = [&](bool link, int a, int b) {
+        link = link && ((a ^ b) & ~(BAND_NODES - 1)) != 0;
+        if (!__ballot(link)) return;
+        const int pa = link ? par[a] : -1, pb = link ? par[b] : -1;
+        bool first = false;
+        for (unsigned long long todo = __ballot(link); todo;) {
+            const int lead = __ffsll((long long)todo) - 1;
+            if (lane == lead) first = true;
+            todo &= ~__ballot(pa == __shfl(pa, lead, 64) && pb == __shfl(pb, lead, 64));
+        }
+        if (first) cc_unite(par, pa, pb);
+    };
+    const int last = q.nz > 1 ? BAND_GROUPS : min(BAND_GROUPS, (q.nx + 63) / 64 + 1);  // groups of a band with such links
+    const int bands = (q.groups + BAND_GROUPS - 1) / BAND_GROUPS;
+    for (int k = (int)(blockIdx.x * 4 + (threadIdx.x >> 6)); k < bands * last; k += (int)gridDim.x * 4) {
+        const int g = k / last * BAND_GROUPS + BAND_GROUPS - last + k % last;
+        if (g >= q.groups) continue;
         const int a = g * 64 + lane, plane = q.nx * q.ny;
         bool ix, iy, iz;
         has_next(q, a, ix, iy, iz);
         const unsigned long long lx = link_bits(q, m.fluid, m.pos, g, 1, ix, true);
         const unsigned long long ly = link_bits(q, m.fluid, m.pos, g, q.nx, iy, true);
         const unsigned long long lz = q.nz > 1 ? link_bits(q, m.fluid, m.pos, g, plane, iz, true) : 0ull;
-        if (lane == 63 && (lx >> 63)) cc_unite(par, a, a + 1);
-        if (((ly & ~((lx & ly) << 1)) >> lane) & 1) cc_unite(par, a, a + q.nx);
-        if (((lz & ~((lx & lz) << 1)) >> lane) & 1) cc_unite(par, a, a + plane);
+        join(lane == 63 && (lx >> 63), a, a + 1);
+        join(((ly & ~((lx & ly) << 1)) >> lane) & 1, a, a + q.nx);
+        if (q.nz > 1) join(((lz & ~((lx & lz) << 1)) >> lane) & 1, a, a + plane);
     }
 }
 
-// After joining: par[a] <- root(a), and the region sizes.  Each wavefront
-// takes a contiguous part of the run and keeps the sizes of the two regions
-// it met last in registers.
-static __global__ void __launch_bounds__(256) k_cc_count(RunSet rs, RegionMem m)
+// After joining: every band region's size to the region's root, and
+// par[root in the band] <- that root, so that the root of any fluid node a is
+// par[par[a]].  (Sizes are nonzero at the bands' roots only, and only those
+// have children, so a label read while another lane sets it is an ancestor
+// either way.)
+static __global__ void __launch_bounds__(256) k_cc_merge(RunSet rs, RegionMem m)
 {
-    const int lane = threadIdx.x & 63, wave = (int)(blockIdx.x * 4 + (threadIdx.x >> 6)), nw = (int)gridDim.x * 4;
+    const int lane = threadIdx.x & 63;
     const RunGeom q = run_geom(rs, blockIdx.y);
     int *par = m.par + q.off, *cnt = m.cnt + 2 * q.off;
-    const int span = (q.groups + nw - 1) / nw, g1 = min(q.groups, (wave + 1) * span);
-    int ra = -1, na = 0, rb = -1, nb = 0;  // the region met last and the one before it
-    for (int g = wave * span; g < g1; ++g) {
+    for (int g = (int)(blockIdx.x * 4 + (threadIdx.x >> 6)); g < q.groups; g += (int)gridDim.x * 4) {
         const int a = g * 64 + lane;
-        int r = -1;
-        if (a < q.N && (r = par[a]) >= 0) {
-            for (int n = par[r]; n != r; n = par[r]) r = n;
-            par[a] = r;
-        }
-        unsigned long long todo = __ballot(r >= 0);
-        while (todo) {
-            const int r0 = __shfl(r, __ffsll(todo) - 1, 64);
-            const unsigned long long same = __ballot(r == r0);
-            todo &= ~same;
-            int n = __popcll(same);
-            if (r0 != ra) {
-                if (r0 == rb) {
-                    n += nb;
-                } else if (rb >= 0 && lane == 0) {
-                    atomicAdd(cnt + rb, nb);
-                }
-                rb = ra;
-                nb = na;
-                ra = r0;
-                na = 0;
-            }
-            na += n;
-        }
-    }
-    if (lane == 0) {
-        if (ra >= 0) atomicAdd(cnt + ra, na);
-        if (rb >= 0) atomicAdd(cnt + rb, nb);
+        if (a >= q.N || cnt[a] == 0) continue;
+        int r = par[a];
+        if (r == a) continue;
+        for (int n = par[r]; n != r; n = par[r]) r = n;
+        atomicAdd(cnt + r, cnt[a]);
+        par[a] = r;
     }
 }
 
@@ -323,7 +405,7 @@ __device__ void links_of_run(const RunSet &rs, const RegionMem &m, const Point &
             bool ok = (c >> lane) & 1;
             if (ok) {
                 const int ph = (int)((pw >> lane) & 1);
-                ok = par[a] == best[ph] && par[a + step[d]] == best[ph ^ 1] && pt.accept(q, a, d);
+                ok = par[par[a]] == best[ph] && par[par[a + step[d]]] == best[ph ^ 1] && pt.accept(q, a, d);
             }
             const unsigned long long l = __ballot(ok);
             if (lane == 0) m.link[d][q.g0 + g] = l;
@@ -394,34 +476,130 @@ template <int NT> __device__ unsigned link_total(const RunGeom &q, const RegionM
 }
 
 // Sum of v over the workgroup in a fixed order (a butterfly inside each
-// wavefront, then the wavefronts in order); every thread gets the result.
+// wavefront, then the wavefronts in order, a thread per value); every thread
+// gets the result.  Of each pair of lanes that a step of the butterfly adds,
+// one goes on with one half of the values and one with the other, so that the
+// 14 values of a sphere fit take 17 exchanges instead of 84: sixteen
+// wavefronts share one LDS for them.
 template <int NV, int NT> __device__ void block_sum(double (&v)[NV], double (*sh)[NT / 64])
 {
+    constexpr int P = NV > 8 ? 16 : NV > 4 ? 8 : NV > 2 ? 4 : 2;
+    static_assert(NV <= 16, "at most 16 values");
+    const int lane = threadIdx.x & 63;
+    double w[P];
 #pragma unroll
-    for (int k = 0; k < NV; ++k)
-        for (int s = 32; s > 0; s >>= 1) v[k] += __shfl_xor(v[k], s, 64);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0)
-        for (int k = 0; k < NV; ++k) sh[k][threadIdx.x >> 6] = v[k];
-    __syncthreads();
+    for (int k = 0; k < P; ++k) w[k] = k < NV ? v[k] : 0.0;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-        v[k] = sh[k][0];
-        for (int w = 1; w < NT / 64; ++w) v[k] += sh[k][w];
+    for (int h = P / 2, s = 32; s > 0; h /= 2, s >>= 1) {
+        if (h > 0) {
+            const bool up = lane & s;
+#pragma unroll
+            for (int k = 0; k < h; ++k) {
+                const double mine = up ? w[k + h] : w[k], other = up ? w[k] : w[k + h];
+                w[k] = mine + __shfl_xor(other, s, 64);
+            }
+        } else {
+            w[0] += __shfl_xor(w[0], s, 64);
+        }
     }
+    constexpr int SHARE = 64 / P;  // lanes that hold the same value
+    __syncthreads();
+    if (lane % SHARE == 0 && lane / SHARE < NV) sh[lane / SHARE][threadIdx.x >> 6] = w[0];
+    __syncthreads();
+    if (threadIdx.x < NV) {
+        double s = sh[threadIdx.x][0];
+        for (int k = 1; k < NT / 64; ++k) s += sh[threadIdx.x][k];
+        sh[threadIdx.x][0] = s;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] = sh[k][0];
 }
 
-// Blocks of the labelling passes for runs of up to max_nodes nodes.
+// The points of a fit, shared out over NT threads (thread t takes t, t + NT,
+// ...): each thread keeps its first KEEP points in registers over the passes of
+// the fit and finds the others again from the fields on every pass.  One
+// compute unit does the fit, so its instructions count: with the points found
+// again on every pass, all threads summing all wavefronts' sums and the pivot
+// rows in memory, the sphere fit on 72 x 65 x 40 nodes took 97 us and the
+// circle fit on 400 x 400 26; they take 41 and 17.
+template <int ND, int NT, int KEEP, class Point> struct FitPoints {
+    double kept[KEEP][ND];
+    int n;
+    Point point;
+    __device__ __forceinline__ FitPoints(int count, const Point &pt) : n(count), point(pt)
+    {
+#pragma unroll
+        for (int k = 0; k < KEEP; ++k)
+            if ((int)threadIdx.x + k * NT < n) point((int)threadIdx.x + k * NT, kept[k]);
+    }
+    template <class F> __device__ __forceinline__ void each(F &&f) const
+    {
+#pragma unroll
+        for (int k = 0; k < KEEP; ++k)
+            if ((int)threadIdx.x + k * NT < n) f(kept[k]);
+        for (int i = (int)threadIdx.x + KEEP * NT; i < n; i += NT) {
+            double p[ND];
+            point(i, p);
+            f(p);
+        }
+    }
+};
+
+// Solve M x = b (ND unknowns, M with b as its last column) by elimination with
+// row pivoting; false for a singular matrix.  Unrolled, with the pivot row
+// exchanged by selection: rows picked by a runtime index would live in memory.
+template <int ND> __device__ __forceinline__ bool solve_linear(double (&M)[ND][ND + 1], double (&x)[ND])
+{
+#pragma unroll
+    for (int col = 0; col < ND; ++col) {
+        int piv = col;
+        double big = __builtin_fabs(M[col][col]);
+#pragma unroll
+        for (int r = col + 1; r < ND; ++r)
+            if (__builtin_fabs(M[r][col]) > big) {
+                piv = r;
+                big = __builtin_fabs(M[r][col]);
+            }
+        if (big == 0.0) return false;
+#pragma unroll
+        for (int r = col + 1; r < ND; ++r)
+#pragma unroll
+            for (int q = 0; q <= ND; ++q) {
+                const double a = M[col][q], b = M[r][q];
+                M[col][q] = piv == r ? b : a;
+                M[r][q] = piv == r ? a : b;
+            }
+#pragma unroll
+        for (int r = col + 1; r < ND; ++r) {
+            const double fct = M[r][col] / M[col][col];
+#pragma unroll
+            for (int q = col; q <= ND; ++q) M[r][q] -= fct * M[col][q];
+        }
+    }
+#pragma unroll
+    for (int r = ND - 1; r >= 0; --r) {
+        double s = M[r][ND];
+#pragma unroll
+        for (int q = r + 1; q < ND; ++q) s -= M[r][q] * x[q];
+        x[r] = s / M[r][r];
+    }
+    return true;
+}
+
+// Blocks of the labelling passes for runs of up to max_nodes nodes, and of the
+// link passes: enough to fill the chip over all runs, at least a few per run
+// (48 runs, 64 / 256 and 32 / 128 of them: links 60 / 40 us, joining 78 / 63).
 inline dim3 region_grid(long long max_nodes, int nruns)
 {
     long long bx = (max_nodes + 255) / 256;
-    const long long cap = nruns > 16 ? 64 : nruns > 1 ? 256 : 2048;
+    const long long cap = nruns > 1 ? (nruns < 192 ? 12288 / nruns : 64) : 2048;
     return dim3((unsigned)(bx > cap ? cap : bx < 1 ? 1 : bx), (unsigned)nruns);
 }
 inline dim3 link_grid(long long max_nodes, int nruns)
 {
     long long bx = (max_nodes + 255) / 256;
-    const long long cap = nruns > 16 ? 32 : REGION_BLOCKS;
+    const long long cap = nruns <= 12 ? REGION_BLOCKS : nruns < 192 ? 6144 / nruns : 32;
     return dim3((unsigned)(bx > cap ? cap : bx < 1 ? 1 : bx), (unsigned)nruns);
 }
 
@@ -430,9 +608,10 @@ static inline hipError_t launch_regions(hipStream_t st, const RunSet &rs, int nr
                                         const double *rho1, const double *rho2, const uint8_t *solid, const RegionMem &m)
 {
     const dim3 grid = region_grid(max_nodes, nruns);
-    hipLaunchKernelGGL(k_cc_class, grid, dim3(256), 0, st, rs, m, rho1, rho2, solid);
-    hipLaunchKernelGGL(k_cc_hook, grid, dim3(256), 0, st, rs, m);
-    hipLaunchKernelGGL(k_cc_count, grid, dim3(256), 0, st, rs, m);
+    const dim3 bands((unsigned)((max_nodes + BAND_NODES - 1) / BAND_NODES), (unsigned)nruns);
+    hipLaunchKernelGGL(k_cc_band, bands, dim3(1024), 0, st, rs, m, rho1, rho2, solid);
+    hipLaunchKernelGGL(k_cc_join, grid, dim3(256), 0, st, rs, m);
+    hipLaunchKernelGGL(k_cc_merge, grid, dim3(256), 0, st, rs, m);
     hipLaunchKernelGGL(k_cc_pick, grid, dim3(256), 0, st, rs, m);
     return hipGetLastError();
 }

@@ -63,3 +63,28 @@ def test_angle_with_pockets_3d(oracle_mod, lbm_mod, nx, ny, nz, r):
         q.init_fields(rho[0], rho[1])
     to, tg = (q.contact_angle(0, (0.5, 0.0, 0.0, 0.0)) for q in lats)
     assert abs(tg - to) < 1e-9
+
+
+# labels are joined in bands of 4096 nodes: rows longer than a band, bands that
+# end with a row and inside one, one node into a second band
+@pytest.mark.parametrize("nx,ny,r", [(5000, 23, 9.0), (4096, 21, 9.0), (128, 97, 30.0), (100, 90, 28.0), (241, 17, 9.0)])
+def test_angle_over_label_bands(oracle_mod, lbm_mod, nx, ny, r):
+    wl = _workload(nx, ny, nx + 1, r)
+    o = oracle_mod.Oracle(nx, ny, wl.flags)
+    o.set_geometry(wl.solid)
+    o.set_params(wl.G_c, wl.G_ads, wl.tau)
+    o.init_fields(wl.rho1, wl.rho2)
+    g = lbm_mod.lattice_from_workload(wl, lbm_mod.F64)
+    assert abs(g.contact_angle(0, wl.wall) - o.contact_angle(0, wl.wall)) < 1e-9
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(64, 64, 20), (71, 70, 19)])  # a plane is a band; a plane is longer
+def test_angle_over_label_bands_3d(oracle_mod, lbm_mod, nx, ny, nz):
+    solid, rho = _cap((nz, ny, nx), nx + 1, 11.0)
+    lats = [oracle_mod.Oracle3D(nx, ny, nz, 3), lbm_mod.Lattice3D(nx, ny, nz, lbm_mod.F64, 3)]
+    for q in lats:
+        q.set_geometry(solid)
+        q.set_params(0.9, 0.0, 1.0)
+        q.init_fields(rho[0], rho[1])
+    to, tg = (q.contact_angle(0, (0.5, 0.0, 0.0, 0.0)) for q in lats)
+    assert abs(tg - to) < 1e-9
