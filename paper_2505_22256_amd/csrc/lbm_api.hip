@@ -126,28 +126,6 @@ struct Tile {
     unsigned sched;
 };
 
-// The tile of the marching kernels: the caller's, or the default, which at
-// relaxation time 1 gives way to the one its kernels run best with.  They
-// keep 4 values per row and component pair instead of 18 (FP32 123 registers
-// against 210, FP64 218 against 256 and 126 accumulation registers), so more
-// wavefronts share a SIMD and wider strips pay.  16384 x 2048 channel, us per
-// step, general kernels in the default tile / relaxation time 1 in that tile
-// / in this one: FP32 737 / 702 / 653, FP16 604 / 520 / 509, BF16 613 / 520 /
-// 505, FP64 (8192 x 2048) 820 / 774 / 702; with open edges (8192 x 1024) FP32
-// - / 248 / 233, FP64 - / 467 / 419; 16-bit storage stays at one step per
-// launch (232 either way).
-Tile march_tile(const lbm_ctx *c)
-{
-    const Tile t = {c->block, c->seg_rows, c->sched};
-    if (c->own_tile || c->tau != 1.0 || !(t.sched & SCHED_TWO_STEP)) return t;
-    const bool bnd = boundary_steps(c);
-    switch (c->storage) {
-    case LBM_F64: return {128, bnd ? 32 : 24, t.sched};
-    case LBM_F32: return {bnd ? 128 : 256, 24, t.sched};
-    default: return bnd ? t : Tile{128, 32, t.sched};
-    }
-}
-
 template <class C>
 KParams<C> make_params(const lbm_ctx *c, const void *A, void *B, const Tile &t, int halo = 2)
 {
@@ -185,6 +163,58 @@ int compute_units(lbm_ctx *c)
         c->cus = (hipGetDeviceProperties(&prop, c->device) == hipSuccess) ? prop.multiProcessorCount : 256;
     }
     return c->cus;
+}
+
+// The tile of the marching kernels: the caller's, or the default with two
+// changes, so long as the caller has set or tuned none.
+//
+// Relaxation time 1: the kernels keep 4 values per row and component pair
+// instead of 18 (FP32 123 registers against 210, FP64 218 against 256 and 126
+// accumulation registers), so more wavefronts share a SIMD and wider strips
+// pay.  16384 x 2048 channel, us per step, general kernels in the default tile
+// / relaxation time 1 in that tile / in this one: FP32 737 / 702 / 653, FP16
+// 604 / 520 / 509, BF16 613 / 520 / 505, FP64 (8192 x 2048) 820 / 774 / 702.
+// With open edges (us per step alone / with three lattices at a time, 8192 x
+// 1024): FP32 in 128 threads 233 / 174, in 256 226 / 162, FP64 - / 467 and 419;
+// 16-bit storage, whose default is one step in 128 threads, 232 / 185, two steps
+// in 64 threads and 24 rows 234 / 155, one step in 256 threads and 12 rows 210 /
+// 167.  Two steps need several rounds of wavefronts to be the better both ways
+// (9000 x 1400 305 / 229 against 305 / 253, 4000 x 1000 155 / 77 against 117 / 83,
+// 2000 x 600 103 / 41 against 66 / 31): three.
+//
+// Rows: a segment is a serial march, so a lattice whose segments are fewer than
+// the wavefronts that hide a march's latency (one per SIMD, two in the light
+// 16-bit kernels) gets shorter ones.  us per step alone / three at a time, the
+// default's rows / this: FP32 at tau 1 1500 x 600 74 / 33, 55 / 26; at 0.85 78
+// / 33, 58 / 31; FP16 at 0.85 2000 x 700 99 / 41, 60 / 30; FP64 at 0.85 2000 x
+// 700 172 / 66, 115 / 65.  More wavefronts than that shorten a lattice alone
+// further, but the halo rows cost three at a time (FP32 at 0.85 2000 x 700 in
+// 16 rows 60 / 46 against 79 / 44).
+// A step that runs alone there (the first on given populations, the last of an
+// odd number) takes the one-step tile in any case.
+Tile march_tile(lbm_ctx *c, bool two)
+{
+    Tile t = {c->block, c->seg_rows, c->sched};
+    if (c->own_tile) return t;
+    const bool bnd = boundary_steps(c), half = c->storage == LBM_F16 || c->storage == LBM_BF16;
+    const int simds = 4 * compute_units(c);
+    if (c->tau == 1.0) {
+        if (c->storage == LBM_F64) {
+            t = {128, bnd ? 32 : 24, t.sched};
+        } else if (c->storage == LBM_F32) {
+            t = {256, 24, t.sched};
+        } else if (!bnd) {
+            t = {128, 32, t.sched};
+        } else {
+            const long long units = (long long)((c->nx + 53) / 54) * ((c->ny + 23) / 24);
+            t = two && units >= 9LL * simds ? Tile{64, 24, SCHED_TWO_STEP | SCHED_BANDS} : Tile{256, 12, SCHED_BANDS};
+        }
+    }
+    const int w = t.block - (t.sched & SCHED_TWO_STEP ? 10 : 4);
+    const long long waves = (long long)((c->nx + w - 1) / w) * (t.block / 64);  // of one segment over the width
+    const long long rows = c->ny * waves / (half ? 2 * simds : simds);
+    t.seg_rows = (int)std::min<long long>(t.seg_rows, std::max<long long>(rows, 8));
+    return t;
 }
 
 // Workgroups of the step kernel that fit on the device at once.
@@ -260,7 +290,7 @@ int run_pass_t(lbm_ctx *c, Pass pass, double *fields, uint8_t *link, uint8_t *nw
     using C = typename Traits<S>::C;
     const bool two = pass == P_STEP2 || pass == P_STEP2_RED1 || pass == P_STEP2_RED2;
     const bool stepping = pass == P_STEP || pass == P_STEP_REDUCE || two;
-    Tile t = march_tile(c);
+    Tile t = march_tile(c, two);
     const bool persistent = t.seg_rows == 0;
     if (persistent) t.seg_rows = 64;
     if (!stepping) t = {256, field_rows(c), c->sched};
@@ -854,7 +884,7 @@ int lbm_step(lbm_ctx *c, int n)
     if (rc) return rc;
     if (n < 0) return set_err(c, LBM_EINVAL, "negative step count");
     const BrickPlan plan = brick_plan(c);
-    const bool two = (march_tile(c).sched & SCHED_TWO_STEP) != 0 && !plan.steps;
+    const bool two = (march_tile(c, true).sched & SCHED_TWO_STEP) != 0 && !plan.steps;
     for (int s = 0; s < n; ++s) {
         const bool diag_now = c->diag_every > 0 && c->t % c->diag_every == 0;
         const bool diag_next = c->diag_every > 0 && (c->t + 1) % c->diag_every == 0;

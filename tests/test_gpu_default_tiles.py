@@ -1,0 +1,38 @@
+"""The tile the library picks where the caller sets none: segments shortened on
+lattices that would leave SIMDs idle, other strips at relaxation time 1, one or
+two steps per launch with open edges by size.  Populations do not depend on the
+tile (bitwise), so each choice is held against a tile set by hand."""
+import numpy as np
+import pytest
+
+from paper_2505_22256_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _workload(kind, nx, ny):
+    if kind == "walls":
+        return W.random_small(nx, nx, ny, 1, n_blobs=40, walls=True)
+    return W.obstacle_drop(nx, ny, side=40, centre=(nx / 3.0, ny / 2.0), r_drop=60.0, drop_centre=(nx / 6.0, ny / 2.0))
+
+
+# past the lattices that run in bricks: rows cut to about 14, to 26, a width of
+# a few strips, and (open, 16 million nodes) three rounds of wavefronts
+@pytest.mark.parametrize("kind,nx,ny,storage,tau", [
+    ("walls", 1100, 800, 1, 0.9), ("walls", 1100, 800, 1, 1.0), ("walls", 1700, 720, 2, 0.9), ("walls", 1700, 720, 3, 1.0),
+    ("walls", 300, 4001, 0, 0.9), ("walls", 300, 4001, 0, 1.0), ("open", 1801, 701, 2, 1.0), ("open", 1801, 701, 1, 1.0),
+    ("open", 8201, 1991, 3, 1.0),
+])
+def test_default_tile_equals_a_set_one(lbm_mod, kind, nx, ny, storage, tau):
+    wl = _workload(kind, nx, ny)
+    wl.tau = tau
+    g = lbm_mod.lattice_from_workload(wl, storage)
+    ref = lbm_mod.lattice_from_workload(wl, storage)
+    ref.set_tile(128, 16, 2)
+    for q in (g, ref):
+        q.step(1)
+        q.step(4)
+    x0, w = nx // 3, min(nx // 3, 400)
+    assert np.array_equal(g.get_populations_window(x0, 0, w, ny), ref.get_populations_window(x0, 0, w, ny))
+    for a, b in zip(g.get_fields(), ref.get_fields()):
+        assert np.array_equal(a, b)
