@@ -728,23 +728,41 @@ __attribute__((amdgpu_waves_per_eu((S == lbm::ST_F32 && !(MODE & K3_REDUCE)) ? 4
         const bool wx = p.flags & F3_PERIODIC_X, wy = p.flags & F3_PERIODIC_Y, wz = p.flags & F3_PERIODIC_Z;
         // psi of the brick and its halo (outside a closed face: the sentinel).  A
         // brick of a lattice at least as wide reaches one period out at most
-        // and wraps without a division.
+        // and wraps without a division.  U loads of a thread are in flight
+        // together (one after the other, a workgroup of few wavefronts waits
+        // out each of them); with the large bricks at relaxation time 1, FP32
+        // aside, many wavefronts are resident and more than two only crowd
+        // their stores.  us per step with 1 / 2 / 7: 200 x 200 x 280 FP32 950 /
+        // 946 / 933 at tau = 1, 1290 / 1294 / 1263 at 1.1, FP16 633 / 630 / 649
+        // and 834 / 820 / 794, FP64 1705 / 1705 / 1716 and 2302 / 2301 / 2305;
+        // 72 x 65 x 40 FP32 30.6 / 30.4 / 29.7, FP16 34.9 / 34.4 / 33.0, FP64
+        // 47.6 / 47.4 / 45.1 at 1.1.
+        constexpr int U = (MODE & K3_TAU1) && BXB >= 32 && S != lbm::ST_F32 ? 2 : 7;
         const bool roomy = p.nx >= BXB + 2 && p.ny >= BYB + 2 && p.nz >= BZB + 2;
         auto stage = [&](auto &&axis) {
-            for (int t = tid; t < BR::TX * BR::TY * BR::TZ; t += NTH) {
-                const int lx = t % BR::TX, r = t / BR::TX;
-                const int ly = r % BR::TY, lz = r / BR::TY;
-                const Axis gx = axis(x0 - 2 + lx, p.nx, wx);
-                const Axis gy = axis(y0 - 2 + ly, p.ny, wy);
-                const Axis gz = axis(z0 - 2 + lz, p.nz, wz);
-                PsiPair<C> v;
-                if (gx.ok && gy.ok && gz.ok) {
-                    v = p.psi[((uint32_t)gz.c * (uint32_t)p.ny + (uint32_t)gy.c) * (uint32_t)p.nx + (uint32_t)gx.c];
-                } else {
-                    v.a = lds_sentinel<C>();
-                    v.b = lds_sentinel<C>();
+            constexpr int NT = BR::TX * BR::TY * BR::TZ;
+#pragma unroll 1
+            for (int t0 = tid; t0 < NT; t0 += U * NTH) {
+                PsiPair<C> v[U];
+                bool in[U];
+#pragma unroll
+                for (int k = 0; k < U; ++k) {
+                    const int t = t0 + k * NTH;
+                    const int lx = t % BR::TX, r = t / BR::TX;
+                    const int ly = r % BR::TY, lz = r / BR::TY;
+                    const Axis gx = axis(x0 - 2 + lx, p.nx, wx);
+                    const Axis gy = axis(y0 - 2 + ly, p.ny, wy);
+                    const Axis gz = axis(z0 - 2 + lz, p.nz, wz);
+                    in[k] = t < NT && gx.ok && gy.ok && gz.ok;
+                    const uint32_t i = ((uint32_t)gz.c * (uint32_t)p.ny + (uint32_t)gy.c) * (uint32_t)p.nx + (uint32_t)gx.c;
+                    v[k] = p.psi[in[k] ? i : 0u];
                 }
-                tile[t] = v;
+#pragma unroll
+                for (int k = 0; k < U; ++k) {
+                    const int t = t0 + k * NTH;
+                    if (!in[k]) v[k].a = v[k].b = lds_sentinel<C>();
+                    if (t < NT) tile[t] = v[k];
+                }
             }
         };
         if (roomy) stage([](int v, int n, bool per) { return make_axis_near(v, n, per); });
