@@ -1,7 +1,7 @@
 // Batched runs (include/lbm.h, lbm_batch_*): many independent lattices of
 // uneven sizes and parameters advanced by one kernel launch per time step.
 // The work list concatenates every run's (strip, segment) items; the batched
-// kernel finds the owning run by binary search over item offsets and then
+// kernel finds the owning run among the item offsets and then
 // executes exactly the per-item code of the single-run kernel, so a run's
 // result is bitwise that of a single context.  Optionally a HIP graph of
 // several steps is captured once and replayed.
@@ -53,7 +53,7 @@ struct lbm_batch {
     long long *d_offs = nullptr;
     WallDesc *d_walls = nullptr;
     double *d_out = nullptr;
-    unsigned *d_tick = nullptr;  // step counter read by the batched kernel
+    unsigned *d_tick = nullptr;  // step counters of the two buffer sides (batch_run in lbm_kernels.hpp)
     hipStream_t stream = nullptr, own_stream = nullptr;
     bool use_graph = false;
     bool two = false;       // two fused steps per launch (LBM_SCHED_TWO_STEP)
@@ -161,20 +161,17 @@ hipError_t launch_batch_t(lbm_batch *b, int flip)
         if (sr)
             hipLaunchKernelGGL((k_step_batch<S, BLOCK, M_STORE | M_SR>), dim3(per_xcd * 8), dim3(BLOCK), 0, b->stream,
                                (const KParams<C> *)b->d_params, b->nruns, b->n_items, per_xcd, flip,
-                               (const unsigned *)b->d_tick);
+                               b->d_tick);
         else
             hipLaunchKernelGGL((k_step_batch<S, BLOCK, M_STORE>), dim3(per_xcd * 8), dim3(BLOCK), 0, b->stream,
                                (const KParams<C> *)b->d_params, b->nruns, b->n_items, per_xcd, flip,
-                               (const unsigned *)b->d_tick);
+                               b->d_tick);
     } else {
         (void)sr;
         hipLaunchKernelGGL((k_step_batch<S, BLOCK, M_STORE>), dim3(per_xcd * 8), dim3(BLOCK), 0, b->stream,
                            (const KParams<C> *)b->d_params, b->nruns, b->n_items, per_xcd, flip,
-                           (const unsigned *)b->d_tick);
+                           b->d_tick);
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_tick, dim3(1), dim3(1), 0, b->stream, b->d_tick, 1u);
     return hipGetLastError();
 }
 
@@ -194,7 +191,7 @@ hipError_t launch_batch2_t(lbm_batch *b, int flip)
     using C = typename Traits<S>::C;
     const int per_xcd = (b->n_items + 7) / 8;
     const auto *prm = (const KParams<C> *)b->d_params;
-    const auto *tick = (const unsigned *)b->d_tick;
+    unsigned *const tick = b->d_tick;
     bool done = false;
     if constexpr (S == ST_F16 || S == ST_BF16) {
         if (b->runs[0].flags & LBM_ROUND_STOCHASTIC) {
@@ -206,9 +203,6 @@ hipError_t launch_batch2_t(lbm_batch *b, int flip)
     if (!done)
         hipLaunchKernelGGL((k_step2_batch<S, BLOCK, M_STORE>), dim3(per_xcd * 8), dim3(BLOCK), 0, b->stream, prm,
                            b->nruns, b->n_items, per_xcd, flip, tick);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_tick, dim3(1), dim3(1), 0, b->stream, b->d_tick, 2u);
     return hipGetLastError();
 }
 
@@ -344,7 +338,7 @@ int fields_all_t(lbm_batch *b)
     const int per_xcd = (b->n_fitems + 7) / 8;
     hipLaunchKernelGGL((k_step_batch<S, FIELD_BLOCK, M_FIELDS>), dim3(per_xcd * 8), dim3(FIELD_BLOCK), 0, b->stream,
                        (const KParams<C> *)b->d_fparams, b->nruns, b->n_fitems, per_xcd, b->flip,
-                       (const unsigned *)b->d_tick);
+                       b->d_tick);
     BCHK(b, hipGetLastError());
     return LBM_OK;
 }
@@ -474,7 +468,7 @@ int lbm_batch_create(lbm_batch **out, int nruns, const lbm_run_desc *runs, int s
          hipMalloc(&b->d_offs, (size_t)nruns * sizeof(long long)) == hipSuccess &&
          hipMalloc(&b->d_walls, (size_t)nruns * sizeof(WallDesc)) == hipSuccess &&
          hipMalloc(&b->d_out, (size_t)nruns * 6 * sizeof(double)) == hipSuccess &&
-         hipMalloc(&b->d_tick, sizeof(unsigned)) == hipSuccess;
+         hipMalloc(&b->d_tick, 2 * sizeof(unsigned)) == hipSuccess;
     if (!ok) {
         lbm_batch_destroy(b);
         return LBM_ENOMEM;
@@ -497,7 +491,7 @@ int lbm_batch_create(lbm_batch **out, int nruns, const lbm_run_desc *runs, int s
     if (e == hipSuccess) e = hipMemcpy(b->d_dims, dims.data(), dims.size() * sizeof(int), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(b->d_offs, offs.data(), offs.size() * sizeof(long long), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(b->d_walls, walls.data(), walls.size() * sizeof(WallDesc), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(b->d_tick, 0, sizeof(unsigned));
+    if (e == hipSuccess) e = hipMemset(b->d_tick, 0, 2 * sizeof(unsigned));
     if (e == hipSuccess) e = hipMemset(b->buf[0], 0xff, bytes);
     if (e == hipSuccess) e = hipMemset(b->buf[1], 0xff, bytes);
     if (e != hipSuccess) {
@@ -569,7 +563,7 @@ int lbm_batch_autotune(lbm_batch *b, int steps)
     const size_t bytes = (size_t)b->total_nodes * 18 * esize(b->storage);
     const int flip0 = b->flip;
     unsigned tick0 = 0;
-    BCHK(b, hipMemcpy(&tick0, b->d_tick, sizeof tick0, hipMemcpyDeviceToHost));
+    BCHK(b, hipMemcpy(&tick0, b->d_tick + flip0, sizeof tick0, hipMemcpyDeviceToHost));
     void *backup = nullptr;
     if (hipMalloc(&backup, bytes) != hipSuccess) return berr(b, LBM_ENOMEM, "autotune backup allocation failed");
     hipError_t e = hipMemcpyAsync(backup, b->buf[flip0], bytes, hipMemcpyDeviceToDevice, b->stream);
@@ -611,7 +605,7 @@ int lbm_batch_autotune(lbm_batch *b, int steps)
         }
     }
     if (e == hipSuccess) e = hipMemcpyAsync(b->buf[flip0], backup, bytes, hipMemcpyDeviceToDevice, b->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(b->d_tick, &tick0, sizeof tick0, hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(b->d_tick + flip0, &tick0, sizeof tick0, hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (ev0) (void)hipEventDestroy(ev0);
     if (ev1) (void)hipEventDestroy(ev1);
