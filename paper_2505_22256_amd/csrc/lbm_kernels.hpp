@@ -342,41 +342,23 @@ __device__ __forceinline__ int stencil_dx(int n, int col, int nx, unsigned flags
     return sx(n) + (!open ? 0 : pc < 0 ? -pc : nx - 1 - pc);
 }
 
-// Stencil value at position n after the wall rules of Sec. 2.4 / Table 1,
-// resolved on the fly from the ring (at most two LDS reads): an unavailable
-// first-layer position reads zero (or psi(x) under WALLPSI_SELF); an
-// unavailable second-layer position reads what its Table 1 partner
+// Cohesion and adhesion sums at a node with unavailable stencil positions, in
+// the pair order of cohesion_sums / adhesion_vector, S(x) from the solid
+// switches.  The wall rules (Sec. 2.4, Table 1; as apply_wall_rules): an
+// unavailable first-layer position reads zero (psi(x) under WALLPSI_SELF), an
+// unavailable second-layer one what its Table 1 partner, a first-layer position,
 // resolves to (zero under E8_COPY_OFF).  Beyond an open edge a first-layer
-// position reads its ghost (when fluid) and a second-layer one takes the
-// Table 1 copy.  `solid` is the switch s of Eq. 9 at the position (beyond
-// an open edge: at its ghost).  Same rules as apply_wall_rules.
-template <class C, bool BND, class Psi>
-__device__ __forceinline__ PsiPair<C> resolve_position(const Psi &psi, int n, int col, int nx, C r1, C r2,
-                                                       unsigned flags, bool &solid)
-{
-    bool open;
-    const int dx = stencil_dx<BND>(n, col, nx, flags, open);
-    const PsiPair<C> v = psi.at(dx, sy(n));
-    solid = lds_sent(v.a);
-    if (!solid && (!open || n < 8)) return v;
-    PsiPair<C> self, zero;
-    self.a = r1;
-    self.b = r2;
-    zero.a = 0;
-    zero.b = 0;
-    const PsiPair<C> first_rule = (flags & FL_WALLPSI_SELF) ? self : zero;
-    if (n < 8) return first_rule;
-    if (flags & FL_COPY_OFF) return zero;
-    const int m = table1(n);
-    bool open_m;
-    const int dx_m = stencil_dx<BND>(m, col, nx, flags, open_m);
-    const PsiPair<C> w = psi.at(dx_m, sy(m));
-    return lds_sent(w.a) ? first_rule : w;
-}
-
-// Cohesion and adhesion sums at a node with unavailable stencil positions:
-// the same pair order as cohesion_sums / adhesion_vector, positions
-// resolved by the wall rules, S(x) from the solid switches.
+// position reads its ghost (when fluid) and a second-layer one takes the Table
+// 1 copy; the switch s of Eq. 9 is that of the position, there of its ghost.
+// Every position is read and what it stands for selected: with a branch per
+// position and lane, and the partner's read behind it, each was up to two LDS
+// round trips with nothing else to do.  The fences keep the reads of the groups
+// (in FP64 of two groups) from all being held at once: FP32 210 -> 203 registers,
+// 123 -> 119 at tau = 1.  us per step alone / three lattices at a time: FP16 800
+// x 600 porous 22.0 / 15.3 -> 18.7 / 13.1, FP32 350 x 150 with an obstacle and
+// open edges 8.2 / 3.7 -> 6.0 / 3.4, open channel of 8192 x 1024 FP32 227 / 162
+// -> 202 / 158 and BF16 210 / 168 -> 200 / 164, FP64 2048 x 1024 porous 183 / 110
+// -> 175 / 107 at tau = 1; FP32 2048 x 1024 porous 88 / 52 either way.
 template <class C, bool BND, class Psi>
 __device__ __forceinline__ void wall_sums(const Psi &psi, int col, int nx, C r1, C r2, unsigned flags, C &s1x, C &s1y,
                                           C &s2x, C &s2y, C &Sx, C &Sy)
@@ -386,21 +368,55 @@ __device__ __forceinline__ void wall_sums(const Psi &psi, int col, int nx, C r1,
     asm volatile("" ::: "memory");
     s1x = 0; s1y = 0; s2x = 0; s2y = 0;
     Sx = 0; Sy = 0;
+    const C f1 = (flags & FL_WALLPSI_SELF) ? r1 : (C)0, f2 = (flags & FL_WALLPSI_SELF) ? r2 : (C)0;
+    // (values, not pairs: a choice between structs would go through memory)
+    C q1[8], q2[8];  // what the first layer reads
+    auto add = [&](int n, C a1, C a2, bool un, C b1, C b2, bool uo) {
+        const C cx = (C)(e8wn(n) * sx(n));
+        const C cy = (C)(e8wn(n) * sy(n));
+        const C d1 = a1 - b1;
+        const C d2 = a2 - b2;
+        const C ds = (C)(int)un - (C)(int)uo;
+        if (sx(n) != 0) { s1x += cx * d1; s2x += cx * d2; Sx += cx * ds; }
+        if (sy(n) != 0) { s1y += cy * d1; s2y += cy * d2; Sy += cy * ds; }
+    };
 #pragma unroll
-    for (int g = 0; g < 6; ++g) {
+    for (int g = 0; g < 2; ++g) {
+        bool u[4];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const int n = 4 * g + h;
+            bool open;
+            const PsiPair<C> v = psi.at(stencil_dx<BND>(n, col, nx, flags, open), sy(n));
+            u[h] = lds_sent(v.a);
+            q1[n] = u[h] ? f1 : v.a;
+            q2[n] = u[h] ? f2 : v.b;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int n = 4 * g + h;
+            add(n, q1[n], q2[n], u[h], q1[n + 2], q2[n + 2], u[h + 2]);
+        }
+    }
+    if (flags & FL_COPY_OFF)
+#pragma unroll
+        for (int n = 0; n < 8; ++n) {
+            q1[n] = 0;
+            q2[n] = 0;
+        }
+#pragma unroll
+    for (int g = 2; g < 6; ++g) {
+        if (sizeof(C) == 4 || g % 2 == 0) asm volatile("" ::: "memory");
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int n = 4 * g + h, o = n + 2;
-            bool un, uo;
-            const PsiPair<C> a = resolve_position<C, BND>(psi, n, col, nx, r1, r2, flags, un);
-            const PsiPair<C> b = resolve_position<C, BND>(psi, o, col, nx, r1, r2, flags, uo);
-            const C cx = (C)(e8wn(n) * sx(n));
-            const C cy = (C)(e8wn(n) * sy(n));
-            const C d1 = a.a - b.a;
-            const C d2 = a.b - b.b;
-            const C ds = (C)(int)un - (C)(int)uo;
-            if (sx(n) != 0) { s1x += cx * d1; s2x += cx * d2; Sx += cx * ds; }
-            if (sy(n) != 0) { s1y += cy * d1; s2y += cy * d2; Sy += cy * ds; }
+            bool on, oo;
+            const PsiPair<C> a = psi.at(stencil_dx<BND>(n, col, nx, flags, on), sy(n));
+            const PsiPair<C> b = psi.at(stencil_dx<BND>(o, col, nx, flags, oo), sy(o));
+            const bool un = lds_sent(a.a), uo = lds_sent(b.a);
+            const bool cn = un || on, co = uo || oo;
+            add(n, cn ? q1[table1(n)] : a.a, cn ? q2[table1(n)] : a.b, un, co ? q1[table1(o)] : b.a,
+                co ? q2[table1(o)] : b.b, uo);
         }
     }
 }
