@@ -36,6 +36,7 @@ template <int S, int RX, int RY> struct BrickPost {
 };
 
 template <int S, int RX, int RY> struct BrickReload {
+    static constexpr bool TOGETHER = false;
     const PopMem<S> &m;
     uint32_t off;  // byte offset of the node in HBM
     const BrickPost<S, RX, RY> *post;

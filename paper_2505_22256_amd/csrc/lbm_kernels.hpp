@@ -106,12 +106,16 @@ __device__ __forceinline__ void issue_node(const PopMem<S> &m, int nx, const Axi
 // Where the bounce-back path reads f*_opp(i)(x, t-1) of the node itself:
 // the post-collision set in HBM (one step per launch) or the LDS ring of
 // the first of two fused steps.
+// TOGETHER: process_full reads several directions at once, in the lanes that
+// want them or not.
 template <int S> struct GlobalReload {
+    static constexpr bool TOGETHER = true;
     const PopMem<S> &m;
     uint32_t off;  // byte offset of the node
-    __device__ __forceinline__ typename Traits<S>::raw_t operator()(int k, int i) const
+    // (a lane that does not want the value loads nothing)
+    __device__ __forceinline__ typename Traits<S>::raw_t operator()(int k, int i, bool want = true) const
     {
-        return pop_load<S>(m, k, i, off);
+        return pop_load<S>(m, k, i, want ? off : OOB);
     }
 };
 
@@ -119,6 +123,15 @@ template <int S> struct GlobalReload {
 // f_i(x, t), with halfway bounce-back f_i(x, t) = f*_opp(i)(x, t-1) where
 // the source is unavailable (a sentinel or outside the domain), and the
 // densities rho_k = sum_i f_i (Eq. 3) in the definition's summation order.
+// The marching kernels read the reflected values four directions together and
+// select: under a branch per direction, one after the other, they cost a
+// wavefront at a wall up to eight trips to the L2 per row.  us per step alone /
+// three lattices at a time: 2048 x 1024 porous at tau 0.85 FP32 84 / 64 -> 78 /
+// 58, FP16 99 / 60 -> 95 / 54, FP64 252 / 147 -> 234 / 133, 3001 x 1027 channel
+// FP64 269 / 130 -> 258 / 126.  The boundary instances lose by it (open channel
+// of 8192 x 1024 FP32 203 / 158 -> 221 / 162: the loads of every direction
+// instead of the few that a straight edge needs), and so do the bricks, whose
+// reads go to LDS after the first step (400 x 400 FP64 13.8 / 8.5 -> 14.0 / 8.5).
 template <int S, bool BND, class St, class Reload>
 __device__ __forceinline__ void process_full(const KParams<typename Traits<S>::C> &p, const Reload &reload,
                                              const Axis &cx, const Axis &ry, bool valid, const RawRow<S> &q, St &st,
@@ -148,17 +161,42 @@ __device__ __forceinline__ void process_full(const KParams<typename Traits<S>::C
         if (__builtin_isnan(s1 + s2)) {
             // an unavailable source (or a non-finite state): reflect
             int info = 0;
+            if constexpr (Reload::TOGETHER) {
+#pragma unroll
+                for (int g = 1; g < 9; g += 4) {
+                    typename T::raw_t b[2][4];
+                    bool miss[4];
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        int col, row;
+                        bool ok;
+                        pull_source(g + h, cx, ry, col, row, ok);
+                        miss[h] = !ok || T::sent(q.v[0][g + h]);
+                        b[0][h] = reload(0, opp(g + h), miss[h]);
+                        b[1][h] = reload(1, opp(g + h), miss[h]);
+                    }
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        info |= (int)miss[h] << (g + h - 1);
+                        st.put_raw(g + h, miss[h] ? b[0][h] : q.v[0][g + h], miss[h] ? b[1][h] : q.v[1][g + h]);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int i = 1; i < 9; ++i) {
+                    int col, row;
+                    bool ok;
+                    pull_source(i, cx, ry, col, row, ok);
+                    if (!ok || T::sent(q.v[0][i])) {
+                        info |= 1 << (i - 1);
+                        st.put_raw(i, reload(0, opp(i)), reload(1, opp(i)));
+                    }
+                }
+            }
             s1 = 0;
             s2 = 0;
 #pragma unroll
             for (int i = 0; i < 9; ++i) {
-                int col, row;
-                bool ok;
-                pull_source(i, cx, ry, col, row, ok);
-                if (i > 0 && (!ok || T::sent(q.v[0][i]))) {
-                    info |= 1 << (i - 1);
-                    st.put_raw(i, reload(0, opp(i)), reload(1, opp(i)));
-                }
                 s1 += st.get(0, i);
                 s2 += st.get(1, i);
             }
@@ -883,9 +921,10 @@ __device__ __forceinline__ void issue_row_lds(FRingMem<S, BLOCK> *fring, int r, 
 }
 
 template <int S, int BLOCK> struct LdsReload {
+    static constexpr bool TOGETHER = true;
     FRingMem<S, BLOCK> *fring;
     int row, lane;
-    __device__ __forceinline__ typename Traits<S>::raw_t operator()(int k, int i) const
+    __device__ __forceinline__ typename Traits<S>::raw_t operator()(int k, int i, bool = true) const
     {
         return fr_at<S, BLOCK>(fring, k, i, row, lane);
     }
