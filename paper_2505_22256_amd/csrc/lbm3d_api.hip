@@ -409,10 +409,14 @@ int lbm3d_set_params(lbm3d_ctx *c, double G_c, double G_ads, double tau)
         // (here and not in a step, which a caller may capture; without room
         // the steps pull twice, as at any other relaxation time)
         const size_t bytes = (size_t)c->N * 6 * (c->storage == LBM_F64 ? sizeof(double) : sizeof(float));
+        // a capture that is under way, here or on another thread, goes on
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
         if (hipMalloc(&c->d_mom, bytes) != hipSuccess) {
             c->d_mom = nullptr;
             (void)hipGetLastError();
         }
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
     return LBM_OK;
 }

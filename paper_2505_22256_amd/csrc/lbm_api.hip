@@ -156,20 +156,13 @@ KParams<C> make_params(const lbm_ctx *c, const void *A, void *B, const Tile &t, 
 int grid_of(int strips, int segs) { return ((strips * segs + 7) / 8) * 8; }
 
 
-int compute_units(lbm_ctx *c)
-{
-    if (c->cus <= 0) {
-        hipDeviceProp_t prop;
-        c->cus = (hipGetDeviceProperties(&prop, c->device) == hipSuccess) ? prop.multiProcessorCount : 256;
-    }
-    return c->cus;
-}
+int compute_units(const lbm_ctx *c) { return c->cus; }
 
 // The tile of the marching kernels: the caller's, or the default with two
 // changes, so long as the caller has set or tuned none.
 //
 // Relaxation time 1: the kernels keep 4 values per row and component pair
-// instead of 18 (FP32 123 registers against 210, FP64 218 against 256 and 126
+// instead of 18 (FP32 119 registers against 203, FP64 211 against 256 and 119
 // accumulation registers), so more wavefronts share a SIMD and wider strips
 // pay.  16384 x 2048 channel, us per step, general kernels in the default tile
 // / relaxation time 1 in that tile / in this one: FP32 737 / 702 / 653, FP16
@@ -566,6 +559,7 @@ static int create_ctx(lbm_ctx **out, int nx, int ny, int storage, unsigned flags
         delete c;
         return LBM_EDEVICE;
     }
+    c->cus = prop.multiProcessorCount;
     const size_t bytes = (size_t)c->N * 18 * elem_size(storage);
     if (ext_a || ext_b) {
         // the caller's buffers: device memory of this device, distinct,

@@ -13,7 +13,7 @@
 // side) and marches down a segment of rows.  Each iteration pulls row y+2
 // into registers and the LDS ring, synchronises once, and finishes row y,
 // whose populations were pulled two iterations earlier and stayed in
-// registers.  HBM traffic is one read and one write of every population;
+// registers (where nothing needs them again, their momenta).  HBM traffic is one read and one write of every population;
 // halo re-reads hit L2.  Work items are dealt to the 8 XCDs in contiguous
 // chunks so that neighbouring segments share an L2.
 #pragma once
