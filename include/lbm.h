@@ -305,7 +305,7 @@ int lbm_set_stream(lbm_ctx *c, void *hip_stream);
  * seg_rows 48, LBM_SCHED_TWO_STEP | LBM_SCHED_BANDS.  Until a tile is set
  * or tuned, lattices too small to fill the GPU with strips (up to 851 968
  * nodes in FP32, 1 179 648 otherwise) run in bricks of several fused steps
- * instead, others too small for the default rows march in shorter segments,
+ * instead, others march in segments that fill the GPU evenly,
  * and at tau = 1 the library marches in wider strips (with open edges two
  * fused steps only on large lattices in 16-bit storage); lbm_get_tile keeps
  * giving the defaults above.  Results do not depend on the tile shape,

@@ -177,12 +177,18 @@ int compute_units(const lbm_ctx *c) { return c->cus; }
 //
 // Rows: a segment is a serial march, so a lattice whose segments are fewer than
 // the wavefronts that hide a march's latency (one per SIMD, two in the light
-// 16-bit kernels) gets shorter ones.  us per step alone / three at a time, the
-// default's rows / this: FP32 at tau 1 1500 x 600 74 / 33, 55 / 26; at 0.85 78
-// / 33, 58 / 31; FP16 at 0.85 2000 x 700 99 / 41, 60 / 30; FP64 at 0.85 2000 x
-// 700 172 / 66, 115 / 65.  More wavefronts than that shorten a lattice alone
-// further, but the halo rows cost three at a time (FP32 at 0.85 2000 x 700 in
-// 16 rows 60 / 46 against 79 / 44).
+// 16-bit kernels) gets shorter ones, and one whose segments are just more than
+// the wavefronts that the registers hold at once (by up to a quarter) gets taller
+// ones, as many as fit: the second round would run nearly empty.  us per step
+// alone / three at a time, the default's rows / these: too few, FP32 at tau 1 1500
+// x 600 74 / 33, 55 / 26; at 0.85 78 / 33, 58 / 31; FP16 at 0.85 2000 x 700 99 /
+// 41, 60 / 30; FP64 porous at 0.85 1800 x 800 172 / 93, 109 / 98; just too many,
+// channels of 3001 x 1027 at 0.85 FP64 258 / 131, 208 / 128, FP32 113 / 63, 92 /
+// 63, porous FP32 3200 x 1000 138 / 86, 95 / 84, FP64 2600 x 1100 305 / 178, 199 /
+// 179.  More wavefronts than that shorten a lattice alone further, but the halo
+// rows cost three at a time (FP32 at 0.85 2000 x 700 in 16 rows 60 / 46 against
+// 79 / 44).
+//
 // A step that runs alone there (the first on given populations, the last of an
 // odd number) takes the one-step tile in any case.
 Tile march_tile(lbm_ctx *c, bool two)
@@ -205,8 +211,13 @@ Tile march_tile(lbm_ctx *c, bool two)
     }
     const int w = t.block - (t.sched & SCHED_TWO_STEP ? 10 : 4);
     const long long waves = (long long)((c->nx + w - 1) / w) * (t.block / 64);  // of one segment over the width
-    const long long rows = c->ny * waves / (half ? 2 * simds : simds);
-    t.seg_rows = (int)std::min<long long>(t.seg_rows, std::max<long long>(rows, 8));
+    long long segs = (c->ny + t.seg_rows - 1) / t.seg_rows;
+    const long long least = half ? 2LL * simds : simds;
+    // wavefronts of the two-step kernels without boundary code that the registers hold at once
+    const long long held = (long long)simds * ((c->storage == LBM_F64 ? 1 : half ? 3 : 2) + (c->tau == 1.0));
+    if (waves * segs < least) segs = std::max<long long>(segs, std::min<long long>(least / waves, c->ny / 8));
+    else if (!bnd && waves * segs > held && 4 * waves * segs <= 5 * held) segs = held / waves;
+    t.seg_rows = (int)((c->ny + segs - 1) / segs);
     return t;
 }
 

@@ -17,10 +17,10 @@ def _workload(kind, nx, ny):
 
 
 # past the lattices that run in bricks: rows cut to about 14, to 26, a width of
-# a few strips, and (open, 16 million nodes) three rounds of wavefronts
+# a few strips, one segment per SIMD and a few more, and (open, 16 million nodes) three rounds of wavefronts
 @pytest.mark.parametrize("kind,nx,ny,storage,tau", [
     ("walls", 1100, 800, 1, 0.9), ("walls", 1100, 800, 1, 1.0), ("walls", 1700, 720, 2, 0.9), ("walls", 1700, 720, 3, 1.0),
-    ("walls", 300, 4001, 0, 0.9), ("walls", 300, 4001, 0, 1.0), ("open", 1801, 701, 2, 1.0), ("open", 1801, 701, 1, 1.0),
+    ("walls", 300, 4001, 0, 0.9), ("walls", 300, 4001, 0, 1.0), ("walls", 1600, 1700, 0, 0.9), ("open", 1801, 701, 2, 1.0), ("open", 1801, 701, 1, 1.0),
     ("open", 8201, 1991, 3, 1.0),
 ])
 def test_default_tile_equals_a_set_one(lbm_mod, kind, nx, ny, storage, tau):
