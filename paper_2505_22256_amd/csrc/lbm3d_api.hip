@@ -185,7 +185,7 @@ int run_pass3_t(lbm3d_ctx *c, Pass3 pass, double *fields, int *nparts)
     KParams3<C> p = make_params3<C>(c, c->buf[c->cur], c->buf[c->cur ^ 1], b.bx, b.by, b.bz);
     const int grid = collide3_grid(p);
     if (nparts) *nparts = grid;
-    if (pass != P3_STEP) {
+    if (pass == P3_REDUCE) {
         int rc = ensure_partials(c, (size_t)grid);
         if (rc) return rc;
         p.partials = c->d_partials;
@@ -273,23 +273,22 @@ int check_adh3(lbm3d_ctx *c, double Gw1, double Gw2, double delta)
     return LBM_OK;
 }
 
-// The diagnostics into d_out[0..8], with the fields (5N doubles) or without
-// (P3_REDUCE: 40 B per node not written; 200^3 FP32 418 -> 371 us).
-int reduce3(lbm3d_ctx *c, Pass3 pass, double *fields)
+// The diagnostics into d_out[0..8].
+int reduce3(lbm3d_ctx *c)
 {
     int nparts = 0;
-    const int rc = run_pass3(c, pass, fields, &nparts);
+    const int rc = run_pass3(c, P3_REDUCE, nullptr, &nparts);
     if (rc) return rc;
     hipLaunchKernelGGL(k_reduce3_final, dim3(1), dim3(256), 0, c->stream, c->d_partials, nparts, c->d_out);
     HIPCHK3(c, hipGetLastError());
     return LBM_OK;
 }
 
-// Fields + diagnostics pass into d_tmp and d_out.
-int fields_reduce3(lbm3d_ctx *c)
+// The fields into d_tmp (5N doubles).
+int fields3(lbm3d_ctx *c)
 {
     const int rc = ensure_tmp(c, (size_t)c->N * 5 * sizeof(double));
-    return rc ? rc : reduce3(c, P3_FIELDS_REDUCE, c->d_tmp);
+    return rc ? rc : run_pass3(c, P3_FIELDS, c->d_tmp, nullptr);
 }
 
 }  // namespace
@@ -544,7 +543,7 @@ int lbm3d_get_fields(lbm3d_ctx *c, double *rho1, double *rho2, double *ux, doubl
 {
     int rc = ready3(c);
     if (rc) return rc;
-    rc = fields_reduce3(c);
+    rc = fields3(c);
     if (rc) return rc;
     void *const outs[5] = {rho1, rho2, ux, uy, uz};
     const void *src[5];
@@ -558,7 +557,7 @@ int lbm3d_reduce(lbm3d_ctx *c, double out[9])
     int rc = ready3(c);
     if (rc) return rc;
     if (!out) return fail(c, LBM_EINVAL, "null output");
-    rc = reduce3(c, P3_REDUCE, nullptr);
+    rc = reduce3(c);
     if (rc) return rc;
     HIPCHK3(c, hipMemcpyAsync(out, c->d_out, 9 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK3(c, hipStreamSynchronize(c->stream));
@@ -575,7 +574,7 @@ int lbm3d_contact_angle(lbm3d_ctx *c, int wall_kind, const double wall[4], doubl
     if (rc) return rc;
     if (!wall || !theta_deg || (wall_kind != LBM3D_WALL_FLAT && wall_kind != LBM3D_WALL_SPHERE))
         return fail(c, LBM_EINVAL, "bad wall description");
-    rc = fields_reduce3(c);
+    rc = fields3(c);
     if (rc) return rc;
     Wall3 wd;
     wd.kind = wall_kind;

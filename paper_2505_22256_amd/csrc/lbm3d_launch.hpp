@@ -7,9 +7,8 @@
 
 namespace lbm3_host {
 
-// Kinds of pass: one step, the fields + diagnostics pass, or the diagnostics
-// alone.
-enum Pass3 { P3_STEP, P3_FIELDS_REDUCE, P3_REDUCE };
+// Kinds of pass: one step, the fields, or the diagnostics.
+enum Pass3 { P3_STEP, P3_FIELDS, P3_REDUCE };
 
 // Launch one pass (the density pass, then the collide pass with the
 // instance selected by the brick bx x by x bz with tz threads in z, the

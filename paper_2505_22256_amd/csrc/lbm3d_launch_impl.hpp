@@ -39,7 +39,7 @@ template <int S>
 hipError_t launch3(const KParams3<typename lbm::Traits<S>::C> &p, Pass3 pass, int bx, int by, int bz, int tz, bool sr,
                    hipStream_t st)
 {
-    if (pass == P3_FIELDS_REDUCE) return launch3_tile<S, K3_FIELDS | K3_REDUCE>(p, bx, by, bz, tz, st);
+    if (pass == P3_FIELDS) return launch3_tile<S, K3_FIELDS>(p, bx, by, bz, tz, st);
     if (pass == P3_REDUCE) return launch3_tile<S, K3_REDUCE>(p, bx, by, bz, tz, st);
     // relaxation time 1 (1 - omega is exactly 0) with room for the momenta
     const bool tau1 = p.omw == 0 && p.mom;

@@ -320,7 +320,7 @@ int run_pass_t(lbm_ctx *c, Pass pass, double *fields, uint8_t *link, uint8_t *nw
             return set_err(c, LBM_EINVAL, "%d workgroup partials exceed the %d the scratch array holds", grid,
                            max_parts);
         p.partials = partials;
-    } else if (pass == P_STEP_REDUCE || pass == P_FIELDS_REDUCE || pass == P_STEP2_RED1 || pass == P_STEP2_RED2 ||
+    } else if (pass == P_STEP_REDUCE || pass == P_STEP2_RED1 || pass == P_STEP2_RED2 ||
                pass == P_REDUCE) {
         int rc = ensure_partials(c, (size_t)grid);
         if (rc) return rc;
@@ -457,17 +457,11 @@ int reduce_only(lbm_ctx *c)
     return LBM_OK;
 }
 
-// Run the fields+diagnostics pass into d_tmp (4N doubles) and d_out[0..7].
-int fields_and_reduce(lbm_ctx *c)
+// The fields into d_tmp (4N doubles); the diagnostics are reduce_only's.
+int fields_only(lbm_ctx *c)
 {
-    int rc = ensure_tmp(c, (size_t)c->N * 4 * sizeof(double));
-    if (rc) return rc;
-    int nparts = 0;
-    rc = run_pass(c, P_FIELDS_REDUCE, c->d_tmp, nullptr, nullptr, nullptr, &nparts);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(256), 0, c->stream, c->d_partials, nparts, c->d_out);
-    HIPCHK(c, hipGetLastError());
-    return LBM_OK;
+    const int rc = ensure_tmp(c, (size_t)c->N * 4 * sizeof(double));
+    return rc ? rc : run_pass(c, P_FIELDS, c->d_tmp, nullptr, nullptr, nullptr, nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -974,7 +968,7 @@ int lbm_get_fields(lbm_ctx *c, double *rho1, double *rho2, double *ux, double *u
 {
     int rc = ready(c);
     if (rc) return rc;
-    rc = fields_and_reduce(c);
+    rc = fields_only(c);
     if (rc) return rc;
     void *const outs[4] = {rho1, rho2, ux, uy};
     const void *src[4];
@@ -1004,7 +998,7 @@ int lbm_contact_angle(lbm_ctx *c, int wall_kind, const double wall[3], double *t
     if (rc) return rc;
     if (!wall || !theta_deg || (wall_kind != LBM_WALL_FLAT && wall_kind != LBM_WALL_CYLINDER))
         return set_err(c, LBM_EINVAL, "bad wall description");
-    rc = fields_and_reduce(c);
+    rc = fields_only(c);
     if (rc) return rc;
     const WallDesc wd = {wall_kind, wall[0], wall[1], wall[2]};
     const RunSet rs = {nullptr, nullptr, c->nx, c->ny, 1};

@@ -47,8 +47,6 @@ struct lbm_batch {
     int n_fitems = 0;            // its work items
     uint8_t *d_solid = nullptr;
     double *d_fields = nullptr;  // 4 * total_nodes
-    double *d_partials = nullptr;
-    size_t partials_cap = 0;
     int *d_dims = nullptr;
     long long *d_offs = nullptr;
     WallDesc *d_walls = nullptr;
@@ -273,15 +271,7 @@ int fields_run_t(lbm_batch *b, int r)
     p.out_ux = b->d_fields + 2 * T + br.off;
     p.out_uy = b->d_fields + 3 * T + br.off;
     const int grid = ((p.n_units + 7) / 8) * 8;
-    if (b->partials_cap < (size_t)grid) {
-        if (b->d_partials) (void)hipFree(b->d_partials);
-        b->d_partials = nullptr;
-        b->partials_cap = 0;
-        BCHK(b, hipMalloc(&b->d_partials, (size_t)grid * 8 * sizeof(double)));
-        b->partials_cap = (size_t)grid;
-    }
-    p.partials = b->d_partials;
-    hipLaunchKernelGGL((k_step<S, 256, M_FIELDS | M_REDUCE>), dim3(grid), dim3(256), 0, b->stream, p, grid / 8);
+    hipLaunchKernelGGL((k_step<S, 256, M_FIELDS>), dim3(grid), dim3(256), 0, b->stream, p, grid / 8);
     BCHK(b, hipGetLastError());
     return LBM_OK;
 }
@@ -524,7 +514,7 @@ void lbm_batch_destroy(lbm_batch *b)
     if (!b) return;
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     drop_graphs(b);
-    void *ptrs[] = {b->buf[0], b->buf[1], b->d_params, b->d_fparams, b->d_solid, b->d_fields, b->d_partials,
+    void *ptrs[] = {b->buf[0], b->buf[1], b->d_params, b->d_fparams, b->d_solid, b->d_fields,
                     b->d_dims, b->d_offs, b->d_walls, b->d_out, b->d_tick};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);

@@ -12,7 +12,7 @@ namespace lbm_host {
 // record the diagnostics of the first / second of them.
 // P_REDUCE records the diagnostics of the current state without writing
 // anything else.
-enum Pass { P_STEP, P_STEP_REDUCE, P_FIELDS_REDUCE, P_TABLES, P_STEP2, P_STEP2_RED1, P_STEP2_RED2, P_REDUCE };
+enum Pass { P_STEP, P_STEP_REDUCE, P_FIELDS, P_TABLES, P_STEP2, P_STEP2_RED1, P_STEP2_RED2, P_REDUCE };
 
 // Launch one pass on `st` with the kernel instance that `pass`, `block`,
 // the rounding mode, `bnd` (open or moving boundaries on: the instance

@@ -75,7 +75,7 @@ hipError_t launch_pass_b(const KParams<typename Traits<S>::C> &p, Pass pass, int
     switch (pass) {
     case P_STEP: return launch_step_b<S, B | M_STORE>(p, block, st);
     case P_STEP_REDUCE: return launch_step_b<S, B | M_STORE | M_REDUCE>(p, block, st);
-    case P_FIELDS_REDUCE:
+    case P_FIELDS:
     case P_TABLES:
     case P_REDUCE: return hipErrorInvalidValue;  // launched by launch_pass
     case P_STEP2:
@@ -138,7 +138,7 @@ template <int S>
 hipError_t launch_pass(const KParams<typename Traits<S>::C> &p, Pass pass, int block, bool sr, bool bnd, hipStream_t st,
                        bool repull)
 {
-    if (pass == P_FIELDS_REDUCE) return launch_step_t<S, 256, M_BND | M_FIELDS | M_REDUCE>(p, st);
+    if (pass == P_FIELDS) return launch_step_t<S, 256, M_BND | M_FIELDS>(p, st);
     if (pass == P_REDUCE) return launch_step_t<S, 256, M_BND | M_REDUCE>(p, st);
     if (pass == P_TABLES) return launch_step_t<S, 256, M_BND | M_TABLES>(p, st);
     // (1 - omega is exactly 0; the diagnostic passes and the re-pull variant
