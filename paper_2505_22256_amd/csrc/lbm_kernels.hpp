@@ -1143,7 +1143,8 @@ __device__ __forceinline__ KParams<C> batch_run(const KParams<C> *__restrict__ r
 }
 
 // Batched step: the work list concatenates the units of all runs; run r
-// owns units [item0_r, item0_r + strips_r * segs_r).
+// owns units [item0_r, item0_r + strips_r * segs_r).  Each XCD takes per_xcd
+// units in a row, or (per_xcd 0) the units go to the XCDs in turn.
 template <int S, int BLOCK, int MODE>
 __global__ void __launch_bounds__(BLOCK)
 k_step_batch(const KParams<typename Traits<S>::C> *__restrict__ runs, int nruns, int n_items, int per_xcd, int flip,
@@ -1152,7 +1153,7 @@ k_step_batch(const KParams<typename Traits<S>::C> *__restrict__ runs, int nruns,
     using C = typename Traits<S>::C;
     __shared__ PsiPair<C> ring[8][BLOCK];
     const int b = blockIdx.x;
-    const int item = (b & 7) * per_xcd + (b >> 3);
+    const int item = per_xcd ? (b & 7) * per_xcd + (b >> 3) : b;
     if (item >= n_items) return;
     KParams<C> p = batch_run(runs, nruns, item, flip, tick);
     if ((MODE & M_STORE) && b == 0 && threadIdx.x == 0) tick[flip ^ 1] = tick[flip] + 1u;
@@ -1171,7 +1172,7 @@ k_step2_batch(const KParams<typename Traits<S>::C> *__restrict__ runs, int nruns
     __shared__ PsiPair<C> ring2[TWO_PR][BLOCK];
     __shared__ FRingMem<S, BLOCK> fring;
     const int b = blockIdx.x;
-    const int item = (b & 7) * per_xcd + (b >> 3);
+    const int item = per_xcd ? (b & 7) * per_xcd + (b >> 3) : b;
     if (item >= n_items) return;
     KParams<C> p = batch_run(runs, nruns, item, flip, tick);
     if (b == 0 && threadIdx.x == 0) tick[flip ^ 1] = tick[flip] + 2u;
