@@ -459,6 +459,71 @@ __device__ __forceinline__ void wall_sums(const Psi &psi, int col, int nx, C r1,
     }
 }
 
+// Stencil value at position n after the wall rules of Sec. 2.4 / Table 1,
+// resolved on the fly from the ring (at most two LDS reads): an unavailable
+// first-layer position reads zero (or psi(x) under WALLPSI_SELF); an
+// unavailable second-layer position reads what its Table 1 partner
+// resolves to (zero under E8_COPY_OFF).  Beyond an open edge a first-layer
+// position reads its ghost (when fluid) and a second-layer one takes the
+// Table 1 copy.  `solid` is the switch s of Eq. 9 at the position (beyond
+// an open edge: at its ghost).  Same rules as apply_wall_rules.
+template <class C, bool BND, class Psi>
+__device__ __forceinline__ PsiPair<C> resolve_position(const Psi &psi, int n, int col, int nx, C r1, C r2,
+                                                       unsigned flags, bool &solid)
+{
+    bool open;
+    const int dx = stencil_dx<BND>(n, col, nx, flags, open);
+    const PsiPair<C> v = psi.at(dx, sy(n));
+    solid = lds_sent(v.a);
+    if (!solid && (!open || n < 8)) return v;
+    PsiPair<C> self, zero;
+    self.a = r1;
+    self.b = r2;
+    zero.a = 0;
+    zero.b = 0;
+    const PsiPair<C> first_rule = (flags & FL_WALLPSI_SELF) ? self : zero;
+    if (n < 8) return first_rule;
+    if (flags & FL_COPY_OFF) return zero;
+    const int m = table1(n);
+    bool open_m;
+    const int dx_m = stencil_dx<BND>(m, col, nx, flags, open_m);
+    const PsiPair<C> w = psi.at(dx_m, sy(m));
+    return lds_sent(w.a) ? first_rule : w;
+}
+
+// wall_sums with a branch per position and lane, the same sums in the same
+// order, for the FP64 boundary instances: at one wavefront per SIMD they have
+// no registers for the resolved first layer (open channels, three lattices at a
+// time: 2608 x 1505 at tau 1.188 188 us per step against 197 with selection,
+// 5000 x 1000 at 0.8 229 against 242; alone the same).
+template <class C, bool BND, class Psi>
+__device__ __forceinline__ void wall_sums_branching(const Psi &psi, int col, int nx, C r1, C r2, unsigned flags, C &s1x, C &s1y,
+                                          C &s2x, C &s2y, C &Sx, C &Sy)
+{
+    // read the stencil afresh rather than keeping the bulk path's values
+    // alive across the branch (a compiler-only memory clobber, no code)
+    asm volatile("" ::: "memory");
+    s1x = 0; s1y = 0; s2x = 0; s2y = 0;
+    Sx = 0; Sy = 0;
+#pragma unroll
+    for (int g = 0; g < 6; ++g) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int n = 4 * g + h, o = n + 2;
+            bool un, uo;
+            const PsiPair<C> a = resolve_position<C, BND>(psi, n, col, nx, r1, r2, flags, un);
+            const PsiPair<C> b = resolve_position<C, BND>(psi, o, col, nx, r1, r2, flags, uo);
+            const C cx = (C)(e8wn(n) * sx(n));
+            const C cy = (C)(e8wn(n) * sy(n));
+            const C d1 = a.a - b.a;
+            const C d2 = a.b - b.b;
+            const C ds = (C)(int)un - (C)(int)uo;
+            if (sx(n) != 0) { s1x += cx * d1; s2x += cx * d2; Sx += cx * ds; }
+            if (sy(n) != 0) { s1y += cy * d1; s2y += cy * d2; Sy += cy * ds; }
+        }
+    }
+}
+
 // Where finish_node's results go: HBM, or the LDS ring of the first of two
 // fused steps (the values held until the second step has read the row
 // before stay in `pend`).
@@ -549,7 +614,11 @@ __device__ __forceinline__ void finish_node(const KParams<typename Traits<S>::C>
     C Sx = 0, Sy = 0;
     const bool near = __builtin_isnan(s1x + s1y + s2x + s2y);
     if (near) {
-        wall_sums<C, (MODE & M_BND) != 0>(psi, cx.c, p.nx, r1, r2, p.flags, s1x, s1y, s2x, s2y, Sx, Sy);
+        constexpr bool BND = (MODE & M_BND) != 0;
+        if constexpr (BND && S == ST_F64)
+            wall_sums_branching<C, BND>(psi, cx.c, p.nx, r1, r2, p.flags, s1x, s1y, s2x, s2y, Sx, Sy);
+        else
+            wall_sums<C, BND>(psi, cx.c, p.nx, r1, r2, p.flags, s1x, s1y, s2x, s2y, Sx, Sy);
     }
 
     if (MODE & M_TABLES) {
