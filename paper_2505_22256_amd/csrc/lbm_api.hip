@@ -237,9 +237,12 @@ int resident_capacity(lbm_ctx *c, int block)
 // the GPU: FP32 100 x 50 28.6 / 3.6, 400 x 400 64.8 / 7.9, 1000 x 800 71 / 22,
 // 1200 x 1000 75 / 31; three lattices stepped at the same time (per lattice):
 // 10.3 / 1.7, 23.3 / 5.6, 28.1 / 27.5, 30.7 / 41.2.  With three the chip is
-// full and the strips' smaller halo wins past 850 000 nodes in FP32; FP16
-// crosses between 1.2 M (38.8 / 27.0) and 2.1 M nodes (45.5 / 57.5), FP64
-// after 1.2 M (68.5 / 63.9, 2.1 M: 85 / 110).
+// full and the strips' smaller halo wins from about half a million nodes in FP32
+// on, while one alone still gains by bricks (1300 x 520, alone / three at a time:
+// bricks 20 / 26, strips 42 / 18; 2388 x 317 27 / 31, 46 / 21); the line lies in
+// between, where strips of 24 rows were no faster either way.  FP16 crosses
+// between 1.2 M (38.8 / 27.0) and 2.1 M nodes (45.5 / 57.5), FP64 after 1.2 M
+// (68.5 / 63.9, 2.1 M: 85 / 110).
 //
 // Steps per launch: while the bricks fit the chip's compute units once, a
 // deeper halo costs only idle units, so the largest region takes the most
@@ -259,7 +262,7 @@ struct BrickPlan {
 
 BrickPlan brick_plan(lbm_ctx *c)
 {
-    const long long most = (c->storage == LBM_F32 ? 13LL : 18LL) << 16;
+    const long long most = (c->storage == LBM_F32 ? 11LL : 18LL) << 16;
     if (c->own_tile || c->N > most) return {0, 0};
     const int cus = compute_units(c);
     auto fits = [&](int region, int steps) {
