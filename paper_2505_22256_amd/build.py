@@ -35,7 +35,7 @@ SOURCES = [os.path.join(CSRC, n + ".hip") for n in
            ["lbm_launch_" + n for n in ("f32", "f32_bnd", "f64_bnd", "f64", "f32_tau1", "f64_tau1")] +
            [u + n for u in ("lbm3d_launch_", "lbm_brick_") for n in ("bf16", "f16", "f64", "f32")] +
            ["lbm3d_api", "lbm_api"]]
-HEADERS = [os.path.join(CSRC, n) for n in ("lbm_device.hpp", "lbm_kernels.hpp", "lbm_params.hpp", "lbm_regions.hpp", "lbm_contact.hpp", "lbm_hostcopy.hpp",
+HEADERS = [os.path.join(CSRC, n) for n in ("lbm_device.hpp", "lbm_kernels.hpp", "lbm_params.hpp", "lbm_plan.hpp", "lbm_regions.hpp", "lbm_contact.hpp", "lbm_hostcopy.hpp",
                                             "lbm_launch.hpp", "lbm_launch_impl.hpp", "lbm_brick.hpp",
                                             "lbm_brick_impl.hpp", "lbm3d_kernels.hpp",
                                             "lbm3d_contact.hpp", "lbm3d_launch.hpp", "lbm3d_launch_impl.hpp")] + \

@@ -36,3 +36,25 @@ def test_default_tile_equals_a_set_one(lbm_mod, kind, nx, ny, storage, tau):
     assert np.array_equal(g.get_populations_window(x0, 0, w, ny), ref.get_populations_window(x0, 0, w, ny))
     for a, b in zip(g.get_fields(), ref.get_fields()):
         assert np.array_equal(a, b)
+
+
+# a few rows, so wide that one row of segments is more wavefronts than the
+# registers hold at once (FP64 60 000 x 10 steps in bricks, its field passes march)
+@pytest.mark.parametrize("nx,ny,storage,tau", [(60000, 40, 0, 0.9), (60000, 10, 0, 0.9), (130000, 20, 0, 1.0),
+                                               (130000, 16, 1, 0.85), (200000, 20, 1, 1.0), (180000, 30, 2, 0.9),
+                                               (250000, 30, 3, 1.0)])
+def test_wide_lattices_of_few_rows(lbm_mod, nx, ny, storage, tau):
+    wl = W.random_small(nx, nx, ny, 1, n_blobs=20, walls=True, drop=False)
+    wl.tau = tau
+    g = lbm_mod.lattice_from_workload(wl, storage)
+    ref = lbm_mod.lattice_from_workload(wl, storage)
+    ref.set_tile(128, 16, 2)
+    for q in (g, ref):
+        q.step(1)
+        q.step(4)
+    for a, b in zip(g.get_fields(), ref.get_fields()):
+        assert np.array_equal(a, b)
+    r, s = g.reduce(), ref.reduce()
+    assert np.array_equal(r[4:], s[4:])  # maxima, minima and a count
+    x0, w = nx // 3, 5000
+    assert np.array_equal(g.get_populations_window(x0, 0, w, ny), ref.get_populations_window(x0, 0, w, ny))

@@ -1,0 +1,63 @@
+"""The rules that choose tiles (csrc/lbm_plan.hpp) are plain arithmetic on sizes:
+compiled for the host and run over lattices of every shape, down to a few rows
+and up to the widest that lbm_create takes, every storage, closed and open, on
+whole and partitioned GPUs.  A segment has at least one row and no more than the
+lattice, and the widest strips are those the kernels are compiled for."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CXX = shutil.which("g++") or shutil.which("c++")
+
+SWEEP = r"""
+#include "lbm_plan.hpp"
+#include <cstdio>
+using namespace lbm_host;
+
+// the defaults of lbm_create, by storage, closed and open
+static Tile dflt(int storage, bool bnd)
+{
+    const unsigned two = SCHED_TWO_STEP | SCHED_BANDS;
+    if (storage == LBM_F32) return {bnd ? 64 : 128, 24, two};
+    if (storage == LBM_F64) return {64, 48, two};
+    return bnd ? Tile{128, 16, SCHED_BANDS} : Tile{64, 32, two};
+}
+
+int main()
+{
+    long long n = 0, bad = 0;
+    const int elem[4] = {8, 4, 2, 2};
+    for (int cus : {256, 128, 64, 32})
+        for (int storage = 0; storage < 4; ++storage)
+            for (int bnd = 0; bnd < 2; ++bnd)
+                for (double tau : {1.0, 0.85})
+                    for (int ny : {5, 7, 8, 12, 16, 20, 23, 24, 25, 31, 32, 33, 40, 48, 49, 64, 100, 333, 2048, 60000})
+                        for (long long nx = 5; nx * ny * 9 * elem[storage] < (1ll << 32); nx += 1 + nx / 37)
+                            for (int two = 0; two < 2; ++two) {
+                                const PlanInput l = {(int)nx, ny, storage, tau, bnd != 0, cus};
+                                const Tile t = march_tile(l, dflt(storage, bnd), two);
+                                const bool ok = t.seg_rows >= 1 && t.seg_rows <= ny &&
+                                                (t.block == 64 || t.block == 128 || t.block == 256) &&
+                                                !(storage == LBM_F64 && t.block == 256 && (t.sched & SCHED_TWO_STEP));
+                                ++n;
+                                if (!ok && bad++ < 5)
+                                    std::printf("%lld x %d storage %d bnd %d tau %g cus %d: %d %d %u\n", nx, ny, storage,
+                                                bnd, tau, cus, t.block, t.seg_rows, t.sched);
+                            }
+    std::printf("%lld lattices, %lld bad\n", n, bad);
+    return bad ? 1 : 0;
+}
+"""
+
+
+@pytest.mark.skipif(CXX is None, reason="no host compiler")
+def test_tiles_of_every_lattice(tmp_path):
+    src, exe = tmp_path / "sweep.cpp", tmp_path / "sweep"
+    src.write_text(SWEEP)
+    subprocess.run([CXX, "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2505_22256_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, (r.returncode, r.stdout)
