@@ -40,15 +40,15 @@ class HostCopier {
     }
 
     // dst[i] <- src[i], bytes each, for i < n (null dst: skipped), after the
-    // stream's work so far; returns when the data are there.
+    // stream's work so far; returns when the data are there.  `device` is the
+    // stream's; any other may be current.
     hipError_t copy(int device, hipStream_t st, void *const *dst, const void *const *src, size_t bytes, int n)
     {
         size_t total = 0;
         for (int i = 0; i < n; ++i) total += dst[i] ? bytes : 0;
-        if (total >= MIN_BYTES && ready()) {
-            bool started = false;
-            const hipError_t e = staged(device, st, dst, src, bytes, n, started);
-            if (started) return e;
+        if (total >= MIN_BYTES && ready(device)) {
+            if (staged(device, st, dst, src, bytes, n) == hipSuccess) return hipSuccess;
+            (void)hipGetLastError();  // the direct copy says whether the stream has failed
         }
         for (int i = 0; i < n; ++i)
             if (dst[i]) {
@@ -65,11 +65,18 @@ class HostCopier {
     hipEvent_t ev_[SLOTS] = {};
     bool failed_ = false;
 
-    bool ready()
+    // The slots and their events, which belong to the stream's device.
+    bool ready(int device)
     {
         if (pin_ || failed_) return pin_ != nullptr;
-        bool ok = hipHostMalloc((void **)&pin_, SLOTS * CHUNK, hipHostMallocDefault) == hipSuccess;
-        for (hipEvent_t &e : ev_) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+        int current = device;
+        bool ok = hipGetDevice(&current) == hipSuccess;
+        if (ok) {
+            if (current != device) ok = hipSetDevice(device) == hipSuccess;
+            ok = ok && hipHostMalloc((void **)&pin_, SLOTS * CHUNK, hipHostMallocDefault) == hipSuccess;
+            for (hipEvent_t &e : ev_) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+            if (current != device) (void)hipSetDevice(current);
+        }
         if (!ok) {
             (void)hipGetLastError();
             if (pin_) (void)hipHostFree(pin_);
@@ -85,8 +92,8 @@ class HostCopier {
         size_t bytes;
     };
 
-    hipError_t staged(int device, hipStream_t st, void *const *dst, const void *const *src, size_t bytes, int n,
-                      bool &started)
+    // (an error: the data may not be there)
+    hipError_t staged(int device, hipStream_t st, void *const *dst, const void *const *src, size_t bytes, int n)
     {
         std::vector<Piece> pieces;
         std::vector<std::thread> pool;
@@ -121,9 +128,8 @@ class HostCopier {
             pool.reserve(THREADS);
             for (int t = 0; t < THREADS; ++t) pool.emplace_back(work);
         } catch (const std::exception &) {
-            if (pool.empty()) return hipSuccess;  // no thread: the caller copies directly
+            if (pool.empty()) return hipErrorOutOfMemory;  // no thread
         }
-        started = true;
         for (long k = 0; k < (long)pieces.size(); ++k) {
             const int s = (int)(k % SLOTS);
             {
