@@ -5,7 +5,10 @@
 // every page fault: 448 MB (the fields of 200 x 200 x 280 nodes) came in 45 ms,
 // 26 ms when the pages were there, 8.2 ms into pinned memory.  Here the copy
 // goes through a few pinned slots in chunks, and several threads move the
-// chunks on (and take the faults) while the next ones arrive.
+// chunks on (and take the faults) while the next ones arrive.  Memory that HIP
+// knows (pinned, managed or device memory of the caller) is copied to directly:
+// into pinned arrays that is the faster way (537 MB 9.9 ms against 13.6 through
+// the slots), and the threads could not write device memory.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -46,7 +49,7 @@ class HostCopier {
     {
         size_t total = 0;
         for (int i = 0; i < n; ++i) total += dst[i] ? bytes : 0;
-        if (total >= MIN_BYTES && ready(device)) {
+        if (total >= MIN_BYTES && ordinary(dst, n) && ready(device)) {
             if (staged(device, st, dst, src, bytes, n) == hipSuccess) return hipSuccess;
             (void)hipGetLastError();  // the direct copy says whether the stream has failed
         }
@@ -64,6 +67,20 @@ class HostCopier {
     char *pin_ = nullptr;
     hipEvent_t ev_[SLOTS] = {};
     bool failed_ = false;
+
+    // Memory that HIP does not know.
+    static bool ordinary(void *const *dst, int n)
+    {
+        for (int i = 0; i < n; ++i) {
+            hipPointerAttribute_t at;
+            if (!dst[i]) continue;
+            if (hipPointerGetAttributes(&at, dst[i]) != hipSuccess)
+                (void)hipGetLastError();  // (older runtimes: an error for such memory)
+            else if (at.type != hipMemoryTypeUnregistered)
+                return false;
+        }
+        return true;
+    }
 
     // The slots and their events, which belong to the stream's device.
     bool ready(int device)

@@ -55,3 +55,18 @@ def test_two_threads(lbm_mod):
     [t.join() for t in th]
     for a, b in zip(got, want):
         assert all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("where", ["pinned", "device"])
+def test_outputs_in_memory_that_hip_knows(lbm_mod, where):
+    """Pinned and device arrays as outputs, above the threshold and below it."""
+    import torch
+    for nx, ny in ((1201, 903), (300, 200)):
+        g, _ = _lattice(lbm_mod, nx, ny, nx)
+        g.step(2)
+        kw = dict(pin_memory=True) if where == "pinned" else dict(device="cuda")
+        out = [torch.empty(ny, nx, dtype=torch.float64, **kw) for _ in range(4)]
+        lbm_mod._check(g.h, lbm_mod.load_library().lbm_get_fields(g.h, *[ctypes.c_void_p(t.data_ptr()) for t in out]))
+        torch.cuda.synchronize()
+        for a, b in zip(out, g.get_fields()):
+            assert np.array_equal(a.cpu().numpy(), b)

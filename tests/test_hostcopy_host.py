@@ -128,7 +128,7 @@ int main(int, char **argv)
 
 
 @pytest.mark.skipif(CXX is None, reason="no host compiler")
-@pytest.mark.parametrize("what", ["plain", "attr-error", "other-device", "no-pin", "half-way"])
+@pytest.mark.parametrize("what", ["plain", "attr-error", "other-device", "pinned", "device", "no-pin", "half-way"])
 def test_copies(tmp_path, what):
     (tmp_path / "hip").mkdir()
     (tmp_path / "hip" / "hip_runtime.h").write_text(HIP)
