@@ -87,12 +87,15 @@ class HostCopier {
     {
         if (pin_ || failed_) return pin_ != nullptr;
         int current = device;
-        bool ok = hipGetDevice(&current) == hipSuccess;
+        // a capture that is under way, here or on another thread, goes on
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        bool ok = hipGetDevice(&current) == hipSuccess && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
         if (ok) {
             if (current != device) ok = hipSetDevice(device) == hipSuccess;
             ok = ok && hipHostMalloc((void **)&pin_, SLOTS * CHUNK, hipHostMallocDefault) == hipSuccess;
             for (hipEvent_t &e : ev_) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
             if (current != device) (void)hipSetDevice(current);
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
         }
         if (!ok) {
             (void)hipGetLastError();

@@ -2,7 +2,7 @@
 the HIP runtime that keeps each call's rules: an event records only on a stream of
 its own device, a chunk's memory is what the runtime says it is.  What a GPU test
 cannot set up: another device current than the stream's, a runtime that fails
-half-way."""
+half-way, a capture under way."""
 import os
 import shutil
 import subprocess
@@ -128,7 +128,7 @@ int main(int, char **argv)
 
 
 @pytest.mark.skipif(CXX is None, reason="no host compiler")
-@pytest.mark.parametrize("what", ["plain", "attr-error", "other-device", "pinned", "device", "no-pin", "half-way"])
+@pytest.mark.parametrize("what", ["plain", "attr-error", "other-device", "pinned", "device", "no-pin", "half-way", "capture"])
 def test_copies(tmp_path, what):
     (tmp_path / "hip").mkdir()
     (tmp_path / "hip" / "hip_runtime.h").write_text(HIP)
