@@ -307,8 +307,8 @@ int lbm_set_stream(lbm_ctx *c, void *hip_stream);
  * nodes in FP32, 1 179 648 otherwise) run in bricks of several fused steps
  * instead, others march in segments that fill the GPU evenly,
  * and at tau = 1 the library marches in wider strips (with open edges two
- * fused steps only on large lattices in 16-bit storage); lbm_get_tile keeps
- * giving the defaults above.  Results do not depend on the tile shape,
+ * fused steps only on large lattices in 16-bit storage); lbm_get_tile gives
+ * the default above until then.  Results do not depend on the tile shape,
  * nor on bricks (bitwise).  sched bits: LBM_SCHED_ALIGN makes
  * strips a multiple of 128 bytes wide from x = 0, so that stores never
  * cover part of a cache line shared with another workgroup;
@@ -325,10 +325,14 @@ int lbm_set_stream(lbm_ctx *c, void *hip_stream);
  * when diagnostics are due every step) runs alone.  Populations are
  * bitwise those of single steps; diagnostics agree to rounding (the sums
  * run in another order).  lbm_autotune times the
- * current tile (or the bricks) and then every candidate for `steps` steps each on the
- * current state (restoring state and time afterwards); a candidate replaces
- * the best so far only when it is at least 2 % faster, so timing noise does
- * not move the choice between near-equal tiles.  LBM_SCHED_REPULL (with
+ * library's own choice (until a tile is set), the current tile and then every
+ * candidate for `steps` steps each on the current state (restoring state and
+ * time afterwards); a candidate replaces the best so far only when it is at
+ * least 2 % faster, so timing noise does not move the choice between near-equal
+ * tiles, and so does the best tile the library's choice.  lbm_get_tile then
+ * gives the best tile, also where the library's choice was faster and stays in
+ * use: setting that tile on a lattice like this one marches in it.
+ * LBM_SCHED_REPULL (with
  * LBM_SCHED_TWO_STEP, 64- or 128-thread strips, closed lattices without
  * sliding walls) makes the first of the two fused steps pull each row
  * again when it finishes it instead of holding the pulled rows in

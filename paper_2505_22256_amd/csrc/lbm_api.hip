@@ -49,9 +49,9 @@ struct lbm_ctx {
     bool fresh = false;
     bool have_geom = false, have_params = false, have_fields = false;
     long t = 0;
-    int block = 256, seg_rows = 0;
-    unsigned sched = 0;
-    bool own_tile = false;  // set by lbm_set_tile or chosen by lbm_autotune
+    lbm_host::Tile dflt = {256, 0, 0};  // the storage's default
+    lbm_host::Tile tile = {256, 0, 0};  // set by lbm_set_tile, the fastest that lbm_autotune timed, or the default
+    bool own_tile = false;              // steps run in `tile`, else as the library chooses
     int diag_every = 0;
     int cus = 0;
     long diag_t = -1;
@@ -160,8 +160,7 @@ PlanInput plan_input(const lbm_ctx *c) { return {c->nx, c->ny, c->storage, c->ta
 // long as the caller has set or tuned none.
 Tile march_tile(const lbm_ctx *c, bool two)
 {
-    const Tile t = {c->block, c->seg_rows, c->sched};
-    return c->own_tile ? t : march_tile(plan_input(c), t, two);
+    return c->own_tile ? c->tile : march_tile(plan_input(c), c->dflt, two);
 }
 
 // Workgroups of the step kernel that fit on the device at once.
@@ -225,7 +224,7 @@ BrickPlan brick_plan(lbm_ctx *c)
 // workgroups of 24 rows, 86 us in FP32, and take 200 of 4 rows, 26 us).
 int field_rows(lbm_ctx *c)
 {
-    const int rows = c->seg_rows > 0 ? c->seg_rows : 64;
+    const int own = c->own_tile ? c->tile.seg_rows : c->dflt.seg_rows, rows = own > 0 ? own : 64;
     const int strips = (c->nx + 251) / 252;
     const long long fill = (long long)c->ny * strips / compute_units(c);
     return (int)std::min<long long>(rows, std::max<long long>(fill, 4));
@@ -243,7 +242,7 @@ int run_pass_t(lbm_ctx *c, Pass pass, double *fields, uint8_t *link, uint8_t *nw
     Tile t = march_tile(c, two);
     const bool persistent = t.seg_rows == 0;
     if (persistent) t.seg_rows = 64;
-    if (!stepping) t = {256, field_rows(c), c->sched};
+    if (!stepping) t = {256, field_rows(c), c->own_tile ? c->tile.sched : c->dflt.sched};
     KParams<C> p = make_params<C>(c, c->buf[c->cur], c->buf[c->cur ^ 1], t, two ? 5 : 2);
     if ((t.sched & SCHED_XCD_SLABS) && stepping) {
         // one unit per (strip, row slab); the grid is 8 * strips so that
@@ -571,23 +570,12 @@ static int create_ctx(lbm_ctx **out, int nx, int ny, int storage, unsigned flags
     // nearest: 42.8 GLUPS against 39.8 for two fused steps in 64)
     const bool open_x = (flags & (LBM_INLET | LBM_OUTFLOW)) != 0;
     const bool sr = (c->flags & LBM_ROUND_STOCHASTIC) != 0;
-    if (storage == LBM_F32) {
-        c->block = open_x ? 64 : 128;
-        c->seg_rows = 24;
-        c->sched = SCHED_TWO_STEP | SCHED_BANDS;
-    } else if (storage == LBM_F64) {
-        c->block = 64;
-        c->seg_rows = 48;
-        c->sched = SCHED_TWO_STEP | SCHED_BANDS;
-    } else if ((storage == LBM_F16 || storage == LBM_BF16) && !(open_x && (sr || storage == LBM_BF16))) {
-        c->block = 64;
-        c->seg_rows = 32;
-        c->sched = SCHED_TWO_STEP | SCHED_BANDS;
-    } else {  // FP16 and BF16 with open x edges, one step per launch
-        c->block = 128;
-        c->seg_rows = 16;
-        c->sched = SCHED_BANDS;
-    }
+    const unsigned fused = SCHED_TWO_STEP | SCHED_BANDS;
+    if (storage == LBM_F32) c->dflt = {open_x ? 64 : 128, 24, fused};
+    else if (storage == LBM_F64) c->dflt = {64, 48, fused};
+    else if (!(open_x && (sr || storage == LBM_BF16))) c->dflt = {64, 32, fused};
+    else c->dflt = {128, 16, SCHED_BANDS};
+    c->tile = c->dflt;
     *out = c;
     return LBM_OK;
 }
@@ -1013,9 +1001,7 @@ int lbm_set_tile(lbm_ctx *c, int block, int seg_rows, unsigned sched)
         return set_err(c, LBM_EINVAL, "LBM_SCHED_REPULL needs LBM_SCHED_TWO_STEP");
     if ((sched & SCHED_TWO_STEP) && c->storage == LBM_F64 && block == 256)
         return set_err(c, LBM_EINVAL, "two fused steps in FP64 take block 64 or 128");
-    c->block = block;
-    c->seg_rows = seg_rows;
-    c->sched = sched;
+    c->tile = {block, seg_rows, sched};
     c->own_tile = true;
     return LBM_OK;
 }
@@ -1023,9 +1009,9 @@ int lbm_set_tile(lbm_ctx *c, int block, int seg_rows, unsigned sched)
 int lbm_get_tile(const lbm_ctx *c, int *block, int *seg_rows, unsigned *sched)
 {
     if (!c) return LBM_EINVAL;
-    if (block) *block = c->block;
-    if (seg_rows) *seg_rows = c->seg_rows;
-    if (sched) *sched = c->sched;
+    if (block) *block = c->tile.block;
+    if (seg_rows) *seg_rows = c->tile.seg_rows;
+    if (sched) *sched = c->tile.sched;
     return LBM_OK;
 }
 
@@ -1046,20 +1032,18 @@ int lbm_autotune(lbm_ctx *c, int steps)
     const bool fresh0 = c->fresh;
     const int blocks[3] = {64, 128, 256};
     const int rows[10] = {0, 8, 16, 24, 32, 48, 64, 128, 256, 512};
-    const int cur_b = c->block, cur_r = c->seg_rows;
-    const unsigned cur_s = c->sched;
+    const Tile cur = c->tile;
     const bool cur_own = c->own_tile;
-    bool best_own = cur_own;
-    int best_b = cur_b, best_r = cur_r;
-    unsigned best_s = cur_s;
-    float best_ms = 1e30f;
-    // candidate -1 is the incumbent tile; the rest need a 2 % margin to win.
+    Tile best = cur;
+    float best_ms = 1e30f, plan_ms = 1e30f;
+    // candidate -2 is the library's own choice, while no tile is set; -1 is the
+    // incumbent tile; the rest need a 2 % margin to win.
     // Each block x rows x schedule is tried with one step per launch and
     // with two fused steps per launch (FP64: 64- and 128-thread strips).
     const int n_two = 2;
-    for (int cand = -1; cand < 3 * 10 * 6 * n_two && e == hipSuccess && rc == LBM_OK; ++cand) {
-        int cb = cur_b, cr = cur_r;
-        unsigned sc = cur_s;
+    for (int cand = cur_own ? -1 : -2; cand < 3 * 10 * 6 * n_two && e == hipSuccess && rc == LBM_OK; ++cand) {
+        int cb = cur.block, cr = cur.seg_rows;
+        unsigned sc = cur.sched;
         if (cand >= 0) {
             const int tw = cand / 180, bi = (cand / 60) % 3, ri = (cand / 6) % 10;
             sc = (unsigned)(cand % 6);  // 0-3: align/bands bits; 4, 5: XCD slabs (+ align)
@@ -1071,10 +1055,8 @@ int lbm_autotune(lbm_ctx *c, int steps)
             cb = blocks[bi];
             cr = rows[ri];
         }
-        c->block = cb;
-        c->seg_rows = cr;
-        c->sched = sc;
-        c->own_tile = cand >= 0 || cur_own;
+        c->tile = {cb, cr, sc};
+        c->own_tile = cand >= -1;
         rc = lbm_step(c, 1);  // warm-up
         if (rc) break;
         e = hipEventRecord(ev0, c->stream);
@@ -1085,12 +1067,12 @@ int lbm_autotune(lbm_ctx *c, int steps)
         if (e == hipSuccess) e = hipEventSynchronize(ev1);
         float ms = 0;
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, ev0, ev1);
-        if (e == hipSuccess && (cand < 0 ? true : ms < 0.98f * best_ms)) {
+        if (e != hipSuccess) break;
+        if (cand == -2) {
+            plan_ms = ms;
+        } else if (cand == -1 || ms < 0.98f * best_ms) {
             best_ms = ms;
-            best_b = cb;
-            best_r = cr;
-            best_s = sc;
-            best_own = cand >= 0 || cur_own;
+            best = c->tile;
         }
     }
     if (e == hipSuccess) e = hipMemcpyAsync(c->buf[cur0], backup, bytes, hipMemcpyDeviceToDevice, c->stream);
@@ -1102,10 +1084,10 @@ int lbm_autotune(lbm_ctx *c, int steps)
     c->t = t0;
     c->fresh = fresh0;
     c->diag_t = diag_t0;
-    c->block = best_b;
-    c->seg_rows = best_r;
-    c->sched = best_s;
-    c->own_tile = best_own;
+    // the library's choice goes on unless a tile beats it; `tile` is the fastest
+    // tile either way, to be set on a lattice like this one
+    c->tile = best;
+    c->own_tile = cur_own || best_ms < 0.98f * plan_ms;
     if (rc) return rc;
     if (e != hipSuccess) return set_err(c, LBM_EDEVICE, "autotune failed: %s", hipGetErrorString(e));
     return LBM_OK;

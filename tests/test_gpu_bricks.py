@@ -84,3 +84,17 @@ def test_a_set_tile_marches_and_tuning_keeps_the_state(lbm_mod):
     a.step(6)
     b.step(11)
     _same(a, b)
+
+
+def test_tuning_reports_the_fastest_tile(lbm_mod):
+    """A lattice that is faster in bricks stays in them when tuned, and the tile
+    that tuning reports is the fastest of the tiles, not the default: the droplet's
+    three workgroups of 24 rows lose to shorter segments by far more than noise."""
+    wl = W.flat_drop()
+    a, b = _pair(lbm_mod, wl, lbm_mod.F32)
+    tile = a.autotune(8)
+    assert tile == a.get_tile() and tile != (128, 24, 10) and tile[1] != 24
+    b.set_tile(*tile)
+    for q in (a, b):
+        q.step(9)
+    _same(a, b)
