@@ -3,6 +3,7 @@
 #pragma once
 
 #include "lbm_launch.hpp"
+#include "lbm_plan.hpp"
 
 #include <algorithm>
 
@@ -99,15 +100,17 @@ hipError_t launch_pass_b(const KParams<typename Traits<S>::C> &p, Pass pass, int
     return hipErrorInvalidValue;
 }
 
-// Steps at relaxation time 1 (M_TAU1): the plain one- and two-step passes.
+// Steps at relaxation time 1 (M_TAU1): the plain passes for which momenta_pay.
 template <int S, int MODE>
 hipError_t launch_tau1_m(const KParams<typename Traits<S>::C> &p, Pass pass, int block, hipStream_t st)
 {
-    if (pass == P_STEP) return launch_step_b<S, MODE>(p, block, st);
-    if constexpr (S == ST_F64)
+    if constexpr (S == ST_F64) {
         return block == 128 ? launch_step2_t<S, 128, MODE>(p, st) : launch_step2_t<S, 64, MODE>(p, st);
-    else
-        return launch_step2_b<S, MODE>(p, block, st);
+    } else if constexpr (S == ST_F32) {
+        return block == 128 ? launch_step2_t<S, 128, MODE>(p, st) : launch_step2_t<S, 256, MODE>(p, st);
+    } else {
+        return pass == P_STEP ? launch_step_b<S, MODE>(p, block, st) : launch_step2_b<S, MODE>(p, block, st);
+    }
 }
 
 template <int S>
@@ -143,7 +146,7 @@ hipError_t launch_pass(const KParams<typename Traits<S>::C> &p, Pass pass, int b
     if (pass == P_TABLES) return launch_step_t<S, 256, M_BND | M_TABLES>(p, st);
     // (1 - omega is exactly 0; the diagnostic passes and the re-pull variant
     // are not compiled for it and give the same results)
-    if (p.omw == 0 && (pass == P_STEP || pass == P_STEP2) && !(repull && !bnd))
+    if (p.omw == 0 && (pass == P_STEP || pass == P_STEP2) && momenta_pay(S, block, pass == P_STEP2) && !(repull && !bnd))
         return launch_tau1<S>(p, pass, block, sr, bnd, st);
     return bnd ? launch_pass_b<S, M_BND>(p, pass, block, sr, st, false)
                : launch_pass_b<S, 0>(p, pass, block, sr, st, repull);

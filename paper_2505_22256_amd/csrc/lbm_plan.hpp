@@ -88,4 +88,18 @@ inline Tile march_tile(const PlanInput &l, Tile t, bool two)
     return t;
 }
 
+// Whether the steps of relaxation time 1 run in the kernels that keep momenta in
+// this block.  One step per launch, FP32 and FP64 gain nothing by them (the state of
+// a row is held for two rows only) and the wavefronts that the registers then admit
+// crowd each other's halo out of the L2: channel of 4096 x 2048, us per step, general
+// / momenta: FP64 (64, 16) in bands 648 / 681, (256, 16) 580 / 606, FP32 (256, 16)
+// 318 / 329; only the porous 2048 x 1024 in FP64 gains, 214 / 203.  Nor do two FP32
+// steps in 64-thread strips: channel in 24 rows 214 / 227, with open edges 136 / 146,
+// porous 75 / 75.  16-bit storage gains everywhere (FP16 (256, 16) 202 / 194).
+inline bool momenta_pay(int storage, int block, bool two)
+{
+    if (storage == LBM_F32) return two && block >= 128;
+    return two || storage != LBM_F64;
+}
+
 }  // namespace lbm_host
