@@ -158,9 +158,9 @@ PlanInput plan_input(const lbm_ctx *c) { return {c->nx, c->ny, c->storage, c->ta
 
 // The tile of the marching kernels: the caller's, or the rule of lbm_plan.hpp so
 // long as the caller has set or tuned none.
-Tile march_tile(const lbm_ctx *c, bool two)
+Tile march_tile(const lbm_ctx *c, bool two, bool record = false)
 {
-    return c->own_tile ? c->tile : march_tile(plan_input(c), c->dflt, two);
+    return c->own_tile ? c->tile : march_tile(plan_input(c), c->dflt, two, record);
 }
 
 // Workgroups of the step kernel that fit on the device at once.
@@ -239,7 +239,7 @@ int run_pass_t(lbm_ctx *c, Pass pass, double *fields, uint8_t *link, uint8_t *nw
     using C = typename Traits<S>::C;
     const bool two = pass == P_STEP2 || pass == P_STEP2_RED1 || pass == P_STEP2_RED2;
     const bool stepping = pass == P_STEP || pass == P_STEP_REDUCE || two;
-    Tile t = march_tile(c, two);
+    Tile t = march_tile(c, two, pass == P_STEP_REDUCE);
     const bool persistent = t.seg_rows == 0;
     if (persistent) t.seg_rows = 64;
     if (!stepping) t = {256, field_rows(c), c->own_tile ? c->tile.sched : c->dflt.sched};

@@ -60,11 +60,22 @@ struct PlanInput {
 //
 // A step that runs alone there (the first on given populations, the last of an
 // odd number) takes the one-step tile in any case.
-inline Tile march_tile(const PlanInput &l, Tile t, bool two)
+//
+// A step that runs alone to record diagnostics (`record`) is a one-step launch in
+// any case, which loses the fewest columns in wide strips.  In the strips of the
+// fused steps it had become slower than it was, for more wavefronts in flight; us
+// per step recording every step, at first / in those strips / in these: FP32 open
+// 8192 x 1024 at 0.85 395 / 416 / 330, channel 8192 x 2048 718 / 708 / 629, porous
+// 2048 x 1024 123 / 107 / 105; FP16 channel 506 / 513 / 418 (256 threads: 379, but
+// porous 143 / 90 / 90 and 96), open at tau 1 281 / 285 / 244.  FP64 gained in its
+// strips (open 438 / 426, porous 250 / 197, in 256 threads 351 and 219) and stays.
+inline Tile march_tile(const PlanInput &l, Tile t, bool two, bool record = false)
 {
     const bool half = l.storage == LBM_F16 || l.storage == LBM_BF16;
     const int simds = 4 * l.cus;
-    if (l.tau == 1.0) {
+    if (record && l.storage != LBM_F64) {
+        t = {half ? 128 : 256, 16, SCHED_BANDS};
+    } else if (l.tau == 1.0) {
         if (l.storage == LBM_F64) {
             t = {128, l.bnd ? 32 : 24, t.sched};
         } else if (l.storage == LBM_F32) {
@@ -83,7 +94,7 @@ inline Tile march_tile(const PlanInput &l, Tile t, bool two)
     // wavefronts of the two-step kernels without boundary code that the registers hold at once
     const long long held = (long long)simds * ((l.storage == LBM_F64 ? 1 : half ? 3 : 2) + (l.tau == 1.0));
     if (waves * segs < least) segs = std::max<long long>(segs, std::min<long long>(least / waves, l.ny / 8));
-    else if (!l.bnd && waves <= held && waves * segs > held && 4 * waves * segs <= 5 * held) segs = held / waves;
+    else if (!l.bnd && (t.sched & SCHED_TWO_STEP) && waves <= held && waves * segs > held && 4 * waves * segs <= 5 * held) segs = held / waves;
     t.seg_rows = (int)((l.ny + segs - 1) / segs);
     return t;
 }

@@ -58,3 +58,26 @@ def test_wide_lattices_of_few_rows(lbm_mod, nx, ny, storage, tau):
     assert np.array_equal(r[4:], s[4:])  # maxima, minima and a count
     x0, w = nx // 3, 5000
     assert np.array_equal(g.get_populations_window(x0, 0, w, ny), ref.get_populations_window(x0, 0, w, ny))
+
+
+# a step that records runs alone in a tile of its own
+@pytest.mark.parametrize("kind,nx,ny,storage", [("walls", 1100, 800, 1), ("walls", 1700, 720, 2), ("walls", 300, 4001, 0),
+                                                ("open", 1801, 701, 1), ("open", 1801, 701, 3), ("open", 1801, 701, 0),
+                                                ("walls", 100, 60, 1), ("open", 350, 150, 2)])
+def test_recording_steps_by_default(lbm_mod, kind, nx, ny, storage):
+    wl = W.obstacle_drop() if kind == "open" and nx == 350 else _workload(kind, nx, ny)
+    wl.tau = 0.9
+    g = lbm_mod.lattice_from_workload(wl, storage)
+    ref = lbm_mod.lattice_from_workload(wl, storage)
+    ref.set_tile(128, 16, 2)
+    for q in (g, ref):
+        q.set_diag_interval(1)
+        q.step(1)
+        q.step(4)
+    (d, t), (r, _) = g.get_diag(), ref.get_diag()
+    tol = 1e-12 if storage == 0 else 1e-5  # sums in another order (FP32 partial sums below FP64)
+    assert t == 4 and np.array_equal(d[4:], r[4:])  # maxima, minima and a count
+    assert np.all(np.abs(d[:2] - r[:2]) <= tol * np.abs(r[:2]))
+    assert np.all(np.abs(d[2:4] - r[2:4]) <= tol * (r[0] + r[1]) * r[4])
+    for a, b in zip(g.get_fields(), ref.get_fields()):
+        assert np.array_equal(a, b)

@@ -43,6 +43,13 @@ int main()
                                                 (t.block == 64 || t.block == 128 || t.block == 256) &&
                                                 !(storage == LBM_F64 && t.block == 256 && (t.sched & SCHED_TWO_STEP));
                                 ++n;
+                                // a recording step runs alone, and not in narrow strips
+                                const Tile r = march_tile(l, dflt(storage, bnd), false, true);
+                                const bool rok = r.seg_rows >= 1 && r.seg_rows <= ny &&
+                                                 (storage == LBM_F64 || (!(r.sched & SCHED_TWO_STEP) && r.block >= 128));
+                                if (!rok && bad++ < 5)
+                                    std::printf("%lld x %d storage %d bnd %d tau %g cus %d recording: %d %d %u\n", nx, ny,
+                                                storage, bnd, tau, cus, r.block, r.seg_rows, r.sched);
                                 if (!ok && bad++ < 5)
                                     std::printf("%lld x %d storage %d bnd %d tau %g cus %d: %d %d %u\n", nx, ny, storage,
                                                 bnd, tau, cus, t.block, t.seg_rows, t.sched);
