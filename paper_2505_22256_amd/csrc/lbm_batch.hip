@@ -36,6 +36,7 @@ struct BatchRun {
 
 struct lbm_batch {
     int nruns = 0, storage = 0;
+    int cus = 256;  // compute units of the device
     int block = 256, seg_rows = 64;
     std::vector<BatchRun> runs;
     long long total_nodes = 0, total_fluid = 0;
@@ -149,28 +150,11 @@ int upload_params(lbm_batch *b)
     }
 }
 
-// Units of a work list that each XCD takes in a row, 0 to deal them to the XCDs
-// in turn.  Runs differ in their walls, and a wavefront at a wall takes longer:
-// in one piece per XCD the XCD with the most walls finishes last, in turn they
-// finish together but neighbours lose their common L2.  In turn pays from two
-// wavefronts per SIMD on in FP32 and FP64, where 16-bit storage, quicker and so
-// more dependent on its loads, wants four, and no more than sixteen, where the
-// pieces are long enough to even out.  us per two steps, in a row / in turn: 48
-// runs of 128 to 512 nodes a side FP32 (64 threads, 16 rows) 298 / 255, (128, 24)
-// 315 / 264, FP16 267 / 257, (128, 24) 316 / 296, (64, 32) 282 / 287; 256 runs
-// FP32 (64, 16) 1268 / 1215, BF16 1094 / 1113; 24 runs FP32 (128, 48) 252 / 261.
-template <int S> int units_per_xcd(int n_items, int block)
-{
-    const long long per_simd = (long long)n_items * (block / 64) / 1024;  // 256 CUs
-    const bool turn = S == ST_F16 || S == ST_BF16 ? per_simd >= 4 && per_simd < 16 : per_simd >= 2;
-    return turn ? 0 : (n_items + 7) / 8;
-}
-
 template <int S, int BLOCK>
 hipError_t launch_batch_t(lbm_batch *b, int flip)
 {
     using C = typename Traits<S>::C;
-    const int per_xcd = units_per_xcd<S>(b->n_items, BLOCK), grid = (b->n_items + 7) / 8 * 8;
+    const int per_xcd = units_per_xcd(S, b->n_items, BLOCK, b->cus), grid = (b->n_items + 7) / 8 * 8;
     const bool sr = (S == ST_F16 || S == ST_BF16) && (b->runs[0].flags & LBM_ROUND_STOCHASTIC);
     if constexpr (S == ST_F16 || S == ST_BF16) {
         if (sr)
@@ -204,7 +188,7 @@ template <int S, int BLOCK>
 hipError_t launch_batch2_t(lbm_batch *b, int flip)
 {
     using C = typename Traits<S>::C;
-    const int per_xcd = units_per_xcd<S>(b->n_items, BLOCK), grid = (b->n_items + 7) / 8 * 8;
+    const int per_xcd = units_per_xcd(S, b->n_items, BLOCK, b->cus), grid = (b->n_items + 7) / 8 * 8;
     const auto *prm = (const KParams<C> *)b->d_params;
     unsigned *const tick = b->d_tick;
     bool done = false;
@@ -342,7 +326,7 @@ int fields_all_t(lbm_batch *b)
         b->d_fparams = d;
         b->n_fitems = item;
     }
-    const int per_xcd = units_per_xcd<S>(b->n_fitems, FIELD_BLOCK), grid = (b->n_fitems + 7) / 8 * 8;
+    const int per_xcd = units_per_xcd(S, b->n_fitems, FIELD_BLOCK, b->cus), grid = (b->n_fitems + 7) / 8 * 8;
     hipLaunchKernelGGL((k_step_batch<S, FIELD_BLOCK, M_FIELDS>), dim3(grid), dim3(FIELD_BLOCK), 0, b->stream,
                        (const KParams<C> *)b->d_fparams, b->nruns, b->n_fitems, per_xcd, b->flip,
                        b->d_tick);
@@ -409,6 +393,12 @@ int lbm_batch_create(lbm_batch **out, int nruns, const lbm_run_desc *runs, int s
     if (!b) return LBM_ENOMEM;
     b->nruns = nruns;
     b->storage = storage;
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess ||
+        hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || b->cus < 1) {
+        delete b;
+        return LBM_EDEVICE;
+    }
     b->runs.resize((size_t)nruns);
     long long off = 0;
     for (int r = 0; r < nruns; ++r) {

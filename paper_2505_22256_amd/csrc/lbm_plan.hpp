@@ -113,4 +113,22 @@ inline bool momenta_pay(int storage, int block, bool two)
     return two || storage != LBM_F64;
 }
 
+// Units of a batch's work list that each XCD takes in a row, 0 to deal them to the XCDs
+// in turn.  Runs differ in their walls, and a wavefront at a wall takes longer:
+// in one piece per XCD the XCD with the most walls finishes last, in turn they
+// finish together but neighbours lose their common L2.  In turn pays from two
+// wavefronts per SIMD on in FP32 and FP64, where 16-bit storage, quicker and so
+// more dependent on its loads, wants four, and no more than sixteen, where the
+// pieces are long enough to even out.  us per two steps, in a row / in turn: 48
+// runs of 128 to 512 nodes a side FP32 (64 threads, 16 rows) 298 / 255, (128, 24)
+// 315 / 264, FP16 267 / 257, (128, 24) 316 / 296, (64, 32) 282 / 287; 256 runs
+// FP32 (64, 16) 1268 / 1215, BF16 1094 / 1113; 24 runs FP32 (128, 48) 252 / 261.
+inline int units_per_xcd(int storage, int n_items, int block, int cus)
+{
+    const long long per_simd = (long long)n_items * (block / 64) / (4 * cus);
+    const bool half = storage == LBM_F16 || storage == LBM_BF16;
+    const bool turn = half ? per_simd >= 4 && per_simd < 16 : per_simd >= 2;
+    return turn ? 0 : (n_items + 7) / 8;
+}
+
 }  // namespace lbm_host

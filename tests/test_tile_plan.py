@@ -54,6 +54,16 @@ int main()
                                     std::printf("%lld x %d storage %d bnd %d tau %g cus %d: %d %d %u\n", nx, ny, storage,
                                                 bnd, tau, cus, t.block, t.seg_rows, t.sched);
                             }
+    // batches: in turn at the same wavefronts per SIMD whatever the GPU's size
+    for (int cus : {256, 128, 64, 32})
+        for (int storage = 0; storage < 4; ++storage)
+            for (int per_simd = 0; per_simd < 20; ++per_simd) {
+                const bool turn = storage < 2 ? per_simd >= 2 : per_simd >= 4 && per_simd < 16;
+                const int items = 4 * cus * per_simd + 3, u = units_per_xcd(storage, items, 64, cus);
+                ++n;
+                if (u != (turn ? 0 : (items + 7) / 8) && bad++ < 5)
+                    std::printf("batch: storage %d cus %d items %d: %d in a row\n", storage, cus, items, u);
+            }
     std::printf("%lld lattices, %lld bad\n", n, bad);
     return bad ? 1 : 0;
 }
