@@ -38,7 +38,7 @@ SOURCES = [os.path.join(CSRC, n + ".hip") for n in
 HEADERS = [os.path.join(CSRC, n) for n in ("lbm_device.hpp", "lbm_kernels.hpp", "lbm_params.hpp", "lbm_plan.hpp", "lbm_regions.hpp", "lbm_contact.hpp", "lbm_hostcopy.hpp",
                                             "lbm_launch.hpp", "lbm_launch_impl.hpp", "lbm_brick.hpp",
                                             "lbm_brick_impl.hpp", "lbm3d_kernels.hpp",
-                                            "lbm3d_contact.hpp", "lbm3d_launch.hpp", "lbm3d_launch_impl.hpp")] + \
+                                            "lbm3d_contact.hpp", "lbm3d_momenta.hpp", "lbm3d_launch.hpp", "lbm3d_launch_impl.hpp")] + \
     [os.path.join(ROOT, "include", "lbm.h"), os.path.join(ROOT, "include", "lbm3d.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -3,6 +3,7 @@
 #include "lbm3d.h"
 #include "lbm3d_contact.hpp"
 #include "lbm3d_launch.hpp"
+#include "lbm3d_momenta.hpp"
 #include "lbm_hostcopy.hpp"
 #include "lbm_params.hpp"
 
@@ -41,7 +42,7 @@ struct lbm3d_ctx {
     bool own_tile = false;                // set by lbm3d_set_tile
     int cus = 256;
     void *d_psi = nullptr;        // density-pass output: psi of both components per node
-    void *d_mom = nullptr;        // and their momenta, once the relaxation time is set to 1
+    Momenta mom;                  // and their momenta, once the relaxation time is set to 1
     lbm_host::HostCopier copier;  // large arrays to host memory
     std::string err;
 };
@@ -106,7 +107,7 @@ KParams3<C> make_params3(const lbm3d_ctx *c, const void *A, void *B, int bx, int
     p.bricks_y = (c->ny + by - 1) / by;
     p.bricks_z = (c->nz + bz - 1) / bz;
     p.psi = (PsiPair<C> *)c->d_psi;
-    p.mom = (PsiPair<C> *)c->d_mom;
+    p.mom = (PsiPair<C> *)c->mom.get();
     p.tick = (unsigned)c->t;
     p.N = c->N;
     const double tau = c->tau;
@@ -172,7 +173,7 @@ Brick3 step_brick(const lbm3d_ctx *c)
     if (c->own_tile) return {c->bx, c->by, c->bz, c->tz};
     if (small_lattice(c, 16)) return {16, 4, 4, 4};
     const bool half = c->storage == LBM_F16 || c->storage == LBM_BF16;
-    return {32, 8, 4, c->tau == 1.0 && c->d_mom ? (half ? 2 : 4) : c->tz};
+    return {32, 8, 4, c->tau == 1.0 && c->mom.get() ? (half ? 2 : 4) : c->tz};
 }
 
 template <int S>
@@ -355,7 +356,7 @@ void lbm3d_destroy(lbm3d_ctx *c)
 {
     if (!c) return;
     if (c->stream) (void)hipStreamSynchronize(c->stream);
-    for (void *p : {c->buf[0], c->buf[1], c->d_psi, c->d_mom, (void *)c->d_solid, (void *)c->d_tmp, (void *)c->d_partials,
+    for (void *p : {c->buf[0], c->buf[1], c->d_psi, (void *)c->d_solid, (void *)c->d_tmp, (void *)c->d_partials,
                     (void *)c->d_out})
         if (p) (void)hipFree(p);
     if (c->own_stream) (void)hipStreamDestroy(c->own_stream);
@@ -404,19 +405,8 @@ int lbm3d_set_params(lbm3d_ctx *c, double G_c, double G_ads, double tau)
     c->delta = 0.8;
     c->tau = tau;
     c->have_params = true;
-    if (tau == 1.0 && !c->d_mom) {
-        // (here and not in a step, which a caller may capture; without room
-        // the steps pull twice, as at any other relaxation time)
-        const size_t bytes = (size_t)c->N * 6 * (c->storage == LBM_F64 ? sizeof(double) : sizeof(float));
-        // a capture that is under way, here or on another thread, goes on
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-        if (hipMalloc(&c->d_mom, bytes) != hipSuccess) {
-            c->d_mom = nullptr;
-            (void)hipGetLastError();
-        }
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-    }
+    // (without room the steps pull twice, as at any other relaxation time)
+    if (tau == 1.0) c->mom.want(c->device, (size_t)c->N * 6 * (c->storage == LBM_F64 ? sizeof(double) : sizeof(float)));
     return LBM_OK;
 }
 

@@ -1,0 +1,117 @@
+"""The memory of the 3-D momenta (csrc/lbm3d_momenta.hpp) on the host, against a
+small stand-in for the HIP runtime: two devices with a bounded amount of memory
+each, and captures that a plain allocation would end."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CXX = shutil.which("g++") or shutil.which("c++")
+
+HIP = r"""
+#pragma once
+#include <cstddef>
+#include <map>
+enum hipError_t { hipSuccess = 0, hipErrorOutOfMemory = 2, hipErrorStreamCaptureUnsupported = 900 };
+enum hipStreamCaptureMode { hipStreamCaptureModeGlobal, hipStreamCaptureModeThreadLocal, hipStreamCaptureModeRelaxed };
+enum hipStreamCaptureStatus { hipStreamCaptureStatusNone, hipStreamCaptureStatusActive };
+struct Stream { bool capturing = false; int syncs = 0; };
+typedef Stream *hipStream_t;
+struct Runtime {
+    int current = 0;
+    size_t room[2] = {1000, 1000};
+    bool capture_elsewhere = false;
+    hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
+    std::map<void *, std::pair<int, size_t>> live;  // address -> device, bytes
+    char *next = (char *)0x1000;
+};
+extern Runtime rt;
+inline hipError_t hipGetDevice(int *d) { *d = rt.current; return hipSuccess; }
+inline hipError_t hipSetDevice(int d) { rt.current = d; return hipSuccess; }
+inline hipError_t hipGetLastError() { return hipSuccess; }
+inline hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *m)
+{
+    const hipStreamCaptureMode old = rt.mode;
+    rt.mode = *m;
+    *m = old;
+    return hipSuccess;
+}
+inline hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *st)
+{
+    *st = s->capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+inline hipError_t hipStreamSynchronize(hipStream_t s)
+{
+    if (s->capturing) return hipErrorStreamCaptureUnsupported;
+    ++s->syncs;
+    return hipSuccess;
+}
+inline hipError_t hipMalloc(void **p, size_t n)
+{
+    if (rt.capture_elsewhere && rt.mode != hipStreamCaptureModeRelaxed) return hipErrorStreamCaptureUnsupported;
+    if (rt.room[rt.current] < n) return hipErrorOutOfMemory;
+    rt.room[rt.current] -= n;
+    *p = rt.next;
+    rt.next += 4096;
+    rt.live[*p] = {rt.current, n};
+    return hipSuccess;
+}
+template <class T> hipError_t hipMalloc(T **p, size_t n) { return hipMalloc((void **)p, n); }
+inline hipError_t hipFree(void *p)
+{
+    rt.room[rt.live[p].first] += rt.live[p].second;
+    rt.live.erase(p);
+    return hipSuccess;
+}
+"""
+
+MAIN = r"""
+#include "lbm3d_momenta.hpp"
+#include <cstdio>
+#include <string>
+using namespace lbm3_host;
+Runtime rt;
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); rc = 1; } } while (0)
+
+int main(int, char **argv)
+{
+    const std::string what = argv[1];
+    int rc = 0;
+    {
+        Momenta m;
+        if (what == "device") {  // on the context's device, the other stays current
+            m.want(1, 300);
+            CHECK(m.get() && rt.room[0] == 1000 && rt.room[1] == 700 && rt.current == 0);
+            m.want(1, 300);  // once
+            CHECK(rt.room[1] == 700);
+        }
+        if (what == "capture") {  // a capture on another thread goes on
+            rt.capture_elsewhere = true;
+            m.want(0, 300);
+            CHECK(m.get() && rt.mode == hipStreamCaptureModeGlobal);
+        }
+        if (what == "no-room") {
+            m.want(0, 2000);
+            CHECK(!m.get() && rt.live.empty());
+        }
+    }
+    CHECK(rt.live.empty());  // freed with the context
+    return rc;
+}
+"""
+
+
+@pytest.mark.skipif(CXX is None, reason="no host compiler")
+@pytest.mark.parametrize("what", ["device", "capture", "no-room"])
+def test_memory(tmp_path, what):
+    (tmp_path / "hip").mkdir()
+    (tmp_path / "hip" / "hip_runtime.h").write_text(HIP)
+    (tmp_path / "main.cpp").write_text(MAIN)
+    exe = tmp_path / "main"
+    subprocess.run([CXX, "-O1", "-std=c++17", "-I", str(tmp_path), "-I", os.path.join(ROOT, "paper_2505_22256_amd", "csrc"),
+                    str(tmp_path / "main.cpp"), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe), what], capture_output=True, text=True)
+    assert r.returncode == 0, (r.returncode, r.stdout)
