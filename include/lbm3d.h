@@ -133,8 +133,9 @@ int lbm3d_contact_angle(lbm3d_ctx *c, int wall_kind, const double wall[4], doubl
  * values per node) and then the collide pass, which stages psi of its brick
  * and a 2-node halo in LDS and pulls the populations of its own nodes; at
  * tau = 1 the density pass also leaves the nodes' momenta (6 values per node
- * of device memory, allocated by lbm3d_set_params when there is room) and
- * the collide pass pulls nothing.  Results do not depend on the brick
+ * of device memory, allocated by lbm3d_set_params when there is room, and
+ * given back to a later call that needs the room for its own scratch unless a
+ * step was captured) and the collide pass pulls nothing.  Results do not depend on the brick
  * (bitwise). */
 int lbm3d_set_tile(lbm3d_ctx *c, int bx, int by, int bz, int tz);
 int lbm3d_get_tile(const lbm3d_ctx *c, int *bx, int *by, int *bz, int *tz);

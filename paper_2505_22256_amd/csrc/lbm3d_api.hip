@@ -76,7 +76,8 @@ int ensure_tmp(lbm3d_ctx *c, size_t bytes)
     if (c->d_tmp) (void)hipFree(c->d_tmp);
     c->d_tmp = nullptr;
     c->tmp_bytes = 0;
-    if (hipMalloc(&c->d_tmp, bytes) != hipSuccess) return fail(c, LBM_ENOMEM, "device allocation of %zu bytes failed", bytes);
+    if (alloc_scratch(&c->d_tmp, bytes, c->mom, c->stream) != hipSuccess)
+        return fail(c, LBM_ENOMEM, "device allocation of %zu bytes failed", bytes);
     c->tmp_bytes = bytes;
     return LBM_OK;
 }
@@ -87,7 +88,8 @@ int ensure_partials(lbm3d_ctx *c, size_t n)
     if (c->d_partials) (void)hipFree(c->d_partials);
     c->d_partials = nullptr;
     c->partials_cap = 0;
-    if (hipMalloc(&c->d_partials, n * 9 * sizeof(double)) != hipSuccess) return fail(c, LBM_ENOMEM, "partials allocation failed");
+    if (alloc_scratch(&c->d_partials, n * 9 * sizeof(double), c->mom, c->stream) != hipSuccess)
+        return fail(c, LBM_ENOMEM, "partials allocation failed");
     c->partials_cap = n;
     return LBM_OK;
 }
@@ -184,6 +186,7 @@ int run_pass3_t(lbm3d_ctx *c, Pass3 pass, double *fields, int *nparts)
                      : small_lattice(c, 8) ? Brick3{16, 4, 4, 4}
                                            : Brick3{32, 8, 4, 1};
     KParams3<C> p = make_params3<C>(c, c->buf[c->cur], c->buf[c->cur ^ 1], b.bx, b.by, b.bz);
+    if (pass == P3_STEP && p.omw == 0) c->mom.used(c->stream);
     const int grid = collide3_grid(p);
     if (nparts) *nparts = grid;
     if (pass == P3_REDUCE) {

@@ -36,8 +36,42 @@ class Momenta {
         (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
 
+    // A step on `st` is about to use them.
+    void used(hipStream_t st)
+    {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusActive;
+        if (!p_ || captured_) return;
+        if (hipStreamIsCapturing(st, &status) != hipSuccess) (void)hipGetLastError();
+        captured_ = status != hipStreamCaptureStatusNone;
+    }
+
+    // Free them after the work on `st`; false where there are none, or a captured
+    // step may use them again.
+    bool give_back(hipStream_t st)
+    {
+        if (!p_ || captured_ || hipStreamSynchronize(st) != hipSuccess) return false;
+        (void)hipFree(p_);
+        p_ = nullptr;
+        return true;
+    }
+
   private:
     void *p_ = nullptr;
+    bool captured_ = false;
 };
+
+// Allocate scratch that a call cannot do without: where the room is gone the
+// momenta, which only save time, make place for it.
+template <class T> hipError_t alloc_scratch(T **p, size_t bytes, Momenta &mom, hipStream_t st)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess) return e;
+    if (mom.give_back(st)) {
+        (void)hipGetLastError();
+        e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) *p = nullptr;
+    return e;
+}
 
 }  // namespace lbm3_host

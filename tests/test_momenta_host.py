@@ -97,6 +97,32 @@ int main(int, char **argv)
             m.want(0, 2000);
             CHECK(!m.get() && rt.live.empty());
         }
+        Stream st;
+        void *scratch = nullptr;
+        if (what == "give-back") {  // room for the scratch but not for both
+            m.want(0, 300);
+            m.used(&st);
+            CHECK(alloc_scratch(&scratch, 600, m, &st) == hipSuccess && m.get() && st.syncs == 0);
+            (void)hipFree(scratch);
+            CHECK(alloc_scratch(&scratch, 800, m, &st) == hipSuccess && scratch && !m.get() && st.syncs == 1);
+            (void)hipFree(scratch);
+            m.want(0, 300);  // and taken again where there is room
+            CHECK(m.get());
+            CHECK(alloc_scratch(&scratch, 2000, m, &st) != hipSuccess && !scratch);
+        }
+        if (what == "captured") {  // a graph may run the step again: it keeps them
+            m.want(0, 300);
+            st.capturing = true;
+            m.used(&st);
+            st.capturing = false;
+            CHECK(alloc_scratch(&scratch, 800, m, &st) != hipSuccess && !scratch && m.get());
+        }
+        if (what == "under-capture") {
+            m.want(0, 300);
+            m.used(&st);
+            st.capturing = true;
+            CHECK(alloc_scratch(&scratch, 800, m, &st) != hipSuccess && m.get());
+        }
     }
     CHECK(rt.live.empty());  // freed with the context
     return rc;
@@ -105,7 +131,7 @@ int main(int, char **argv)
 
 
 @pytest.mark.skipif(CXX is None, reason="no host compiler")
-@pytest.mark.parametrize("what", ["device", "capture", "no-room"])
+@pytest.mark.parametrize("what", ["device", "capture", "no-room", "give-back", "captured", "under-capture"])
 def test_memory(tmp_path, what):
     (tmp_path / "hip").mkdir()
     (tmp_path / "hip" / "hip_runtime.h").write_text(HIP)
