@@ -303,9 +303,10 @@ int lbm_set_stream(lbm_ctx *c, void *hip_stream);
  * LBM_INLET or LBM_OUTFLOW BF16, and FP16 with stochastic rounding (its
  * default), take block 128, seg_rows 16, LBM_SCHED_BANDS; FP64 block 64,
  * seg_rows 48, LBM_SCHED_TWO_STEP | LBM_SCHED_BANDS.  Until a tile is set
- * or tuned, lattices too small to fill the GPU with strips (up to 720 896
- * nodes in FP32, 1 179 648 otherwise) run in bricks of several fused steps
- * instead, others march in segments that fill the GPU evenly,
+ * or tuned, lattices too small to fill the GPU with strips (up to 557 056
+ * nodes in FP32, 655 360 in FP64 and 1 179 648 in 16-bit storage; with open or
+ * sliding boundaries 720 896, 851 968 and 688 128) run in bricks of several
+ * fused steps instead, others march in segments that fill the GPU evenly,
  * and at tau = 1 the library marches in wider strips (with open edges two
  * fused steps only on large lattices in 16-bit storage); lbm_get_tile gives
  * the default above until then.  Results do not depend on the tile shape,

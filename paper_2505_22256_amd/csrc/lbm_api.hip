@@ -170,53 +170,9 @@ int resident_capacity(lbm_ctx *c, int block)
     return step_occupancy<S>(block) * compute_units(c);
 }
 
-// Bricks (lbm_brick.hpp) for the steps of this lattice: the region and the
-// steps per launch, or no steps where marching strips is faster.  A tile
-// that the caller has set or tuned always marches.
-//
-// The line: a lattice stops being a latency chain when the strips fill the
-// chip.  Cylinder lattices, us per step marching / in bricks, one lattice on
-// the GPU: FP32 100 x 50 28.6 / 3.6, 400 x 400 64.8 / 7.9, 1000 x 800 71 / 22,
-// 1200 x 1000 75 / 31; three lattices stepped at the same time (per lattice):
-// 10.3 / 1.7, 23.3 / 5.6, 28.1 / 27.5, 30.7 / 41.2.  With three the chip is
-// full and the strips' smaller halo wins from about half a million nodes in FP32
-// on, while one alone still gains by bricks (1300 x 520, alone / three at a time:
-// bricks 20 / 26, strips 42 / 18; 2388 x 317 27 / 31, 46 / 21); the line lies in
-// between, where strips of 24 rows were no faster either way.  FP16 crosses
-// between 1.2 M (38.8 / 27.0) and 2.1 M nodes (45.5 / 57.5), FP64 after 1.2 M
-// (68.5 / 63.9, 2.1 M: 85 / 110).
-//
-// Steps per launch: while the bricks fit the chip's compute units once, a
-// deeper halo costs only idle units, so the largest region takes the most
-// steps that still fit (FP32 100 x 50: 4 steps 3.6, 2 steps 4.4, 1 step 6.7;
-// 200 x 200: 3 steps 5.3, 2 6.5, 4 7.0, where 400 bricks no longer fit).
-// Past that FP32 and the 16-bit storages take single steps in 32 x 16
-// regions, which finish 66 % of their nodes (400 x 400 FP32: 7.9 against 8.7
-// for two steps in 32 x 32; FP16 8.6 against 10.2); FP64, whose pulls are
-// twice as long, and the boundary instances take two steps in 32 x 32
-// (720 x 700 FP64 28.7 against 29.7, 26.6 against 30.2 with three lattices;
-// 700 x 300 with open edges, FP32 13.2 against 15.2).  The FP64 boundary
-// instance has no registers for 32 x 32 (204 B per lane spilled) and stays
-// in 32 x 16 (700 x 300: 22.0 against 28.3).
-struct BrickPlan {
-    int region, steps;
-};
-
-BrickPlan brick_plan(lbm_ctx *c)
-{
-    const long long most = (c->storage == LBM_F32 ? 11LL : 18LL) << 16;
-    if (c->own_tile || c->N > most) return {0, 0};
-    const int cus = compute_units(c);
-    auto fits = [&](int region, int steps) {
-        const int w = brick_core(brick_rx(region), steps), h = brick_core(brick_ry(region), steps);
-        return (long long)((c->nx + w - 1) / w) * ((c->ny + h - 1) / h) <= cus;
-    };
-    const bool bnd = boundary_steps(c);
-    if (c->storage == LBM_F64 && bnd) return {1, fits(1, 2) ? 2 : 1};
-    for (int k = 4; k > 1; --k)
-        if (fits(2, k)) return {2, k};
-    return c->storage == LBM_F64 || bnd ? BrickPlan{2, 2} : BrickPlan{1, 1};
-}
+// Bricks for the steps of this lattice: the rule of lbm_plan.hpp; a tile that
+// the caller has set or tuned always marches.
+BrickPlan brick_plan(const lbm_ctx *c) { return c->own_tile ? BrickPlan{0, 0} : brick_plan(plan_input(c)); }
 
 // Rows per segment of the field, diagnostic and table passes: the tile's, or
 // as few as give every compute unit a workgroup where the tile leaves some idle

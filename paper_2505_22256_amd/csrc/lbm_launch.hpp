@@ -5,6 +5,7 @@
 #pragma once
 
 #include "lbm_kernels.hpp"
+#include "lbm_plan.hpp"
 
 namespace lbm_host {
 
@@ -22,13 +23,6 @@ enum Pass { P_STEP, P_STEP_REDUCE, P_FIELDS, P_TABLES, P_STEP2, P_STEP2_RED1, P_
 template <int S>
 hipError_t launch_pass(const lbm::KParams<typename lbm::Traits<S>::C> &p, Pass pass, int block, bool sr, bool bnd,
                        hipStream_t st, bool repull = false);
-
-// Regions of the brick kernel (lbm_brick.hpp): nodes along x and y, one
-// thread each, and what is left of a side after the halo of `steps` steps.
-constexpr int BRICK_REGIONS = 3;
-constexpr int brick_rx(int region) { return region == 0 ? 16 : 32; }
-constexpr int brick_ry(int region) { return region == 2 ? 32 : 16; }
-constexpr int brick_core(int side, int steps) { return side - 2 * (3 * steps - 1); }
 
 // Advance `steps` steps in one launch of the brick kernel.
 template <int S>

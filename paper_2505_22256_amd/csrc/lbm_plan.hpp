@@ -113,6 +113,64 @@ inline bool momenta_pay(int storage, int block, bool two)
     return two || storage != LBM_F64;
 }
 
+// Regions of the brick kernel (lbm_brick.hpp): nodes along x and y, one
+// thread each, and what is left of a side after the halo of `steps` steps.
+constexpr int BRICK_REGIONS = 3;
+constexpr int brick_rx(int region) { return region == 0 ? 16 : 32; }
+constexpr int brick_ry(int region) { return region == 2 ? 32 : 16; }
+constexpr int brick_core(int side, int steps) { return side - 2 * (3 * steps - 1); }
+
+// Bricks for the steps of a lattice: the region and the steps per launch, or no
+// steps where marching strips is the choice.
+//
+// The line: a lattice stops being a latency chain when the strips fill the chip.
+// One lattice on the GPU gains by bricks far beyond that; several stepped at the
+// same time fill it together, and there the strips' smaller halo wins (bricks step
+// up where they need another round of workgroups).  The line lies where bricks would
+// lose, with three lattices, to the strips as they were before bricks came; wide
+// channels with few wall nodes, the quickest in strips, decide it.  us per step alone
+// / three at a time (per lattice), those strips / bricks / today's strips: FP32
+// channels 1732 x 289 56 / 21.2, 17 / 14.6, 35 / 14.0; 2660 x 221 51 / 19.8, 20 /
+// 22.2, -; 2049 x 342 60 / 24.6, 22 / 27.0, 41 / 17.4; open 837 x 836 84 / 33.6, 26 /
+// 25.6, 62 / 25.0; FP64 channels 2792 x 232 117 / 44.5, 39 / 40.1, -; 2898 x 241 111
+// / 41.9, 41 / 42.4, -; 2569 x 428 146 / 59.5, 71 / 64.5, 81 / 52.7; open 2191 x 365
+// 219 / 78.8, 64 / 70.3, 96 / 48.7; 1049 x 1049 227 / 85.8, 98 / 91.8, 116 / 70.2;
+// 16-bit closed 3746 x 312 82 / 35.3, 31 / 33.3, -; open 2877 x 239 65 / 28.6, 31 /
+// 24.9, -; 2939 x 244 61 / 26.8, 34 / 27.9, -; 1000 x 1000 70 / 31.0, 40 / 34.3, 44 /
+// 22.6.
+//
+// Steps per launch: while the bricks fit the chip's compute units once, a
+// deeper halo costs only idle units, so the largest region takes the most
+// steps that still fit (FP32 100 x 50: 4 steps 3.6, 2 steps 4.4, 1 step 6.7;
+// 200 x 200: 3 steps 5.3, 2 6.5, 4 7.0, where 400 bricks no longer fit).
+// Past that FP32 and the 16-bit storages take single steps in 32 x 16
+// regions, which finish 66 % of their nodes (400 x 400 FP32: 7.9 against 8.7
+// for two steps in 32 x 32; FP16 8.6 against 10.2); FP64, whose pulls are
+// twice as long, and the boundary instances take two steps in 32 x 32
+// (720 x 700 FP64 28.7 against 29.7, 26.6 against 30.2 with three lattices;
+// 700 x 300 with open edges, FP32 13.2 against 15.2).  The FP64 boundary
+// instance has no registers for 32 x 32 (204 B per lane spilled) and stays
+// in 32 x 16 (700 x 300: 22.0 against 28.3).
+struct BrickPlan {
+    int region, steps;
+};
+
+inline BrickPlan brick_plan(const PlanInput &l)
+{
+    const long long most = l.storage == LBM_F32   ? (l.bnd ? 11LL << 16 : 17LL << 15)
+                           : l.storage == LBM_F64 ? (l.bnd ? 13LL << 16 : 10LL << 16)
+                                                  : (l.bnd ? 21LL << 15 : 18LL << 16);
+    if ((long long)l.nx * l.ny > most) return {0, 0};
+    auto fits = [&](int region, int steps) {
+        const int w = brick_core(brick_rx(region), steps), h = brick_core(brick_ry(region), steps);
+        return (long long)((l.nx + w - 1) / w) * ((l.ny + h - 1) / h) <= l.cus;
+    };
+    if (l.storage == LBM_F64 && l.bnd) return {1, fits(1, 2) ? 2 : 1};
+    for (int k = 4; k > 1; --k)
+        if (fits(2, k)) return {2, k};
+    return l.storage == LBM_F64 || l.bnd ? BrickPlan{2, 2} : BrickPlan{1, 1};
+}
+
 // Units of a batch's work list that each XCD takes in a row, 0 to deal them to the XCDs
 // in turn.  Runs differ in their walls, and a wavefront at a wall takes longer:
 // in one piece per XCD the XCD with the most walls finishes last, in turn they

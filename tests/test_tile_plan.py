@@ -54,6 +54,29 @@ int main()
                                     std::printf("%lld x %d storage %d bnd %d tau %g cus %d: %d %d %u\n", nx, ny, storage,
                                                 bnd, tau, cus, t.block, t.seg_rows, t.sched);
                             }
+    // bricks: a core is left of every region, small lattices run in them, and wide ones
+    // that strips step faster several at a time do not
+    for (int cus : {256, 64})
+        for (int storage = 0; storage < 4; ++storage)
+            for (int bnd = 0; bnd < 2; ++bnd)
+                for (int ny : {5, 28, 100, 341, 1000})
+                    for (long long nx = 5; nx < 200000; nx += 1 + nx / 29) {
+                        const BrickPlan b = brick_plan({(int)nx, ny, storage, 0.85, bnd != 0, cus});
+                        const bool ok = b.steps ? b.steps <= 4 && brick_core(brick_rx(b.region), b.steps) > 0 &&
+                                                      brick_core(brick_ry(b.region), b.steps) > 0 && nx * ny < 1200000
+                                                : nx * ny > 500000;
+                        ++n;
+                        if (!ok && bad++ < 5)
+                            std::printf("bricks: %lld x %d storage %d bnd %d cus %d: %d %d\n", nx, ny, storage, bnd, cus,
+                                        b.region, b.steps);
+                    }
+    const int wide[][4] = {{2660, 221, 1, 0}, {2049, 342, 1, 0}, {2898, 241, 0, 0}, {2569, 428, 0, 0},
+                           {1049, 1049, 0, 1}, {2939, 244, 2, 1}, {1000, 1000, 3, 1}};
+    for (auto &w : wide) {
+        ++n;
+        if (brick_plan({w[0], w[1], w[2], 0.85, w[3] != 0, 256}).steps && bad++ < 5)
+            std::printf("%d x %d storage %d bnd %d runs in bricks\n", w[0], w[1], w[2], w[3]);
+    }
     // batches: in turn at the same wavefronts per SIMD whatever the GPU's size
     for (int cus : {256, 128, 64, 32})
         for (int storage = 0; storage < 4; ++storage)
