@@ -13,8 +13,8 @@
 // per two steps (FP32); in bricks the same two steps are two pulls and two
 // finishes of all nodes at once.  The price is the halo, computed again by
 // every brick that touches it (a 32 x 32 region finishes 22 x 22 nodes of two
-// steps, 10 x 10 of four), which idle compute units pay for; brick_steps (in
-// lbm_launch.hpp) draws the line.
+// steps, 10 x 10 of four), which idle compute units pay for; brick_plan (in
+// lbm_plan.hpp) draws the line.
 #pragma once
 
 #include "lbm_kernels.hpp"

@@ -25,11 +25,10 @@ hipError_t launch_brick_m(KParams<typename Traits<S>::C> &p, int region, int ste
     if (w < 1 || h < 1) return hipErrorInvalidValue;
     const int tiles_x = (p.nx + w - 1) / w, tiles_y = (p.ny + h - 1) / h;
     p.n_units = tiles_x * tiles_y;
-    switch (region) {
-    case 0: return launch_brick_t<S, brick_rx(0), brick_ry(0), MODE>(p, steps, tiles_x, st);
-    case 1: return launch_brick_t<S, brick_rx(1), brick_ry(1), MODE>(p, steps, tiles_x, st);
-    default: return launch_brick_t<S, brick_rx(2), brick_ry(2), MODE>(p, steps, tiles_x, st);
-    }
+    if (region == 0) return launch_brick_t<S, brick_rx(0), brick_ry(0), MODE>(p, steps, tiles_x, st);
+    // (FP64 with boundary code has no registers for the larger region)
+    if constexpr (S == ST_F64 && (MODE & M_BND)) return hipErrorInvalidValue;
+    else return launch_brick_t<S, brick_rx(1), brick_ry(1), MODE>(p, steps, tiles_x, st);
 }
 
 template <int S>

@@ -113,11 +113,10 @@ inline bool momenta_pay(int storage, int block, bool two)
     return two || storage != LBM_F64;
 }
 
-// Regions of the brick kernel (lbm_brick.hpp): nodes along x and y, one
-// thread each, and what is left of a side after the halo of `steps` steps.
-constexpr int BRICK_REGIONS = 3;
-constexpr int brick_rx(int region) { return region == 0 ? 16 : 32; }
-constexpr int brick_ry(int region) { return region == 2 ? 32 : 16; }
+// Regions of the brick kernel (lbm_brick.hpp), 32 x 16 and 32 x 32: nodes along x
+// and y, one thread each, and what is left of a side after the halo of `steps` steps.
+constexpr int brick_rx(int) { return 32; }
+constexpr int brick_ry(int region) { return region == 0 ? 16 : 32; }
 constexpr int brick_core(int side, int steps) { return side - 2 * (3 * steps - 1); }
 
 // Bricks for the steps of a lattice: the region and the steps per launch, or no
@@ -149,8 +148,8 @@ constexpr int brick_core(int side, int steps) { return side - 2 * (3 * steps - 1
 // twice as long, and the boundary instances take two steps in 32 x 32
 // (720 x 700 FP64 28.7 against 29.7, 26.6 against 30.2 with three lattices;
 // 700 x 300 with open edges, FP32 13.2 against 15.2).  The FP64 boundary
-// instance has no registers for 32 x 32 (204 B per lane spilled) and stays
-// in 32 x 16 (700 x 300: 22.0 against 28.3).
+// instance had no registers for 32 x 32 (204 B per lane spilled, 700 x 300 28.3
+// us against 22.0) and stays in 32 x 16.
 struct BrickPlan {
     int region, steps;
 };
@@ -165,10 +164,10 @@ inline BrickPlan brick_plan(const PlanInput &l)
         const int w = brick_core(brick_rx(region), steps), h = brick_core(brick_ry(region), steps);
         return (long long)((l.nx + w - 1) / w) * ((l.ny + h - 1) / h) <= l.cus;
     };
-    if (l.storage == LBM_F64 && l.bnd) return {1, fits(1, 2) ? 2 : 1};
+    if (l.storage == LBM_F64 && l.bnd) return {0, fits(0, 2) ? 2 : 1};
     for (int k = 4; k > 1; --k)
-        if (fits(2, k)) return {2, k};
-    return l.storage == LBM_F64 || l.bnd ? BrickPlan{2, 2} : BrickPlan{1, 1};
+        if (fits(1, k)) return {1, k};
+    return l.storage == LBM_F64 || l.bnd ? BrickPlan{1, 2} : BrickPlan{0, 1};
 }
 
 // Units of a batch's work list that each XCD takes in a row, 0 to deal them to the XCDs

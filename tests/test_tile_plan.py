@@ -63,7 +63,8 @@ int main()
                     for (long long nx = 5; nx < 200000; nx += 1 + nx / 29) {
                         const BrickPlan b = brick_plan({(int)nx, ny, storage, 0.85, bnd != 0, cus});
                         const bool ok = b.steps ? b.steps <= 4 && brick_core(brick_rx(b.region), b.steps) > 0 &&
-                                                      brick_core(brick_ry(b.region), b.steps) > 0 && nx * ny < 1200000
+                                                      brick_core(brick_ry(b.region), b.steps) > 0 && nx * ny < 1200000 &&
+                                                      (b.region == 0 || (b.region == 1 && !(storage == LBM_F64 && bnd)))
                                                 : nx * ny > 500000;
                         ++n;
                         if (!ok && bad++ < 5)
