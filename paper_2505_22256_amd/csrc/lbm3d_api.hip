@@ -574,6 +574,8 @@ int lbm3d_contact_angle(lbm3d_ctx *c, int wall_kind, const double wall[4], doubl
     for (int q = 0; q < 4; ++q) wd.w[q] = wall[q];
     const lbm::RunSet rs = {nullptr, nullptr, c->nx, c->ny, c->nz};
     // labels and link list in the velocity part of the field staging
+    if (lbm::region_bytes(c->N, 1, 3) > (size_t)c->N * 3 * sizeof(double))
+        return fail(c, LBM_ENOMEM, "no room for the labels");
     const lbm::RegionMem m = lbm::region_mem(c->d_tmp + 2 * c->N, c->N, 1, 3);
     const double *r1 = c->d_tmp, *r2 = c->d_tmp + c->N;
     const dim3 lg = lbm::link_grid(c->N, 1);

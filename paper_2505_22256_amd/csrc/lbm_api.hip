@@ -893,6 +893,7 @@ int lbm_contact_angle(lbm_ctx *c, int wall_kind, const double wall[3], double *t
     const WallDesc wd = {wall_kind, wall[0], wall[1], wall[2]};
     const RunSet rs = {nullptr, nullptr, c->nx, c->ny, 1};
     // labels and link list in the velocity half of the field staging
+    if (region_bytes(c->N, 1, 2) > (size_t)c->N * 2 * sizeof(double)) return set_err(c, LBM_ENOMEM, "no room for the labels");
     const RegionMem m = region_mem(c->d_tmp + 2 * c->N, c->N, 1, 2);
     const double *r1 = c->d_tmp, *r2 = c->d_tmp + c->N;
     const dim3 lg = link_grid(c->N, 1);

@@ -698,6 +698,7 @@ int lbm_batch_contact_angles(lbm_batch *b, double *theta_deg)
     for (const BatchRun &br : b->runs) max_nodes = std::max(max_nodes, (long long)br.nx * br.ny);
     const RunSet rs = {b->d_dims, b->d_offs, 0, 0, 1};
     // labels and link lists in the velocity half of the fields
+    if (region_bytes(T, b->nruns, 2) > (size_t)T * 2 * sizeof(double)) return berr(b, LBM_ENOMEM, "no room for the labels");
     const RegionMem m = region_mem(b->d_fields + 2 * T, T, b->nruns, 2);
     const double *r1 = b->d_fields, *r2 = b->d_fields + T;
     const dim3 lg = link_grid(max_nodes, b->nruns);

@@ -20,7 +20,7 @@
 // memory: joined there, every walk up a chain of labels is a round trip to the
 // L2 per step, and a chain as long as the lattice is high.  The interface links
 // are compacted into a list, so that the fit reads a few hundred points and
-// not the lattice.  FIXME
+// not the lattice.
 #pragma once
 
 #include <hip/hip_runtime.h>
