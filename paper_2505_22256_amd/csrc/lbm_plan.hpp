@@ -37,11 +37,14 @@ struct PlanInput {
 // 604 / 520 / 509, BF16 613 / 520 / 505, FP64 (8192 x 2048) 820 / 774 / 702.
 // With open edges (us per step alone / with three lattices at a time, 8192 x
 // 1024): FP32 in 128 threads 233 / 174, in 256 226 / 162, FP64 - / 467 and 419;
-// 16-bit storage, whose default is one step in 128 threads, 232 / 185, two steps
-// in 64 threads and 24 rows 234 / 155, one step in 256 threads and 12 rows 210 /
-// 167.  Two steps need several rounds of wavefronts to be the better both ways
-// (9000 x 1400 305 / 229 against 305 / 253, 4000 x 1000 155 / 77 against 117 / 83,
-// 2000 x 600 103 / 41 against 66 / 31): three.
+// 16-bit storage, whose default is one step in 128 threads, 232 / 185, takes one
+// step in 256 threads and 12 rows, 201 / 165, or two in 64 threads and 24 rows, 206 /
+// 145.  The two-step kernel holds three wavefronts per SIMD, 3072 at once, and two
+// steps win three at a time from one such round on (BF16 6000 x 1000, 1.5 rounds, 153
+// / 120 one step, 162 / 104 two; 4000 x 1000, 1.03, 108 / 81 and 136 / 72) but lose
+// alone, less with every round and with a last one that is full (8192 x 1024 in 26
+// rows, 1.98 rounds, 206 / 147; 9000 x 1400 in 24, 3.2, 268 / 213 against 288 / 246):
+// the line lies where they win both ways, at three rounds.
 //
 // Rows: a segment is a serial march, so a lattice whose segments are fewer than
 // the wavefronts that hide a march's latency (one per SIMD, two in the light
@@ -83,15 +86,17 @@ inline Tile march_tile(const PlanInput &l, Tile t, bool two, bool record = false
         } else if (!l.bnd) {
             t = {128, 32, t.sched};
         } else {
+            // (units of one wavefront)
             const long long units = (long long)((l.nx + 53) / 54) * ((l.ny + 23) / 24);
-            t = two && units >= 9LL * simds ? Tile{64, 24, SCHED_TWO_STEP | SCHED_BANDS} : Tile{256, 12, SCHED_BANDS};
+            t = two && units >= 3 * 3LL * simds ? Tile{64, 24, SCHED_TWO_STEP | SCHED_BANDS} : Tile{256, 12, SCHED_BANDS};
         }
     }
     const int w = t.block - (t.sched & SCHED_TWO_STEP ? 10 : 4);
     const long long waves = (long long)((l.nx + w - 1) / w) * (t.block / 64);  // of one segment over the width
     long long segs = (l.ny + t.seg_rows - 1) / t.seg_rows;
     const long long least = half ? 2LL * simds : simds;
-    // wavefronts of the two-step kernels without boundary code that the registers hold at once
+    // wavefronts of the two-step kernels without boundary code that the registers hold at once: per
+    // SIMD one in FP64, two in FP32 and three in 16-bit storage, one more at relaxation time 1
     const long long held = (long long)simds * ((l.storage == LBM_F64 ? 1 : half ? 3 : 2) + (l.tau == 1.0));
     if (waves * segs < least) segs = std::max<long long>(segs, std::min<long long>(least / waves, l.ny / 8));
     else if (!l.bnd && (t.sched & SCHED_TWO_STEP) && waves <= held && waves * segs > held && 4 * waves * segs <= 5 * held) segs = held / waves;
