@@ -4,8 +4,8 @@
 One step = one lattice time step of the fused kernel (pull streaming with
 bounce-back, densities, E8 cohesion with the second-layer copy, local
 adhesion, body force, BGK-Guo collision, store), with the FP64 diagnostics
-fused into every 100th step.  With the FP32 default tile two steps run per
-launch (the first step's post-collision rows stay in LDS), so HBM moves
+fused into every 100th step.  Unless --tile names one, the library chooses the
+strips; on this lattice two steps run per launch (the first step's post-collision rows stay in LDS), so HBM moves
 fewer bytes per update than the one-step algorithmic count the roofline
 uses; `roofline.hbm_bytes_per_update` gives the measured figure.  Workload: the 16384 x 2048 walled microchannel
 with 64 square constrictions (side 128), two components as parallel streams,
@@ -74,11 +74,14 @@ def copy_bandwidth(nbytes: int = 1 << 31, repeats: int = 5):
     return round(2.0 * 4 * n / (best * 1e-3) / 1e9, 1)
 
 
+BY_LIBRARY = {"chosen_by": "library"}  # what ran where no tile was set: the rules of csrc/lbm_plan.hpp
+
+
 def kernel_source_hash() -> str:
     """Hash of the sources that define the step kernel and its launch
-    geometry (the tile is checked separately)."""
+    geometry (a tile set by hand is checked separately)."""
     h = hashlib.sha256()
-    for name in ("lbm_device.hpp", "lbm_kernels.hpp", "lbm_params.hpp"):
+    for name in ("lbm_device.hpp", "lbm_kernels.hpp", "lbm_params.hpp", "lbm_plan.hpp", "lbm_launch_impl.hpp", "lbm_api.hip"):
         with open(os.path.join(ROOT, "paper_2505_22256_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     # the compiler flags shape the kernels too
@@ -89,14 +92,15 @@ def kernel_source_hash() -> str:
 
 def measured_traffic(storage_name: str, tile):
     """HBM bytes per step launch from the committed rocprofv3 counter runs,
-    only while they were taken on the current kernel source and tile."""
+    only while they were taken on the current kernel source and tile (BY_LIBRARY, or
+    block, seg_rows and sched by name)."""
     try:
         with open(TRAFFIC_FILE) as f:
             rec = json.load(f)
     except (OSError, ValueError):
         return None
     ent = rec.get(storage_name)
-    if not ent or rec.get("kernel_hash") != kernel_source_hash() or list(ent.get("tile", [])) != list(tile):
+    if not ent or rec.get("kernel_hash") != kernel_source_hash() or ent.get("tile") != tile:
         return None
     return ent.get("bytes_per_launch")
 
@@ -392,7 +396,8 @@ def open_channel(args):
         ms = _timed_steps(lat, stream, steps, args.warmup)
         m = lat.reduce()
         out[name] = {"MLUPS": round(lat.fluid_nodes * steps / (ms * 1e-3) / 1e6, 1),
-                     "ms_per_step": round(ms / steps, 4), "tile": list(lat.get_tile()),
+                     "ms_per_step": round(ms / steps, 4),
+                     "tile": list(lat.get_tile()) if args.tile not in ("default", "auto") else BY_LIBRARY,
                      "mass1": float(m[0]), "mass2": float(m[1]), "max_u": float(m[4]),
                      "nonfinite": int(m[7])}
         lat.close()
@@ -527,7 +532,7 @@ def sphere_drop(args):
                        + rounding_label(args),
            "value": round(n_fluid / (ms_step * 1e-3) / 1e6, 1), "unit": "MLUPS", "fluid_nodes": n_fluid,
            "ms_per_step": round(ms_step, 5), "repeats_ms_per_step": [round(v, 5) for v in rep],
-           "tile": list(g.get_tile()),
+           "tile": list(g.get_tile()) if args.tile not in ("default", "auto") else BY_LIBRARY,
            "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": round(achieved / HBM_PEAK_GBS, 4), "bytes_per_update": bpu},
            "mass1": float(m[0]), "mass2": float(m[1]), "max_u": float(m[5]), "nonfinite": int(m[8])}
@@ -559,8 +564,8 @@ def main():
                     help="f16/bf16: round-to-nearest-even stores instead of the default stochastic rounding")
     ap.add_argument("--diag-every", type=int, default=100)
     ap.add_argument("--tile", default="default",
-                    help="default (the library's measured default for the storage), auto (autotune on the "
-                         "workload) or BLOCK,ROWS[,SCHED]")
+                    help="default (the library chooses), auto (the fastest tile that autotune finds on the "
+                         "workload, set) or BLOCK,ROWS[,SCHED]")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-accuracy", action="store_true")
     ap.add_argument("--workload", default="constrictions",
@@ -631,13 +636,15 @@ def main():
     lat = lbm.lattice_from_workload(wl, storage, flags)
     lat.set_stream(stream.cuda_stream)
     if args.tile == "default":
-        block, rows, sched = lat.get_tile()
-    elif args.tile == "auto":
-        block, rows, sched = lat.autotune(8)
+        sched, tile = lat.get_tile()[2], BY_LIBRARY
     else:
-        vals = [int(v) for v in args.tile.split(",")]
-        block, rows, sched = vals[0], vals[1], (vals[2] if len(vals) > 2 else 0)
+        if args.tile == "auto":
+            block, rows, sched = lat.autotune(8)
+        else:
+            vals = [int(v) for v in args.tile.split(",")]
+            block, rows, sched = vals[0], vals[1], (vals[2] if len(vals) > 2 else 0)
         lat.set_tile(block, rows, sched)
+        tile = {"block": block, "seg_rows": rows, "sched": sched}
     lat.set_diag_interval(args.diag_every)
     n_fluid = lat.fluid_nodes
     bpu = lat.bytes_per_update
@@ -665,8 +672,8 @@ def main():
     ms_step = float(np.median(rep_ms_step))
     mlups = n_fluid / (ms_step * 1e-3) / 1e6
     achieved = bpu * n_fluid / (ms_step * 1e-3) / 1e9
-    traffic = measured_traffic(args.storage + ("_rne" if args.nearest else ""), (block, rows, sched))
-    steps_per_launch = 2 if (sched & lbm.SCHED_TWO_STEP) and storage != lbm.F64 else 1
+    traffic = measured_traffic(args.storage + ("_rne" if args.nearest else ""), tile)
+    steps_per_launch = 2 if sched & lbm.SCHED_TWO_STEP else 1
     lat.close()
     copy_gbs = copy_bandwidth()
     # real HBM rate of the step kernel: counter bytes per launch over the
@@ -690,7 +697,7 @@ def main():
                                f"G_c=0.9 G_ads=0.15 tau=1 g=2e-6, {args.storage} storage"
                                + rounding_label(args),
                    "nx": wl.nx, "ny": wl.ny, "fluid_nodes": n_fluid, "storage": args.storage,
-                   "tile": {"block": block, "seg_rows": rows, "sched": sched},
+                   "tile": tile,
                    "diag_every": args.diag_every},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
