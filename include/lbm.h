@@ -257,9 +257,9 @@ int lbm_reduce(lbm_ctx *c, double out[8]);
  * lattice that needs more (the pass runs 252-column strips in segments of
  * the tile's seg_rows rows, 64 when that is 0: ceil(nx / 252) times
  * ceil(ny / seg_rows), rounded up to a multiple of 8, must not exceed
- * 16384; a small lattice runs shorter segments, at most one workgroup per
- * compute unit and strip more than there are compute units).  Every call on one GPU uses the same
- * array: calls that overlap in time on one GPU (other streams, other
+ * 16384; on a lattice whose segments are fewer than the compute units they are
+ * shorter, which takes no lattice past that limit).  Every call on one GPU uses
+ * the same array: calls that overlap in time on one GPU (other streams, other
  * contexts, other threads) race and must be serialised by the caller; the
  * array needs no clearing (every record is written before it is read).
  * ESTATE before initialisation; EINVAL for a null or misaligned d_out. */

@@ -144,8 +144,9 @@ hipError_t launch_pass(const KParams<typename Traits<S>::C> &p, Pass pass, int b
     if (pass == P_FIELDS) return launch_step_t<S, 256, M_BND | M_FIELDS>(p, st);
     if (pass == P_REDUCE) return launch_step_t<S, 256, M_BND | M_REDUCE>(p, st);
     if (pass == P_TABLES) return launch_step_t<S, 256, M_BND | M_TABLES>(p, st);
-    // (1 - omega is exactly 0; the diagnostic passes and the re-pull variant
-    // are not compiled for it and give the same results)
+    // (1 - omega is exactly 0; the blocks for which momenta do not pay, the
+    // diagnostic passes and the re-pull variant run the general kernels, with the
+    // same results)
     if (p.omw == 0 && (pass == P_STEP || pass == P_STEP2) && momenta_pay(S, block, pass == P_STEP2) && !(repull && !bnd))
         return launch_tau1<S>(p, pass, block, sr, bnd, st);
     return bnd ? launch_pass_b<S, M_BND>(p, pass, block, sr, st, false)

@@ -30,7 +30,7 @@ struct PlanInput {
 // storage's default `t` with two changes.
 //
 // Relaxation time 1: the kernels keep 4 values per row and component pair
-// instead of 18 (FP32 119 registers against 203, FP64 211 against 256 and 119
+// instead of 18 (FP32 119 registers against 203, FP64 210 against 256 and 122
 // accumulation registers), so more wavefronts share a SIMD and wider strips
 // pay.  16384 x 2048 channel, us per step, general kernels in the default tile
 // / relaxation time 1 in that tile / in this one: FP32 737 / 702 / 653, FP16
